@@ -14,6 +14,7 @@
 #include "fx_tables.h"
 #include "kernels.h"
 #include "plan.h"
+#include "split_shape.h"
 
 using moff::GatherEntry;
 using moff::HostPlan;
@@ -38,6 +39,11 @@ struct moff_plan_s {
   int* d_ktype_off = nullptr;
   GatherEntry* d_mfma_prog = nullptr;   // reduced-precision path (MOFF_MFMA_*)
   uint16_t* d_mfma_dft = nullptr;
+  uint4* d_split_prog = nullptr;        // matrix-core float32 path (HostPlan::Split)
+  float2* d_split_progi = nullptr;
+  uint32_t* d_split_ends = nullptr;
+  int* d_split_steps = nullptr;
+  uint16_t* d_split_coef = nullptr;
   double* d_Pn = nullptr;               // uv-plane autocorrelation rule (MOFF_AUTOCORR_UV)
   uint32_t* d_adj_slots[moff::kMaxVariants] = {};   // fused adjoint: antennas per lane; null if they do not fit
   // visibility route (moff_image_fx), built on first use
@@ -120,7 +126,8 @@ void free_device(moff_plan p) {
   void* ptrs[] = {p->d_tw,        p->d_Pp,        p->d_ant_type, p->d_ktab,        p->d_csr_ptr,
                   p->d_csr_ant,   p->d_csr_tap,   p->d_ant_cells, p->d_ktype_k,    p->d_ktype_off,
                   p->d_mfma_prog, p->d_mfma_dft,  p->d_Pn,        p->d_ws,         p->d_aux,
-                  p->d_fx_ptr,    p->d_fx_ab,     p->d_fx_x};
+                  p->d_fx_ptr,    p->d_fx_ab,     p->d_fx_x,     p->d_split_prog,  p->d_split_progi,
+                  p->d_split_ends, p->d_split_steps, p->d_split_coef};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
   for (int v = 0; v < moff::kMaxVariants; ++v) {
@@ -196,6 +203,11 @@ constexpr float kTuneSlack = 0.03f;   // calls this much slower than the fastest
 
 bool is_mfma(const HostPlan& hp) { return hp.mfma.prec != 0; }
 
+// The matrix-core float32 kernel is the shape variant after the FFT kernel's.
+bool is_split(const HostPlan& hp, int variant) {
+  return hp.split.on && variant == static_cast<int>(hp.variants.size());
+}
+
 // Work items per time slice, LDS bytes and resident workgroups of a variant.
 struct KernelFootprint {
   int per_slice;
@@ -214,6 +226,11 @@ KernelFootprint footprint(moff_plan p, int variant) {
     f.lds = moff::mfma_lds_bytes(hp.N, hp.n_taps, hp.n_ant, hp.mfma.prog_len, in_lds);
     f.resident = std::max(1, moff::mfma_blocks_per_cu(hp.N, hp.mfma.prec, ci4, f.lds)) * std::max(1, p->cu_count);
     f.threads = moff::mfma_threads(hp.N);
+  } else if (is_split(hp, variant)) {
+    f.per_slice = hp.n_chan;
+    f.lds = static_cast<size_t>(moff::split_layout(hp.N, hp.n_ant).end);
+    f.resident = std::max(1, moff::split_blocks_per_cu(hp.N, ci4, !hp.split.real, hp.n_ant)) * std::max(1, p->cu_count);
+    f.threads = moff::split_shape(hp.N).NW * 64;
   } else {
     const HostPlan::Variant& V = hp.variants[variant];
     f.per_slice = V.shape.SX * hp.n_chan;
@@ -224,7 +241,9 @@ KernelFootprint footprint(moff_plan p, int variant) {
   return f;
 }
 
-int n_variants(const HostPlan& hp) { return is_mfma(hp) ? 1 : static_cast<int>(hp.variants.size()); }
+int n_variants(const HostPlan& hp) {
+  return is_mfma(hp) ? 1 : static_cast<int>(hp.variants.size()) + (hp.split.on ? 1 : 0);
+}
 
 // Workgroups of a fused launch with `slices` time slices.  The float32 kernel
 // places the column classes of one (channel, slice) on one XCD and pads the
@@ -233,6 +252,7 @@ int n_variants(const HostPlan& hp) { return is_mfma(hp) ? 1 : static_cast<int>(h
 int launch_grid(const HostPlan& hp, int variant, int slices) {
   if (is_mfma(hp)) return hp.n_chan * slices;
   const int cs = hp.n_chan * slices;
+  if (is_split(hp, variant)) return (cs + moff::kXcds - 1) / moff::kXcds * moff::kXcds;
   return hp.variants[variant].shape.SX * ((cs + moff::kXcds - 1) / moff::kXcds * moff::kXcds);
 }
 
@@ -300,6 +320,29 @@ moff::MfmaArgs mfma_args(moff_plan p, const void* E, int64_t n_time, const float
   return a;
 }
 
+moff::SplitArgs split_args(moff_plan p, const void* E, int64_t n_time, const float* gains) {
+  const HostPlan& hp = p->hp;
+  moff::SplitArgs a{};
+  a.E = E;
+  a.gains = reinterpret_cast<const float2*>(gains);
+  a.prog = p->d_split_prog;
+  a.progi = p->d_split_progi;
+  a.ends = p->d_split_ends;
+  a.n_steps = p->d_split_steps;
+  a.steps = hp.split.steps;
+  (void)std::frexp(hp.split.wmax, &a.wexp);
+  a.coef = p->d_split_coef;
+  a.ant_type = p->d_ant_type;
+  a.n_ant = hp.n_ant;
+  a.n_chan = hp.n_chan;
+  a.n_types = hp.n_ktypes;
+  a.n_time = n_time;
+  a.Pp = p->d_Pp;
+  a.subtract = (hp.flags & MOFF_AUTOCORR_NONE) ? 0 : 1;
+  a.minus_one = -1.f;
+  return a;
+}
+
 // One launch of the plan's fused kernel (float32 FFT or reduced-precision MFMA
 // transform) writing `out` / `outA` in epilogue `mode`.
 hipError_t launch_fused_kernel(moff_plan p, const LaunchConfig& lc, const void* E, int64_t n_time,
@@ -315,6 +358,16 @@ hipError_t launch_fused_kernel(moff_plan p, const LaunchConfig& lc, const void* 
     a.outA = outA;
     a.mode = mode;
     return moff::launch_mfma(a, hp.N, hp.mfma.prec, ci4, lc.grid, st);
+  }
+  if (is_split(hp, lc.variant)) {
+    moff::SplitArgs a = split_args(p, E, n_time, gains);
+    a.slices = lc.slices;
+    a.scale = image_scale(hp, n_time);
+    a.out = out;
+    a.outA = outA;
+    a.mode = mode;
+    a.acc64 = run64;
+    return moff::launch_split(a, hp.N, ci4, lc.grid, st);
   }
   moff::FusedArgs a = fused_args(p, lc.variant, E, n_time, gains);
   a.progress_prio = footprint(p, lc.variant).resident > std::max(1, p->cu_count) ? 1 : 0;
@@ -344,7 +397,8 @@ FusedScratch fused_scratch(const HostPlan& hp, const LaunchConfig& lc, int64_t n
   }
   const int64_t longest = (n_time + lc.slices - 1) / lc.slices;
   if (!is_mfma(hp) && longest > moff::kBlockFrames)
-    f.run_bytes = sizeof(double) * moff::fused_lane_values(hp.N, lc.variant) * hp.n_chan * lc.slices;
+    f.run_bytes = sizeof(double) * hp.n_chan * lc.slices *
+                  (is_split(hp, lc.variant) ? static_cast<size_t>(hp.N) * hp.N : moff::fused_lane_values(hp.N, lc.variant));
   return f;
 }
 
@@ -614,6 +668,15 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
       up(upload(&p->d_mfma_prog, hp.mfma.prog.data(), sizeof(GatherEntry) * hp.mfma.prog.size()));
       up(upload(&p->d_mfma_dft, hp.mfma.dft.data(), sizeof(uint16_t) * hp.mfma.dft.size()));
     }
+    if (hp.split.on) {
+      const HostPlan::Split& T = hp.split;
+      up(upload(&p->d_split_prog, T.prog.data(), sizeof(uint32_t) * T.prog.size()));
+      if (!T.real) up(upload(&p->d_split_progi, T.progi.data(), sizeof(float) * T.progi.size()));
+      up(upload(&p->d_split_ends, T.ends.data(), sizeof(uint32_t) * T.ends.size()));
+      up(upload(&p->d_split_steps, T.n_steps.data(), sizeof(int32_t) * T.n_steps.size()));
+      up(upload(&p->d_split_coef, T.coef.data(), sizeof(uint16_t) * T.coef.size()));
+      p->variant = static_cast<int>(hp.variants.size());
+    }
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, hip_device) == hipSuccess) p->cu_count = prop.multiProcessorCount;
     if (hip_device < kMaxDevices) {
@@ -837,7 +900,7 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
   struct Timed {
     int v, sl;
     float ms;
-  } timed[moff::kMaxVariants * 11];
+  } timed[(moff::kMaxVariants + 1) * 11];
   int n_timed = 0;
   moff_status result = MOFF_OK;
   {
@@ -926,7 +989,7 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
     if (hipMalloc(reinterpret_cast<void**>(&grad), sizeof(float) * 2 * hp.n_chan * hp.n_ant) != hipSuccess)
       result = MOFF_ERR_NOMEM;
     float best_adj = 1e30f;
-    for (int av = 0; av < n_variants(hp) && result == MOFF_OK; ++av) {
+    for (int av = 0; av < static_cast<int>(hp.variants.size()) && result == MOFF_OK; ++av) {
       const size_t alds = moff::fused_lds_bytes(hp.N, av, hp.variants[av].n_weights(), hp.n_ant);
       if (!p->d_adj_slots[av] || alds > size_t(159) * 1024) continue;
       for (int wv = 1; wv <= wmax && result == MOFF_OK; ++wv) {

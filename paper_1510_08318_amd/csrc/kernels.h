@@ -162,6 +162,35 @@ struct MfmaArgs {
   int mode;
 };
 
+// Matrix-core float32 kernel (split.hip): one workgroup per (channel, time
+// slice); same epilogue modes and outputs as FusedArgs.
+struct SplitArgs {
+  const void* E;               // [T][C][n_ant] c64 or ci4
+  const float2* gains;         // [C][n_ant] or nullptr
+  const uint4* prog;           // HostPlan::Split::prog
+  const float2* progi;         // HostPlan::Split::progi, or nullptr (real tables)
+  const uint32_t* ends;
+  const int* n_steps;
+  int steps;
+  int wexp;                    // wmax <= 2^wexp
+  const uint16_t* coef;
+  const int* ant_type;
+  int n_ant, n_chan, n_types;
+  int64_t n_time;
+  int slices;
+  float* out;
+  double* outA;
+  const double* Pp;
+  double scale;
+  int subtract;
+  int mode;
+  double* acc64;               // [items][N^2] running sums when a slice is longer than kBlockFrames
+  float minus_one;             // -1 (see split2)
+};
+// grid: workgroups, a multiple of kXcds covering every (channel, slice)
+hipError_t launch_split(const SplitArgs& a, int N, bool ci4, int grid, hipStream_t st);
+int split_blocks_per_cu(int N, bool ci4, bool cw, int n_ant);
+
 size_t mfma_lds_bytes(int N, int n_taps, int n_ant, int prog_len, bool prog_in_lds);
 bool mfma_prog_in_lds(int N, int n_taps, int n_ant, int prog_len);
 int mfma_threads(int N);

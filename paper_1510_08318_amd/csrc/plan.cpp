@@ -219,6 +219,19 @@ uint16_t to_bfloat16(double x) {
   return static_cast<uint16_t>(bits >> 16);
 }
 
+double from_binary16(uint16_t h) {
+  const int ex = (h >> 10) & 31;
+  const double m = (h & 1023) / 1024.0;
+  const double v = ex ? std::ldexp(1.0 + m, ex - 15) : std::ldexp(m, -14);
+  return (h & 0x8000u) ? -v : v;
+}
+
+uint32_t float_bits(float x) {
+  uint32_t b = 0;
+  std::memcpy(&b, &x, sizeof(b));
+  return b;
+}
+
 moff_status build_host_plan(const moff_geometry* g, HostPlan* hp, std::string* why) {
   if (!g || !hp) return fail(why, MOFF_ERR_INVALID_ARG, "null geometry or plan");
   if (g->n_ant < 2 || g->n_ant > kMaxAnt) return fail(why, MOFF_ERR_INVALID_ARG, "n_ant out of [2, 4000]");
@@ -613,6 +626,8 @@ moff_status build_host_plan(const moff_geometry* g, HostPlan* hp, std::string* w
   if (P.flags & (MOFF_MFMA_F16 | MOFF_MFMA_BF16)) {
     moff_status s = build_mfma_tables(P, why);
     if (s != MOFF_OK) return s;
+  } else {
+    build_split_tables(P);
   }
   return MOFF_OK;
 }

@@ -36,6 +36,8 @@ constexpr uint32_t kFirstBit = 0x40000000u;
 //      table, bits 24..27 table side k;   w1 = ix0 | iy0 << 16.
 constexpr int kAdjSlots = 4;
 constexpr uint32_t kAdjEmpty = 0xFFFu;
+// Steps per batch of the matrix-core float32 kernel's gather programs.
+constexpr int kSplitBatch = 4;
 constexpr int kMaxAnt = 4000;
 constexpr int kMaxTypes = 4;
 constexpr int kMaxK = 15;
@@ -94,6 +96,20 @@ struct HostPlan {
     std::vector<uint32_t> slots;             // [NT][kAdjSlots][2]; empty if the antennas do not fit
   };
   std::vector<Variant> variants;
+
+  // matrix-core float32 frame transform (split.hip, split_tables.cpp); a shape
+  // variant of its own after the entries of `variants`
+  struct Split {
+    bool on = false;                         // built for this grid and antenna count
+    bool real = true;                        // real illumination tables: progi is empty
+    int steps = 0;                           // program length allotted per wave
+    std::vector<int32_t> n_steps;            // [waves] steps in use
+    std::vector<uint32_t> prog;              // [waves][steps / 2][64][2] x (8 slot | grid byte << 16, weight bits)
+    std::vector<float> progi;                // [waves][steps / 2][64][2] imaginary weights
+    std::vector<uint32_t> ends;              // [waves][(steps + 31) / 32] bit s: step s ends its cells
+    std::vector<uint16_t> coef;              // phase factors, see build_split_tables
+    double wmax = 1.0;                       // largest folded value per unit of the largest sample component
+  } split;
   int max_cell_entries = 0;
 
   // reduced-precision frame transform (MOFF_MFMA_*): dense DFT matrices on the
@@ -109,6 +125,11 @@ struct HostPlan {
 // 16-bit encodings of a float64 value, rounded to nearest (ties to even).
 uint16_t to_binary16(double x);
 uint16_t to_bfloat16(double x);
+double from_binary16(uint16_t h);   // finite values
+uint32_t float_bits(float x);
+
+// Tables of the matrix-core float32 transform, from the finished CSR (split_tables.cpp).
+void build_split_tables(HostPlan& P);
 
 // Validate the geometry and build every host table.  Returns MOFF_OK or the
 // status describing the first problem; `why` gets a human-readable reason.
