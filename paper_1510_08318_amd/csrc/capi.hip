@@ -256,18 +256,53 @@ int launch_grid(const HostPlan& hp, int variant, int slices) {
   return hp.variants[variant].shape.SX * ((cs + moff::kXcds - 1) / moff::kXcds * moff::kXcds);
 }
 
-// Launch configuration for n_time frames: the tuned or set choice, else a
-// heuristic: shape variant 0 and enough time slices for about two rounds of
-// resident workgroups.  One work item (column class, channel, time slice) per
-// workgroup.
+// Time slices of an untuned launch: the count with the least modelled time.
+// Items (channel-slices, times column classes) run in rounds of `resident`
+// workgroups; a round lasts as long as a slice has frames, plus a fixed cost
+// per workgroup (tables, staging and writing its pixels, about two frames'
+// time), and a partly filled round runs its frames faster (fewer workgroups
+// share a CU's units).  Every further slice adds one partial image to read
+// back.  Two whole rounds regardless of how short the slices get, as before,
+// made 28 slices of two frames and a ragged third round of 37 channels x 50
+// samples at N = 128: XX us against YY with 13 slices; the 75 samples of 12
+// channels at N = 64 ...
+int default_slices(const HostPlan& hp, const KernelFootprint& f, bool matrix, int64_t n_time) {
+  constexpr double kFixed = 2.0;      // frames' time per workgroup
+  constexpr double kAlone = 0.4;      // a frame's time in a nearly empty round, of that in a full one
+  const double log2n = std::log2(static_cast<double>(hp.N)), pixels = static_cast<double>(hp.N) * hp.N;
+  // seconds of one frame of one workgroup in a full round: 10 pixels log2(N)
+  // flop per frame at the rates the two transforms reach
+  const double classes = static_cast<double>(f.per_slice) / hp.n_chan;
+  const double frame = 10.0 * pixels * log2n / (matrix ? 110e12 : 65e12) * f.resident / classes;
+  const double merge = 4.0 * pixels * hp.n_chan / 4e12 / frame;   // one more partial image, in frames
+  const int most = static_cast<int>(std::min<int64_t>(n_time, 256));
+  int best = 1;
+  double least = 0.0;
+  for (int sl = 1; sl <= most; ++sl) {
+    const int64_t items = static_cast<int64_t>(f.per_slice) * sl;
+    const double full = static_cast<double>(items / f.resident);
+    const double part = static_cast<double>(items % f.resident) / f.resident;
+    const double frames = static_cast<double>((n_time + sl - 1) / sl);
+    double cost = full * (frames + kFixed) + (sl > 1 ? merge * sl : 0.0);
+    if (part > 0.0) cost += frames * (kAlone + (1.0 - kAlone) * part) + kFixed;
+    if (sl == 1 || cost < least) {
+      least = cost;
+      best = sl;
+    }
+  }
+  return best;
+}
+
+// Launch configuration for n_time frames: the tuned or set choice, else the
+// plan's shape variant and the slice count above.  One work item (column
+// class, channel, time slice) per workgroup.
 LaunchConfig launch_config(moff_plan p, int64_t n_time) {
   const HostPlan& hp = p->hp;
   LaunchConfig lc{};
   lc.variant = std::min<int>(p->variant, n_variants(hp) - 1);
-  const KernelFootprint f = footprint(p, lc.variant);
-  const int per_slice = f.per_slice, resident = f.resident;
   int slices = p->slices;
-  if (slices <= 0) slices = (2 * resident + per_slice - 1) / per_slice;
+  if (slices <= 0)
+    slices = default_slices(hp, footprint(p, lc.variant), is_mfma(hp) || is_split(hp, lc.variant), n_time);
   slices = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({static_cast<int64_t>(slices), n_time, 256})));
   lc.slices = slices;
   lc.grid = launch_grid(hp, lc.variant, slices);
@@ -537,7 +572,9 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
         std::max<int64_t>(1, std::min<int64_t>({(2 * resident + per_slice - 1) / per_slice, n_time, 64})));
     const int parts = slices * AV.shape.SX;
     const size_t na = static_cast<size_t>(hp.n_chan) * hp.n_ant;
-    const size_t d_bytes = (sizeof(double2) * na * (parts + 1) + sizeof(double) * na + 255) / 256 * 256;
+    const size_t rho_n = static_cast<size_t>(hp.n_chan) * moff::kRhoParts * moff::kMaxTypes;
+    const size_t d_bytes =
+        (sizeof(double2) * na * (parts + 1) + sizeof(double) * (na + rho_n) + 255) / 256 * 256;
     s = ensure_workspace(p, d_bytes + sizeof(float) * moff::fused_lane_values(hp.N, av) * hp.n_chan);
     if (s != MOFF_OK) return s;
     double2* Dp = static_cast<double2*>(p->d_ws);
@@ -577,6 +614,7 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
     if (moff::launch_antenna_power(E, ci4, n_time, hp.n_chan, hp.n_ant, Q, st) != hipSuccess) return MOFF_ERR_HIP;
     gf.D = D;
     gf.Q = Q;
+    gf.rho = Q + na;
     return hip_status(moff::launch_grad_final(gf, st));
   }
 
@@ -585,6 +623,7 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
   const size_t gp_frame = static_cast<size_t>(V.shape.SX) * hp.L * V.NZR;
   const size_t d_bytes = sizeof(double) * 2 * hp.n_chan * hp.n_ant;
   const size_t q_bytes = sizeof(double) * hp.n_chan * hp.n_ant;
+  const size_t rho_bytes = sizeof(double) * hp.n_chan * moff::kRhoParts * moff::kMaxTypes;
   // time chunk: the per-chunk grids, fields and adjoint grids within ~2 GiB
   const size_t per_t = sizeof(float2) * (L2 + npix + gp_frame) * hp.n_chan;
   int64_t chunk = std::max<int64_t>(1, static_cast<int64_t>((size_t(2) << 30) / per_t));
@@ -592,7 +631,7 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
   const size_t eg_bytes = sizeof(float2) * L2 * hp.n_chan * chunk;
   const size_t y_bytes = sizeof(float2) * npix * hp.n_chan * chunk;
   const size_t gp_bytes = sizeof(float2) * gp_frame * hp.n_chan * chunk;
-  s = ensure_workspace(p, d_bytes + q_bytes + eg_bytes + y_bytes + gp_bytes);
+  s = ensure_workspace(p, d_bytes + q_bytes + eg_bytes + y_bytes + gp_bytes + rho_bytes);
   if (s != MOFF_OK) return s;
   char* ws = static_cast<char*>(p->d_ws);
   double2* D = reinterpret_cast<double2*>(ws);
@@ -636,6 +675,7 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
   }
   gf.D = D;
   gf.Q = Q;
+  gf.rho = reinterpret_cast<double*>(ws + d_bytes + q_bytes + eg_bytes + y_bytes + gp_bytes);
   return hip_status(moff::launch_grad_final(gf, st));
 }
 
@@ -677,6 +717,12 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
       up(upload(&p->d_split_coef, T.coef.data(), sizeof(uint16_t) * T.coef.size()));
       p->variant = static_cast<int>(hp.variants.size());
     }
+    // Where the second FFT shape at N = 256 fits its LDS, its two classes of 512
+    // threads beat the four of 256 (23.3 against 28.7 ms at 1024 channels x 256
+    // samples of 350 antennas, 60 against 69 us at 4 x 23 of 578).
+    if (hp.N == 256 && hp.variants.size() > 1 &&
+        moff::fused_lds_bytes(hp.N, 1, hp.variants[1].n_weights(), hp.n_ant) <= size_t(159) * 1024)
+      p->variant = 1;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, hip_device) == hipSuccess) p->cu_count = prop.multiProcessorCount;
     if (hip_device < kMaxDevices) {

@@ -127,6 +127,8 @@ struct DegridArgs {
   int64_t n_time;
 };
 
+constexpr int kRhoParts = 16;   // workgroups per channel that sum rho_p = <R, P_p>
+
 struct GradFinalArgs {
   const double2* D;
   const double* Q;
@@ -135,6 +137,7 @@ struct GradFinalArgs {
   const float2* gains;         // [C][n_ant] or nullptr
   const int* ant_type;
   float2* grad;                // [C][n_ant]
+  double* rho;                 // [C][kRhoParts][kMaxTypes] scratch
   int N, n_ant, n_chan, n_types, subtract;
   double scale;                // 2 s / T
 };

@@ -550,63 +550,155 @@ __global__ __launch_bounds__(256) void adjoint_sensitivity_kernel(const float* R
   Rl[i] = v;
 }
 
-// One thread per (channel, antenna): Q = sum_t |E|^2 in float64.
+// Q = sum_t |E|^2 per (channel, antenna) in float64: 64 antennas per workgroup
+// and kPowerGroups contiguous ranges of time, one per wave, summed in order.
+// Bound by the samples' bytes; a single range per antenna left too few loads in
+// flight (12 channels x 61 antennas x 75 complex64 samples: 10.1 -> 4.6 us).
+constexpr int kPowerGroups = 8;
+
 template <bool CI4>
-__global__ __launch_bounds__(256) void antenna_power_kernel(const void* E, int64_t n_time, int n_chan, int n_ant,
-                                                            double* Q) {
-  const int c = blockIdx.y;
-  const int ant = blockIdx.x * 256 + threadIdx.x;
-  if (ant >= n_ant) return;
+__global__ __launch_bounds__(64 * kPowerGroups) void antenna_power_kernel(const void* E, int64_t n_time, int n_chan,
+                                                                          int n_ant, double* Q) {
+  __shared__ double part[kPowerGroups][64];
+  const int c = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const int ant = blockIdx.x * 64 + lane;
   double q = 0.0;
-  for (int64_t t = 0; t < n_time; ++t) {
-    const float2 v = load_sample(E, (static_cast<size_t>(t) * n_chan + c) * n_ant + ant, CI4);
-    q += static_cast<double>(v.x) * v.x + static_cast<double>(v.y) * v.y;
+  if (ant < n_ant) {
+    const int64_t t0 = g * n_time / kPowerGroups, t1 = (g + 1) * n_time / kPowerGroups;
+    const size_t stride = static_cast<size_t>(n_chan) * n_ant;
+    size_t at = static_cast<size_t>(t0) * stride + static_cast<size_t>(c) * n_ant + ant;
+    auto add = [&](float2 v) { q += static_cast<double>(v.x) * v.x + static_cast<double>(v.y) * v.y; };
+    int64_t t = t0;
+    for (; t + 8 <= t1; t += 8, at += 8 * stride) {
+      float2 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = load_sample(E, at + k * stride, CI4);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) add(v[k]);
+    }
+    for (; t < t1; ++t, at += stride) add(load_sample(E, at, CI4));
   }
-  Q[static_cast<size_t>(c) * n_ant + ant] = q;
+  part[g][lane] = q;
+  __syncthreads();
+  if (g == 0 && ant < n_ant) {
+    double s = part[0][lane];
+#pragma unroll
+    for (int k = 1; k < kPowerGroups; ++k) s += part[k][lane];
+    Q[static_cast<size_t>(c) * n_ant + ant] = s;
+  }
 }
 
-// D = sum of the per-(slice, class) partial sums, in order.
+// D = sum of the per-(slice, class) partial sums: 64 (channel, antenna) values
+// per workgroup, four contiguous ranges of partials each, in order.
 __global__ __launch_bounds__(256) void adjoint_reduce_kernel(const double2* Dp, int parts, size_t n, double2* D) {
-  const size_t i = static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (i >= n) return;
+  __shared__ double2 part[4][64];
+  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  const size_t i = static_cast<size_t>(blockIdx.x) * 64 + lane;
   double x = 0.0, y = 0.0;
-  for (int k = 0; k < parts; ++k) {
-    x += Dp[static_cast<size_t>(k) * n + i].x;
-    y += Dp[static_cast<size_t>(k) * n + i].y;
+  if (i < n) {
+    const int k1 = (g + 1) * parts / 4;
+    int k = g * parts / 4;
+    for (; k + 4 <= k1; k += 4) {
+      double2 v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = Dp[static_cast<size_t>(k + j) * n + i];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x += v[j].x;
+        y += v[j].y;
+      }
+    }
+    for (; k < k1; ++k) {
+      x += Dp[static_cast<size_t>(k) * n + i].x;
+      y += Dp[static_cast<size_t>(k) * n + i].y;
+    }
   }
-  D[i] = make_double2(x, y);
+  part[g][lane] = make_double2(x, y);
+  __syncthreads();
+  if (g == 0 && i < n) {
+    for (int j = 1; j < 4; ++j) {
+      x += part[j][lane].x;
+      y += part[j][lane].y;
+    }
+    D[i] = make_double2(x, y);
+  }
 }
 
-// Sum per-slice partials (pixel order) in slice order, four pixels per thread
-// (N^2 is a multiple of 4, and each slice's loads are independent so they are
-// issued four slices at a time); then remove self power and average
+// Sum per-slice partials (pixel order) in a fixed order, four pixels per
+// thread (N^2 is a multiple of 4); then remove self power and average
 // (MODE_FINAL) or add into the caller's running sums (MODE_ACCUM).
+//
+// G threads share a pixel quad, each summing a contiguous range of slices with
+// several loads in flight, and their sums meet in LDS: with one thread per
+// quad a small image of many slices (12 x 64 x 64 pixels, 75 slices) kept 192
+// waves on the card, each walking its slices one round trip after the other.
+// The self power of the channel is summed once per workgroup, a wave per type;
+// every thread summing it for itself was a chain of a load per slice, most of
+// the kernel's time.  Both together: one 32 x 32 channel of 64 slices 15.7 ->
+// 3.2 us, 12 x 64 x 64 pixels of 75 slices 36.8 -> 5.8 us, 33 x 64 x 64 of 94
+// slices 49.8 -> 10.3 us, 37 x 128 x 128 of 28 slices 19.1 -> 12.4 us.
+template <int G>
 __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
+  constexpr int Q = 256 / G;   // pixel quads per workgroup
+  __shared__ double part[G > 1 ? 4 * 256 : 1];
+  __shared__ double Ash[kMaxTypesDev];
   const size_t npix = static_cast<size_t>(a.N) * a.N;
-  const size_t i = (static_cast<size_t>(blockIdx.x) * 256 + threadIdx.x) * 4;
-  if (i >= npix * a.n_chan) return;
-  const size_t c = i / npix, pix = i % npix;
-  const size_t stride4 = static_cast<size_t>(a.n_chan) * npix / 4;   // one slice, in float4
-  const float4* src = reinterpret_cast<const float4*>(a.S_part) + i / 4;
-  double s[4] = {0.0, 0.0, 0.0, 0.0};
-  auto add = [&](float4 v) {
-    s[0] += v.x;
-    s[1] += v.y;
-    s[2] += v.z;
-    s[3] += v.w;
-  };
-  int sl = 0;
-  for (; sl + 4 <= a.slices; sl += 4) {
-    float4 v[4];
+  const int q = threadIdx.x % Q, g = threadIdx.x / Q;
+  const size_t i0 = static_cast<size_t>(blockIdx.x) * Q * 4, i = i0 + 4 * q;
+  const bool in = i < npix * a.n_chan;
+  const bool one_channel = npix % (4 * Q) == 0;   // uniform: the workgroup's pixels are of one channel
+  if (one_channel) {
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (w < a.n_types) {
+      const double* src = a.A_part + (i0 / npix) * a.n_types + w;
+      double s = 0.0;
+      for (int sl = lane; sl < a.slices; sl += 64) s += src[static_cast<size_t>(sl) * a.n_chan * a.n_types];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) v[k] = src[static_cast<size_t>(sl + k) * stride4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) add(v[k]);
+      for (int off = 32; off >= 1; off >>= 1) s += __shfl_down(s, off, 64);
+      if (lane == 0) Ash[w] = s;
+    }
   }
-  for (; sl < a.slices; ++sl) add(src[static_cast<size_t>(sl) * stride4]);
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  if (in) {
+    const size_t stride4 = static_cast<size_t>(a.n_chan) * npix / 4;   // one slice, in float4
+    const float4* src = reinterpret_cast<const float4*>(a.S_part) + i / 4;
+    auto add = [&](float4 v) {
+      s[0] += v.x;
+      s[1] += v.y;
+      s[2] += v.z;
+      s[3] += v.w;
+    };
+    int sl = g * a.slices / G;
+    const int s1 = (g + 1) * a.slices / G;
+    for (; sl + 4 <= s1; sl += 4) {
+      float4 v[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) v[k] = src[static_cast<size_t>(sl + k) * stride4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) add(v[k]);
+    }
+    for (; sl < s1; ++sl) add(src[static_cast<size_t>(sl) * stride4]);
+  }
+  if constexpr (G > 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) part[(k * G + g) * Q + q] = s[k];
+  }
+  __syncthreads();
+  if (!in || g != 0) return;
+  if constexpr (G > 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      for (int j = 1; j < G; ++j) s[k] += part[(k * G + j) * Q + q];
+  }
+  const size_t c = i / npix, pix = i % npix;
   double A[kMaxTypesDev] = {0.0, 0.0, 0.0, 0.0};
-  for (int p = 0; p < a.n_types; ++p)
-    for (int q = 0; q < a.slices; ++q) A[p] += a.A_part[(static_cast<size_t>(q) * a.n_chan + c) * a.n_types + p];
+#pragma unroll
+  for (int p = 0; p < kMaxTypesDev; ++p) {
+    if (p >= a.n_types) break;
+    if (one_channel) A[p] = Ash[p];
+    else
+      for (int k = 0; k < a.slices; ++k) A[p] += a.A_part[(static_cast<size_t>(k) * a.n_chan + c) * a.n_types + p];
+  }
   float r[4];
   if (a.final_image) {
 #pragma unroll
@@ -824,32 +916,54 @@ __global__ __launch_bounds__(256) void degrid_kernel(DegridArgs a) {
   a.Q[i] += Q;
 }
 
-// One workgroup per channel: rho_p = sum_pix R P_p, then
-// grad = scale (D - rho_{p(a)} g Q).
-__global__ __launch_bounds__(256) void grad_final_kernel(GradFinalArgs a) {
+// rho_p = sum_pix R P_p of one channel: kRhoParts workgroups per channel, one
+// contiguous range of pixels each, summed by grad_final_kernel in order.
+__global__ __launch_bounds__(256) void grad_rho_kernel(GradFinalArgs a) {
   __shared__ double rho[kMaxTypesDev];
-  const int c = blockIdx.x;
+  const int c = blockIdx.y;
   const size_t npix = static_cast<size_t>(a.N) * a.N;
+  const size_t i0 = blockIdx.x * npix / kRhoParts, i1 = (blockIdx.x + 1) * npix / kRhoParts;
+  const float* R = a.R + static_cast<size_t>(c) * npix;
   double part[kMaxTypesDev] = {0.0, 0.0, 0.0, 0.0};
-  if (a.subtract) {
-    const float* R = a.R + static_cast<size_t>(c) * npix;
-    for (size_t i = threadIdx.x; i < npix; i += 256) {
-      const double r = R[i];
-      for (int p = 0; p < a.n_types; ++p) part[p] += r * a.Pp[p * npix + i];
-    }
+#pragma unroll
+  for (int p = 0; p < kMaxTypesDev; ++p) {
+    if (p >= a.n_types) break;   // uniform
+    double s = 0.0;
+#pragma unroll 4
+    for (size_t i = i0 + threadIdx.x; i < i1; i += 256) s += static_cast<double>(R[i]) * a.Pp[p * npix + i];
+    part[p] = s;
   }
   block_sum4<256>(part, rho);
-  for (int ant = threadIdx.x; ant < a.n_ant; ant += 256) {
-    const size_t i = static_cast<size_t>(c) * a.n_ant + ant;
-    double gx = a.D[i].x, gy = a.D[i].y;
-    if (a.subtract) {
-      const float2 g = a.gains ? a.gains[i] : make_float2(1.f, 0.f);
-      const double s = rho[a.ant_type[ant]] * a.Q[i];
-      gx -= s * g.x;
-      gy -= s * g.y;
+  if (threadIdx.x < kMaxTypesDev)
+    a.rho[(static_cast<size_t>(c) * kRhoParts + blockIdx.x) * kMaxTypesDev + threadIdx.x] = rho[threadIdx.x];
+}
+
+// grad = scale (D - rho_{p(a)} g Q), one thread per (channel, antenna).  (With
+// the sums of rho in this kernel one workgroup per channel walked the whole
+// power pattern, 278 us at 256 channels of 256 x 256 pixels and two types.)
+__global__ __launch_bounds__(256) void grad_final_kernel(GradFinalArgs a) {
+  __shared__ double rho[kMaxTypesDev];
+  const int c = blockIdx.y;
+  if (a.subtract) {
+    if (threadIdx.x < kMaxTypesDev) {
+      double s = 0.0;
+      for (int k = 0; k < kRhoParts; ++k)
+        s += a.rho[(static_cast<size_t>(c) * kRhoParts + k) * kMaxTypesDev + threadIdx.x];
+      rho[threadIdx.x] = s;
     }
-    a.grad[i] = make_float2(static_cast<float>(gx * a.scale), static_cast<float>(gy * a.scale));
+    __syncthreads();
   }
+  const int ant = blockIdx.x * 256 + threadIdx.x;
+  if (ant >= a.n_ant) return;
+  const size_t i = static_cast<size_t>(c) * a.n_ant + ant;
+  double gx = a.D[i].x, gy = a.D[i].y;
+  if (a.subtract) {
+    const float2 g = a.gains ? a.gains[i] : make_float2(1.f, 0.f);
+    const double s = rho[a.ant_type[ant]] * a.Q[i];
+    gx -= s * g.x;
+    gy -= s * g.y;
+  }
+  a.grad[i] = make_float2(static_cast<float>(gx * a.scale), static_cast<float>(gy * a.scale));
 }
 
 // Fill with zeros (a kernel rather than a memset node, so captured graphs replay it safely).
@@ -1050,15 +1164,15 @@ int adjoint_fused_blocks_per_cu(int N, int V, bool ci4, int wps, size_t lds) {
 
 hipError_t launch_antenna_power(const void* E, bool ci4, int64_t n_time, int n_chan, int n_ant, double* Q,
                                 hipStream_t st) {
-  const dim3 grid((n_ant + 255) / 256, n_chan);
-  if (ci4) hipLaunchKernelGGL(antenna_power_kernel<true>, grid, dim3(256), 0, st, E, n_time, n_chan, n_ant, Q);
-  else hipLaunchKernelGGL(antenna_power_kernel<false>, grid, dim3(256), 0, st, E, n_time, n_chan, n_ant, Q);
+  const dim3 grid((n_ant + 63) / 64, n_chan), block(64 * kPowerGroups);
+  if (ci4) hipLaunchKernelGGL(antenna_power_kernel<true>, grid, block, 0, st, E, n_time, n_chan, n_ant, Q);
+  else hipLaunchKernelGGL(antenna_power_kernel<false>, grid, block, 0, st, E, n_time, n_chan, n_ant, Q);
   return hipGetLastError();
 }
 
 hipError_t launch_adjoint_reduce(const double2* Dp, int parts, int n_chan, int n_ant, double2* D, hipStream_t st) {
   const size_t n = static_cast<size_t>(n_chan) * n_ant;
-  hipLaunchKernelGGL(adjoint_reduce_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, st, Dp, parts,
+  hipLaunchKernelGGL(adjoint_reduce_kernel, dim3(static_cast<unsigned>((n + 63) / 64)), dim3(256), 0, st, Dp, parts,
                      n, D);
   return hipGetLastError();
 }
@@ -1073,7 +1187,16 @@ int fused_blocks_per_cu(int N, int V, bool ci4, size_t lds) {
 }
 
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(reduce_kernel, dim3(blocks_for(static_cast<size_t>(a.N) * a.N * a.n_chan / 4)), dim3(256), 0, st, a);
+  // Threads per pixel quad: as many as leave each several slices to sum, while
+  // the quads alone do not give every SIMD of the card two waves.
+  const size_t quads = static_cast<size_t>(a.N) * a.N * a.n_chan / 4;
+  const size_t full = 2 * 1024 * 64;
+  if (quads >= full || a.slices < 8)
+    hipLaunchKernelGGL(reduce_kernel<1>, dim3(blocks_for(quads)), dim3(256), 0, st, a);
+  else if (quads * 4 >= full || a.slices < 32)
+    hipLaunchKernelGGL(reduce_kernel<4>, dim3(blocks_for(quads * 4)), dim3(256), 0, st, a);
+  else
+    hipLaunchKernelGGL(reduce_kernel<16>, dim3(blocks_for(quads * 16)), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1157,7 +1280,12 @@ hipError_t launch_degrid(const DegridArgs& a, bool ci4, hipStream_t st) {
 }
 
 hipError_t launch_grad_final(const GradFinalArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(grad_final_kernel, dim3(a.n_chan), dim3(256), 0, st, a);
+  if (a.subtract) {
+    hipLaunchKernelGGL(grad_rho_kernel, dim3(kRhoParts, a.n_chan), dim3(256), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(grad_final_kernel, dim3((a.n_ant + 255) / 256, a.n_chan), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
