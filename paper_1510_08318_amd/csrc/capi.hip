@@ -50,7 +50,9 @@ struct moff_plan_s {
   int* d_fx_ptr = nullptr;
   int* d_fx_ab = nullptr;
   float2* d_fx_x = nullptr;
-  int fx_NL = 0, fx_xs = 0;
+  int* d_fx_cells = nullptr;            // one table type: cells with pairs, then row starts
+  int fx_NL = 0, fx_xs = 0, fx_cells = 0;
+  int64_t fx_pairs = 0;
   // workspace, grown on demand
   void* d_ws = nullptr;
   size_t ws_bytes = 0;
@@ -126,7 +128,7 @@ void free_device(moff_plan p) {
   void* ptrs[] = {p->d_tw,        p->d_Pp,        p->d_ant_type, p->d_ktab,        p->d_csr_ptr,
                   p->d_csr_ant,   p->d_csr_tap,   p->d_ant_cells, p->d_ktype_k,    p->d_ktype_off,
                   p->d_mfma_prog, p->d_mfma_dft,  p->d_Pn,        p->d_ws,         p->d_aux,
-                  p->d_fx_ptr,    p->d_fx_ab,     p->d_fx_x,     p->d_split_prog,  p->d_split_progi,
+                  p->d_fx_ptr,    p->d_fx_ab,     p->d_fx_x,     p->d_fx_cells,   p->d_split_prog,  p->d_split_progi,
                   p->d_split_ends, p->d_split_steps, p->d_split_coef};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
@@ -1303,9 +1305,19 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
     moff_status u = upload(&p->d_fx_ptr, t.ptr.data(), sizeof(int32_t) * t.ptr.size());
     if (u == MOFF_OK) u = upload(&p->d_fx_ab, t.ab.data(), sizeof(int32_t) * t.ab.size());
     if (u == MOFF_OK) u = upload(&p->d_fx_x, t.xcorr.data(), sizeof(float) * t.xcorr.size());
+    p->fx_cells = static_cast<int>(t.cell_at.size());
+    p->fx_pairs = static_cast<int64_t>(t.ab.size());
+    if (u == MOFF_OK && hp.n_ktypes == 1) {
+      try {
+        t.cell_at.insert(t.cell_at.end(), t.row_ptr.begin(), t.row_ptr.end());
+      } catch (...) {
+        u = MOFF_ERR_NOMEM;
+      }
+      if (u == MOFF_OK) u = upload(&p->d_fx_cells, t.cell_at.data(), sizeof(int32_t) * t.cell_at.size());
+    }
     if (u != MOFF_OK) {
       for (void** q : {reinterpret_cast<void**>(&p->d_fx_ptr), reinterpret_cast<void**>(&p->d_fx_ab),
-                       reinterpret_cast<void**>(&p->d_fx_x)})
+                       reinterpret_cast<void**>(&p->d_fx_x), reinterpret_cast<void**>(&p->d_fx_cells)})
         if (*q) {
           (void)hipFree(*q);
           *q = nullptr;
@@ -1318,9 +1330,10 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   const int NL = p->fx_NL, NTP = hp.n_ktypes * hp.n_ktypes;
   // workspace per channel; channels run in chunks that keep it within ~2 GiB
   const size_t v_per = sizeof(float2) * hp.n_ant * hp.n_ant;
-  const size_t h_per = sizeof(float2) * NTP * NL * NL;
-  const size_t r_per = sizeof(float2) * NL * NL;
-  const size_t z_per = sizeof(float2) * NL * hp.N;
+  const bool one_type = hp.n_ktypes == 1;
+  const size_t h_per = sizeof(float2) * (one_type ? static_cast<size_t>(p->fx_cells) : static_cast<size_t>(NTP) * NL * NL);
+  const size_t r_per = one_type ? 0 : sizeof(float2) * NL * NL;
+  const size_t z_per = sizeof(float2) * hp.L * hp.N;
   const size_t per_chan = v_per + h_per + r_per + z_per;
   const int chunk = static_cast<int>(std::max<size_t>(
       1, std::min<size_t>({static_cast<size_t>(hp.n_chan), (size_t(2) << 30) / per_chan, size_t(65535)})));
@@ -1340,6 +1353,14 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   a.xs = p->fx_xs;
   a.pair_ptr = p->d_fx_ptr;
   a.pair_ab = p->d_fx_ab;
+  a.n_pairs = p->fx_pairs;
+  a.n_cells = p->fx_cells;
+  a.cell_at = p->d_fx_cells;
+  a.row_ptr = one_type ? p->d_fx_cells + p->fx_cells : nullptr;
+  a.real_tables = 1;
+  for (size_t i = 1; i < hp.kvals.size(); i += 2)
+    if (hp.kvals[i] != 0.f) a.real_tables = 0;
+  a.Pp = p->d_Pp;
   a.ktype_k = p->d_ktype_k;
   a.xcorr = p->d_fx_x;
   a.tw = p->d_tw;

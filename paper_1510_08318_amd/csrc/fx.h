@@ -20,13 +20,19 @@ struct FxArgs {
   int N, L, NL, xs;            // xs: side of each pair-response table
   const int* pair_ptr;         // [NTP * NL * NL + 1] CSR over (type pair, footprint offset)
   const int* pair_ab;          // [entries] upper-triangle index of V, kFxConjBit: read conjugated
+  int64_t n_pairs;             // entries of pair_ab
+  const int* cell_at;          // [n_cells] cells with pairs, in order (one type)
+  const int* row_ptr;          // [L + 1] first of them in each lag row up to the zero lag
+  int n_cells;
+  int real_tables;             // every table entry is real
+  const double* Pp;            // [N][N] power pattern (one type)
   const int* ktype_k;          // [n_types]
   const float2* xcorr;         // [NTP][xs][xs] pair responses of the tables
   const float2* tw;            // [N] exp(+2 pi i k / N)
   float2* V;                   // [n_launch][n_ant][n_ant] workspace (upper triangle used)
-  float2* H;                   // [n_launch][NTP][NL][NL] workspace
-  float2* R;                   // [n_launch][NL][NL] workspace
-  float2* Z;                   // [n_launch][NL][N] workspace
+  float2* H;                   // [n_launch][n_cells] (one type) or [n_launch][NTP][NL][NL] workspace
+  float2* R;                   // [n_launch][NL][NL] workspace (several types; rows 0 .. L - 1 used)
+  float2* Z;                   // [n_launch][L][N] workspace
   float* out;                  // [n_chan][N][N]
   double scale;
 };

@@ -65,6 +65,17 @@ void build_fx_tables(const HostPlan& hp, bool keep_autos, FxTables* t) {
         const uint32_t upper = static_cast<uint32_t>(std::min(a, b)) * na + std::max(a, b);
         t->ab[static_cast<size_t>(fill[row_of(a, b)]++)] = static_cast<int32_t>(upper | (a > b ? kFxConjBit : 0u));
       }
+  if (nt == 1) {
+    t->row_ptr.assign(L + 1, 0);
+    for (int ly = 0; ly < L; ++ly) {
+      t->row_ptr[ly] = static_cast<int32_t>(t->cell_at.size());
+      for (int lx = 0; lx < NL; ++lx) {
+        const int i = ly * NL + lx;
+        if (t->ptr[i + 1] > t->ptr[i]) t->cell_at.push_back(i);
+      }
+    }
+    t->row_ptr[L] = static_cast<int32_t>(t->cell_at.size());
+  }
 }
 
 }  // namespace moff

@@ -19,13 +19,16 @@ namespace moff {
 //              negated), which holds the conjugate sum, have entries.  An entry
 //              is min(a, b) * n_ant + max(a, b), the upper-triangle visibility,
 //              with kFxConjBit set when a > b (read it conjugated).
+//   cell_at / row_ptr : with one table type, the cells that have entries, in
+//              order, and the first of them in each lag row up to the zero lag
+//              [L + 1] (rows past it are mirrors).
 //   xcorr    : per type pair, X[u][v] = sum K_p[s][t] conj(K_q[s - u + k_q - 1][t - v + k_q - 1])
 //              on a (k_p + k_q - 1)^2 support, stored [pair][xs][xs] as float32 (re, im).
 constexpr uint32_t kFxConjBit = 0x80000000u;
 
 struct FxTables {
   int NL = 0, xs = 0;
-  std::vector<int32_t> ptr, ab;
+  std::vector<int32_t> ptr, ab, cell_at, row_ptr;
   std::vector<float> xcorr;
 };
 void build_fx_tables(const HostPlan& hp, bool keep_autos, FxTables* t);
