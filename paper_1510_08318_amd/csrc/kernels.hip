@@ -726,15 +726,33 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
 // staged kernels
 // ---------------------------------------------------------------------------
 
-// One workgroup per frame: calibrate into LDS, then every aperture cell sums
-// its CSR row (antenna-ascending) and writes Eg.
+// Calibrate a frame into LDS, then every aperture cell sums its CSR row
+// (antenna-ascending) and writes Eg.  One workgroup per 256 x kGridCells cells
+// of a frame: each thread walks its cells' rows side by side, so that the loads
+// of all of them are in flight at once (a cell at a time, one workgroup per
+// frame, was a chain of loads per cell: 23 us became 18 at 768 frames of 256
+// antennas, N = 128, whose grids take 25 MB).
+constexpr int kGridCells = 8;
+
 template <bool CI4>
 __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
   extern __shared__ float2 lds[];
   float2* e = lds;               // [n_ant]
   float2* K = e + a.n_ant;       // [n_taps]
-  const int64_t f = blockIdx.x;  // frame = t * n_chan + c
+  const int ncell = a.L * a.L, parts = (ncell + 256 * kGridCells - 1) / (256 * kGridCells);
+  const int64_t f = blockIdx.x / parts;  // frame = t * n_chan + c
   const int c = static_cast<int>(f % a.n_chan);
+  const int cell0 = static_cast<int>(blockIdx.x % parts) * 256 * kGridCells + threadIdx.x;
+  int k0[kGridCells], k1[kGridCells];
+#pragma unroll
+  for (int i = 0; i < kGridCells; ++i) {
+    const int cell = cell0 + 256 * i;
+    k0[i] = k1[i] = 0;
+    if (cell < ncell) {
+      k0[i] = a.csr_ptr[cell];
+      k1[i] = a.csr_ptr[cell + 1];
+    }
+  }
   const size_t base = static_cast<size_t>(f) * a.n_ant;
   for (int i = threadIdx.x; i < a.n_ant; i += 256) {
     const float2 g = a.gains ? a.gains[static_cast<size_t>(c) * a.n_ant + i] : make_float2(1.f, 0.f);
@@ -742,17 +760,32 @@ __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
   }
   for (int i = threadIdx.x; i < a.n_taps; i += 256) K[i] = a.ktab[i];
   __syncthreads();
-  const int ncell = a.L * a.L;
-  float2* out = a.Eg + static_cast<size_t>(f) * ncell;
-  for (int cell = threadIdx.x; cell < ncell; cell += 256) {
-    float2 s = make_float2(0.f, 0.f);
-    for (int k = a.csr_ptr[cell]; k < a.csr_ptr[cell + 1]; ++k) {
-      const float2 ev = e[a.csr_ant[k]], kv = K[a.csr_tap[k]];
-      s.x = fmaf(ev.x, kv.x, fmaf(-ev.y, kv.y, s.x));
-      s.y = fmaf(ev.x, kv.y, fmaf(ev.y, kv.x, s.y));
-    }
-    out[cell] = s;
+  float2 s[kGridCells];
+#pragma unroll
+  for (int i = 0; i < kGridCells; ++i) s[i] = make_float2(0.f, 0.f);
+  for (bool more = true; more;) {
+    more = false;
+    int ant[kGridCells], tap[kGridCells];
+#pragma unroll
+    for (int i = 0; i < kGridCells; ++i)
+      if (k0[i] < k1[i]) {
+        ant[i] = a.csr_ant[k0[i]];
+        tap[i] = a.csr_tap[k0[i]];
+      }
+#pragma unroll
+    for (int i = 0; i < kGridCells; ++i)
+      if (k0[i] < k1[i]) {
+        const float2 ev = e[ant[i]], kv = K[tap[i]];
+        s[i].x = fmaf(ev.x, kv.x, fmaf(-ev.y, kv.y, s[i].x));
+        s[i].y = fmaf(ev.x, kv.y, fmaf(ev.y, kv.x, s[i].y));
+        ++k0[i];
+        more = more || k0[i] < k1[i];
+      }
   }
+  float2* out = a.Eg + static_cast<size_t>(f) * ncell;
+#pragma unroll
+  for (int i = 0; i < kGridCells; ++i)
+    if (cell0 + 256 * i < ncell) out[cell0 + 256 * i] = s[i];
 }
 
 // One workgroup per channel: A[c][p] += sum_t sum_{a of type p} |g E|^2.
@@ -776,8 +809,14 @@ __global__ __launch_bounds__(256) void self_power_kernel(GridArgs a) {
   if (threadIdx.x < a.n_types) a.A[static_cast<size_t>(c) * a.n_types + threadIdx.x] += tot[threadIdx.x];
 }
 
-// One workgroup per (column class, frame): load and fold the aperture grid,
-// transform, store the complex image field in pixel order.
+// One workgroup per (row class, frame): load and fold the aperture grid,
+// transform, store the complex image field in pixel order.  As in the fused
+// kernel the transform runs on the transposed aperture, so that a workgroup owns
+// whole image rows; a lane's outputs of the two half-rounds are adjacent pixels
+// and leave as one 16-byte store, four lanes to 64 bytes of a row.  (With
+// classes of columns each 8-byte store touched every other pixel of a row: 51 us
+// became 45 at 768 frames, N = 128, whose 126 MB take about 25 at the rate of a
+// copy; one and a half rounds of four workgroups per CU are the rest.)
 template <int N>
 __global__ __launch_bounds__((FT<N, 0>::NT)) void fft2_kernel(Fft2Args a) {
   using C = FT<N, 0>;
@@ -792,22 +831,37 @@ __global__ __launch_bounds__((FT<N, 0>::NT)) void fft2_kernel(Fft2Args a) {
   fold_factors<N, 0>(a.tw, w, fin);
   const float2* src = a.Eg + static_cast<size_t>(f) * C::L * C::L;
   for (int cell = threadIdx.x; cell < C::L * C::NZR; cell += C::NT) {
-    const int iy = cell / C::NZR, n = cell % C::NZR;
+    const int n = cell / C::L, ix = cell % C::L;
     float2 v = make_float2(0.f, 0.f);
     for (int j = 0; j * C::M + n < C::L; ++j) {
-      const float2 x = quarter_rot(src[iy * C::L + n + j * C::M], j * w, C::SX);
+      const float2 x = quarter_rot(src[(n + j * C::M) * C::L + ix], j * w, C::SX);
       v = c_add(v, x);
     }
-    G[iy * C::P + n] = v;
+    G[ix * C::P + n] = v;
   }
   __syncthreads();
   row_stage<N, 0>(G, twr, fin);
   __syncthreads();
   float2* dst = a.Y + static_cast<size_t>(f) * N * N;
-  col_stage<N, 0>(G, twc, [&](int, int r, int col, float2 v) {
-    const int q = C::SX * col + w;
-    dst[((r + N / 2) & (N - 1)) * N + ((q + N / 2) & (N - 1))] = v;
-  });
+  float2 y[C::NACC];
+  col_stage<N, 0>(G, twc, [&](int idx, int, int, float2 v) { y[idx] = v; });
+  const bool aligned = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;   // uniform
+#pragma unroll
+  for (int idx = 0; idx < C::NACC; ++idx) {
+    constexpr int HALF = C::JB * C::QC;   // accumulators of a half-round
+    if ((idx / HALF) % 2) continue;
+    int q, m;
+    acc_pixel<N, 0>(idx, q, m);           // (q even; the other half-round's is q + 1)
+    if (C::CGUARD && m >= C::M) continue;
+    float2* at = dst + ((C::SX * m + w + N / 2) & (N - 1)) * N + ((q + N / 2) & (N - 1));
+    const float2 v0 = y[idx], v1 = y[idx + HALF];
+    if (aligned) {
+      *reinterpret_cast<float4*>(at) = make_float4(v0.x, v0.y, v1.x, v1.y);
+    } else {
+      at[0] = v0;
+      at[1] = v1;
+    }
+  }
 }
 
 // One thread per (channel, pixel): S += sum_t |Y|^2.
@@ -1202,11 +1256,12 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {
 
 hipError_t launch_grid(const GridArgs& a, bool ci4, hipStream_t st) {
   const size_t lds = sizeof(float2) * (a.n_ant + a.n_taps);
-  const unsigned frames = static_cast<unsigned>(a.n_time * a.n_chan);  // checked < 2^31 by the caller
+  const int64_t parts = (static_cast<int64_t>(a.L) * a.L + 256 * kGridCells - 1) / (256 * kGridCells);
+  const int64_t blocks = a.n_time * a.n_chan * parts;   // frames checked < 2^31 by the caller
   if (ci4)
-    hipLaunchKernelGGL(grid_kernel<true>, dim3(frames), dim3(256), lds, st, a);
+    hipLaunchKernelGGL(grid_kernel<true>, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, a);
   else
-    hipLaunchKernelGGL(grid_kernel<false>, dim3(frames), dim3(256), lds, st, a);
+    hipLaunchKernelGGL(grid_kernel<false>, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, a);
   return hipGetLastError();
 }
 
