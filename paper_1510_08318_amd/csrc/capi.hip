@@ -47,12 +47,11 @@ struct moff_plan_s {
   double* d_Pn = nullptr;               // uv-plane autocorrelation rule (MOFF_AUTOCORR_UV)
   uint32_t* d_adj_slots[moff::kMaxVariants] = {};   // fused adjoint: antennas per lane; null if they do not fit
   // visibility route (moff_image_fx), built on first use
-  int* d_fx_ptr = nullptr;
-  int* d_fx_ab = nullptr;
+  int* d_fx_rows = nullptr;             // antenna order and places, summed rows, row starts (FxTables)
+  uint32_t* d_fx_ab = nullptr;
+  uint16_t* d_fx_dx = nullptr;
   float2* d_fx_x = nullptr;
-  int* d_fx_cells = nullptr;            // one table type: cells with pairs, then row starts
-  int fx_NL = 0, fx_xs = 0, fx_cells = 0;
-  int64_t fx_pairs = 0;
+  int fx_NL = 0, fx_xs = 0, fx_rows = 0;
   // workspace, grown on demand
   void* d_ws = nullptr;
   size_t ws_bytes = 0;
@@ -128,7 +127,7 @@ void free_device(moff_plan p) {
   void* ptrs[] = {p->d_tw,        p->d_Pp,        p->d_ant_type, p->d_ktab,        p->d_csr_ptr,
                   p->d_csr_ant,   p->d_csr_tap,   p->d_ant_cells, p->d_ktype_k,    p->d_ktype_off,
                   p->d_mfma_prog, p->d_mfma_dft,  p->d_Pn,        p->d_ws,         p->d_aux,
-                  p->d_fx_ptr,    p->d_fx_ab,     p->d_fx_x,     p->d_fx_cells,   p->d_split_prog,  p->d_split_progi,
+                  p->d_fx_rows,   p->d_fx_ab,     p->d_fx_dx,     p->d_fx_x,       p->d_split_prog,  p->d_split_progi,
                   p->d_split_ends, p->d_split_steps, p->d_split_coef};
   for (void* q : ptrs)
     if (q) (void)hipFree(q);
@@ -1295,48 +1294,67 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   DeviceGuard guard(p->device);
   if (!guard.ok()) return MOFF_ERR_HIP;
   const bool keep_autos = (hp.flags & MOFF_AUTOCORR_NONE) != 0;
-  if (!p->d_fx_ptr) {
+  if (!p->d_fx_rows) {
     moff::FxTables t;
+    std::vector<int32_t> lists;
     try {
       moff::build_fx_tables(hp, keep_autos, &t);
+      lists = t.order;
+      lists.resize(2 * static_cast<size_t>(hp.n_ant));
+      for (int i = 0; i < hp.n_ant; ++i) lists[hp.n_ant + t.order[i]] = i;
+      lists.insert(lists.end(), t.rows.begin(), t.rows.end());
+      lists.insert(lists.end(), t.ptr.begin(), t.ptr.end());
     } catch (...) {   // the tables' host vectors: a failed allocation
       return MOFF_ERR_NOMEM;
     }
-    moff_status u = upload(&p->d_fx_ptr, t.ptr.data(), sizeof(int32_t) * t.ptr.size());
+    int* rows = nullptr;
+    moff_status u = upload(&rows, lists.data(), sizeof(int32_t) * lists.size());
     if (u == MOFF_OK) u = upload(&p->d_fx_ab, t.ab.data(), sizeof(int32_t) * t.ab.size());
+    if (u == MOFF_OK) u = upload(&p->d_fx_dx, t.dx.data(), sizeof(uint16_t) * t.dx.size());
     if (u == MOFF_OK) u = upload(&p->d_fx_x, t.xcorr.data(), sizeof(float) * t.xcorr.size());
-    p->fx_cells = static_cast<int>(t.cell_at.size());
-    p->fx_pairs = static_cast<int64_t>(t.ab.size());
-    if (u == MOFF_OK && hp.n_ktypes == 1) {
-      try {
-        t.cell_at.insert(t.cell_at.end(), t.row_ptr.begin(), t.row_ptr.end());
-      } catch (...) {
-        u = MOFF_ERR_NOMEM;
-      }
-      if (u == MOFF_OK) u = upload(&p->d_fx_cells, t.cell_at.data(), sizeof(int32_t) * t.cell_at.size());
-    }
     if (u != MOFF_OK) {
-      for (void** q : {reinterpret_cast<void**>(&p->d_fx_ptr), reinterpret_cast<void**>(&p->d_fx_ab),
-                       reinterpret_cast<void**>(&p->d_fx_x), reinterpret_cast<void**>(&p->d_fx_cells)})
+      if (rows) (void)hipFree(rows);
+      for (void** q : {reinterpret_cast<void**>(&p->d_fx_ab), reinterpret_cast<void**>(&p->d_fx_dx),
+                       reinterpret_cast<void**>(&p->d_fx_x)})
         if (*q) {
           (void)hipFree(*q);
           *q = nullptr;
         }
       return u;
     }
+    p->d_fx_rows = rows;
+    p->fx_rows = static_cast<int>(t.rows.size());
     p->fx_NL = t.NL;
     p->fx_xs = t.xs;
   }
   const int NL = p->fx_NL, NTP = hp.n_ktypes * hp.n_ktypes;
-  // workspace per channel; channels run in chunks that keep it within ~2 GiB
-  const size_t v_per = sizeof(float2) * hp.n_ant * hp.n_ant;
-  const bool one_type = hp.n_ktypes == 1;
-  const size_t h_per = sizeof(float2) * (one_type ? static_cast<size_t>(p->fx_cells) : static_cast<size_t>(NTP) * NL * NL);
+  // Workspace per channel; channels run in chunks that keep it within ~2 GiB.
+  // The staged samples of a long integration are taken in passes over time
+  // where fewer than eight channels (one per XCD) would fit otherwise; the
+  // visibilities are then summed over the passes in float64.
+  const bool ci4 = hp.flags & MOFF_IN_CI4, one_type = hp.n_ktypes == 1;
+  const size_t budget = size_t(2) << 30, pairs = static_cast<size_t>(hp.n_ant) * hp.n_ant;
+  const size_t v_per = sizeof(float2) * pairs;
+  const size_t h_per = sizeof(float2) * (one_type ? static_cast<size_t>(hp.L) : static_cast<size_t>(NTP) * NL) * NL;
   const size_t r_per = one_type ? 0 : sizeof(float2) * NL * NL;
   const size_t z_per = sizeof(float2) * hp.L * hp.N;
-  const size_t per_chan = v_per + h_per + r_per + z_per;
-  const int chunk = static_cast<int>(std::max<size_t>(
-      1, std::min<size_t>({static_cast<size_t>(hp.n_chan), (size_t(2) << 30) / per_chan, size_t(65535)})));
+  size_t per_chan = v_per + h_per + r_per + z_per, d_per = 0, s_per = moff::fx_plane_bytes(ci4, hp.n_ant, n_time);
+  int64_t pass = n_time;
+  const size_t few = static_cast<size_t>(std::min(hp.n_chan, 8));
+  if ((per_chan + s_per) * few > budget) {
+    d_per = sizeof(double2) * pairs;
+    const size_t step = moff::fx_plane_bytes(ci4, hp.n_ant, 1);
+    const size_t room = budget / few > per_chan + d_per ? budget / few - per_chan - d_per : 0;
+    pass = static_cast<int64_t>(std::max<size_t>(1, room / step)) * moff::fx_step(ci4);
+    if (pass >= n_time) {
+      pass = n_time;
+      d_per = 0;
+    }
+    s_per = moff::fx_plane_bytes(ci4, hp.n_ant, pass);
+  }
+  per_chan = (per_chan + d_per + s_per + 255) / 256 * 256;
+  const int chunk = static_cast<int>(
+      std::max<size_t>(1, std::min<size_t>({static_cast<size_t>(hp.n_chan), budget / per_chan, size_t(65535)})));
   s = ensure_workspace(p, per_chan * chunk);
   if (s != MOFF_OK) return s;
   char* ws = static_cast<char*>(p->d_ws);
@@ -1351,12 +1369,13 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   a.L = hp.L;
   a.NL = NL;
   a.xs = p->fx_xs;
-  a.pair_ptr = p->d_fx_ptr;
+  a.order = p->d_fx_rows;
+  a.place = p->d_fx_rows + hp.n_ant;
+  a.rows = a.place + hp.n_ant;
+  a.row_ptr = a.rows + p->fx_rows;
+  a.n_rows = p->fx_rows;
   a.pair_ab = p->d_fx_ab;
-  a.n_pairs = p->fx_pairs;
-  a.n_cells = p->fx_cells;
-  a.cell_at = p->d_fx_cells;
-  a.row_ptr = one_type ? p->d_fx_cells + p->fx_cells : nullptr;
+  a.pair_dx = p->d_fx_dx;
   a.real_tables = 1;
   for (size_t i = 1; i < hp.kvals.size(); i += 2)
     if (hp.kvals[i] != 0.f) a.real_tables = 0;
@@ -1364,17 +1383,30 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   a.ktype_k = p->d_ktype_k;
   a.xcorr = p->d_fx_x;
   a.tw = p->d_tw;
+  // (the parts with the strictest alignment first)
+  a.planes = ws;
+  ws += s_per * chunk;
+  a.Vd = d_per ? reinterpret_cast<double2*>(ws) : nullptr;
+  ws += d_per * chunk;
   a.V = reinterpret_cast<float2*>(ws);
-  a.H = reinterpret_cast<float2*>(ws + v_per * chunk);
-  a.R = reinterpret_cast<float2*>(ws + (v_per + h_per) * chunk);
-  a.Z = reinterpret_cast<float2*>(ws + (v_per + h_per + r_per) * chunk);
+  ws += v_per * chunk;
+  a.H = reinterpret_cast<float2*>(ws);
+  ws += h_per * chunk;
+  a.R = reinterpret_cast<float2*>(ws);
+  ws += r_per * chunk;
+  a.Z = reinterpret_cast<float2*>(ws);
   a.out = image;
   a.scale = image_scale(hp, n_time);
-  const bool ci4 = hp.flags & MOFF_IN_CI4;
   for (int c0 = 0; c0 < hp.n_chan; c0 += chunk) {
     a.c0 = c0;
     a.n_launch = std::min(chunk, hp.n_chan - c0);
-    if (moff::launch_fx(a, ci4, static_cast<hipStream_t>(stream)) != hipSuccess) return MOFF_ERR_HIP;
+    for (int64_t t0 = 0; t0 < n_time; t0 += pass) {
+      a.t0 = t0;
+      a.t1 = std::min(t0 + pass, n_time);
+      a.first = t0 == 0;
+      a.last = a.t1 == n_time;
+      if (moff::launch_fx(a, ci4, static_cast<hipStream_t>(stream)) != hipSuccess) return MOFF_ERR_HIP;
+    }
   }
   return MOFF_OK;
 }

@@ -18,23 +18,42 @@ struct FxArgs {
   int c0, n_launch;            // this launch's channels c0 .. c0 + n_launch - 1 (workspace holds n_launch)
   int64_t n_time;
   int N, L, NL, xs;            // xs: side of each pair-response table
-  const int* pair_ptr;         // [NTP * NL * NL + 1] CSR over (type pair, footprint offset)
-  const int* pair_ab;          // [entries] upper-triangle index of V, kFxConjBit: read conjugated
-  int64_t n_pairs;             // entries of pair_ab
-  const int* cell_at;          // [n_cells] cells with pairs, in order (one type)
-  const int* row_ptr;          // [L + 1] first of them in each lag row up to the zero lag
-  int n_cells;
+  const int* order;            // [n_ant] antennas in the order of the visibilities (FxTables)
+  const int* place;            // [n_ant] each antenna's position in it
+  const int* rows;             // [n_rows] lag rows that are summed, (p * n_types + q) * NL + dy
+  const int* row_ptr;          // [n_rows + 1] their entries
+  const uint32_t* pair_ab;     // [entries] upper-triangle index of V, kFxConjBit: read conjugated
+  const uint16_t* pair_dx;     // [entries] column
+  int n_rows;
   int real_tables;             // every table entry is real
   const double* Pp;            // [N][N] power pattern (one type)
   const int* ktype_k;          // [n_types]
   const float2* xcorr;         // [NTP][xs][xs] pair responses of the tables
   const float2* tw;            // [N] exp(+2 pi i k / N)
+  // samples of this launch's channels in the order of the visibilities, staged
+  // for the correlators: blocks of 64 antennas x fx_step samples,
+  // [n_launch][tiles][steps][planes][64][fx_step]
+  int64_t t0, t1;              // time samples of this pass over them
+  char* planes;
+  double2* Vd;                 // [n_launch][n_ant][n_ant] sums of earlier passes, or null (one pass)
+  int first, last;             // first / last pass
   float2* V;                   // [n_launch][n_ant][n_ant] workspace (upper triangle used)
-  float2* H;                   // [n_launch][n_cells] (one type) or [n_launch][NTP][NL][NL] workspace
+  float2* H;                   // [n_launch][NTP][NL][NL], or [n_launch][L][NL] (one type), workspace
   float2* R;                   // [n_launch][NL][NL] workspace (several types; rows 0 .. L - 1 used)
   float2* Z;                   // [n_launch][L][N] workspace
   float* out;                  // [n_chan][N][N]
   double scale;
 };
+
+// Staged blocks: 4+4-bit samples as int8 planes (re, im) of 64 samples;
+// complex64 samples, calibrated, as three bfloat16 levels of x and of y, of 32.
+constexpr int kFxTile = 64;
+constexpr int fx_step(bool ci4) { return ci4 ? 64 : 32; }
+constexpr size_t fx_block_bytes(bool ci4) { return static_cast<size_t>(kFxTile) * (ci4 ? 64 * 2 : 32 * 2 * 6); }
+inline size_t fx_plane_bytes(bool ci4, int n_ant, int64_t n_time) {   // of one channel
+  return fx_block_bytes(ci4) * ((n_ant + kFxTile - 1) / kFxTile) *
+         static_cast<size_t>((n_time + fx_step(ci4) - 1) / fx_step(ci4));
+}
+// One pass over samples t0 .. t1 (a.last: then the image).
 hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st);
 }  // namespace moff

@@ -6,31 +6,28 @@
 // dirty-image-FX, give the MOFF image; with the zero-spacing a == b terms left
 // out it equals the image with the antennas' self power removed).
 //
+//   fx_stage_*_kernel    the samples as the correlators read them, antennas in
+//                        the order of their cells
 //   fx_correlate_kernel  V[c][a][b] = sum_t e_a conj(e_b), e = g E, for a <= b
 //                        (the upper triangle; V is Hermitian): float32 as three
-//                        bfloat16 levels on the matrix cores over 32-sample
-//                        chunks, chunks summed in float64 (complex64 samples);
+//                        bfloat16 levels on the matrix cores, summed in float64
+//                        over steps of 32 samples (complex64 samples);
 //                        fx_correlate_i8_kernel: exact integer products on the
 //                        matrix cores (4+4-bit samples)
-//   one table type:
-//   fx_bin_cells_kernel  H[c][k] = sum of V[c][a][b] over the pairs whose
-//                        footprints are offset by that of the k-th cell with
-//                        pairs (half the cells: the others are conjugates)
-//   fx_row_kernel        Z[c][ly][q] = sum_lx H[c][ly][lx] w^((lx - L + 1)(q - N/2))
-//                        (rows up to the zero lag; the others are conjugates)
-//   fx_col_kernel        I[c][r][q] = scale P[r][q] Re sum_ly w^((ly - L + 1)(r - N/2)) Z[c][ly][q],
-//                        P the table's power pattern, the transform of its
-//                        autocorrelation (real, two columns per complex transform)
-//   several types:
-//   fx_bin_kernel        H[c][pq][dy][dx] the same per ordered pair of table
-//                        types (p, q), a dense grid of offsets (dy, dx) - (L - 1)
-//                        (plan-time CSR, fixed order); half the cells are
-//                        summed, their mirrors H[qp][-dy][-dx] written as the
+//   fx_bin_kernel        H[c][pq][dy][dx] = sum of V[c][a][b] over the pairs of
+//                        table types (p, q) whose footprints are offset by
+//                        (dy, dx) - (L - 1) cells (fixed order); half the rows
+//                        are summed, their mirrors H[qp][-dy][-dx] are the
 //                        conjugates
 //   fx_lag_kernel        R[c][ly][lx] = sum_pq sum_(u,v) X_pq[u][v]
 //                        H[c][pq][ly - u + k_q - 1][lx - v + k_q - 1]  (LDS-tiled;
-//                        rows up to the zero lag)
-//   fx_row_kernel, fx_col_kernel   as above, of R and without P
+//                        rows up to the zero lag; several table types)
+//   fx_row_kernel        Z[c][ly][q] = sum_lx R[c][ly][lx] w^((lx - L + 1)(q - N/2))
+//                        (rows up to the zero lag; the others are conjugates)
+//   fx_col_kernel        I[c][r][q] = scale Re sum_ly w^((ly - L + 1)(r - N/2)) Z[c][ly][q]
+//                        (real, two columns per complex transform)
+//   With one table type the last two take H for R and multiply the image by the
+//   table's power pattern, the transform of its autocorrelation X.
 //
 // w = exp(+2 pi i / N); lags span -(L - 1) .. L - 1, so the image comes out in
 // the same pixel order as the MOFF image.  Every sum runs in a fixed order
@@ -51,7 +48,6 @@ namespace moff {
 
 namespace {
 
-constexpr int kFxChunk = 32;   // time samples staged per step
 constexpr unsigned kFxXcds = 8;  // accelerator dies (XCDs), each with its own L2
 
 // Workgroups go to the XCDs round-robin by linear index.  For a 1-D grid of
@@ -73,132 +69,204 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 
 }  // namespace
 
-// Complex64 samples, on the matrix cores (v_mfma_f32_16x16x32_bf16): every
-// calibrated float32 component is held as three bfloat16 numbers, high, middle
-// and low, 8 bits each and so all 24 of it at float32's own range, and a
-// product takes the six terms above 2^-24 (hh, hm, mh, mm, hl, lh) with float32
-// accumulation: the accuracy of the float32 matrix instruction at 2.7 times its
-// rate (64 channels x 128 samples of 1024 antennas: 438 us with that
-// instruction, 294 here, of which the products take 87 at their peak rate and
-// the conversions, repeated for every tile an antenna is in, most of the rest;
-// relative error of the image 2.05e-7 and 2.02e-7).  The visibility matrix is Hermitian, V_ba = conj(V_ab), and the binning
-// reads its upper triangle only, so only the tiles on and above the diagonal
-// are formed.  One workgroup per (64 x 64 antenna tile, channel), four waves
-// of a 32 x 32 sub-tile each (2 x 2 blocks of 16 x 16).  With e = x + i y,
-//   Re V_ab = sum x_a x_b + y_a y_b,   Im V_ab = sum y_a x_b - sum x_a y_b.
-// A and B take their samples in the same lane order, so each is summed once
-// whatever order the instruction gives its contraction index; the accumulators
-// hold D[4 (l / 16) + v][l % 16].  Each 32-sample chunk is summed in float32
-// and the chunks in float64.
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Staging: a workgroup takes 64 antennas x one step of samples of a channel and
+// writes them in the form the correlators read, antennas at their places in the
+// order of the visibilities (four lanes to an antenna: 64-byte row segments).  Every block is then read by all tiles of its antennas
+// (one per 64 other antennas), which earlier converted it each for itself.
+//
+// Complex64 samples: e = g E, each component as three bfloat16 numbers, high,
+// middle and low (8 bits each, all 24 of it, at float32's own range):
+// [x, y][level][antenna][sample].
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 b16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 b16x8 __attribute__((ext_vector_type(8)));
-constexpr int kC64Tile = 64;                // antennas per side of a tile
-constexpr int kC64Pitch = kFxChunk + 8;     // LDS row, bfloat16: 16-byte operand reads of 16 rows hit distinct banks
+typedef int i32x4 __attribute__((ext_vector_type(4)));
+constexpr int kC64Step = fx_step(false), kI8Step = fx_step(true);
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fx_correlate_kernel(FxArgs a) {
-  // [block a, b][x, y][high, middle, low][antenna][sample]
-  __shared__ __attribute__((aligned(16))) __bf16 pl[2][2][3][kC64Tile][kC64Pitch];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wa = wave >> 1, wb = wave & 1, r16 = lane & 15, kk = lane >> 4;
-  const int na = a.n_ant, n_tiles = (na + kC64Tile - 1) / kC64Tile;
-  int cl;
-  unsigned tri;
-  if (!xcd_channel(blockIdx.x, static_cast<unsigned>(n_tiles * (n_tiles + 1) / 2), a.n_launch, &cl, &tri)) return;
-  int t = static_cast<int>(tri), ta = 0;      // upper-triangle tile (ta, tb), tb >= ta
-  while (ta < n_tiles && t >= n_tiles - ta) {
-    t -= n_tiles - ta;
-    ++ta;
+__global__ __launch_bounds__(256) void fx_stage_c64_kernel(FxArgs a) {
+  constexpr int PER = kC64Step * kFxTile / 256;   // samples per thread
+  static_assert(PER == 8, "one 16-byte row segment per thread, part and level");
+  const int na = a.n_ant, tiles = (na + kFxTile - 1) / kFxTile;
+  const int cl = blockIdx.z, sg = threadIdx.x % 4, ant = blockIdx.y * kFxTile + threadIdx.x / 4;
+  const int c = a.c0 + cl, pos = ant < na ? a.place[ant] : ant;
+  const int64_t t = a.t0 + static_cast<int64_t>(blockIdx.x) * kC64Step + PER * sg;
+  float2 v[PER];
+#pragma unroll
+  for (int i = 0; i < PER; ++i) v[i] = make_float2(0.f, 0.f);
+  if (ant < na) {
+    const float2 g = a.gains ? a.gains[static_cast<size_t>(c) * na + ant] : make_float2(1.f, 0.f);
+    const float2* E = reinterpret_cast<const float2*>(a.E) + (static_cast<size_t>(t) * a.n_chan + c) * na + ant;
+    const size_t stride = static_cast<size_t>(a.n_chan) * na;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (t + i < a.t1) v[i] = E[i * stride];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) v[i] = t + i < a.t1 ? cmul(g, v[i]) : make_float2(0.f, 0.f);
   }
-  if (ta >= n_tiles) return;                  // beyond the triangle (the launch has none)
-  const int tb = ta + t;
-  const int a0 = ta * kC64Tile, b0 = tb * kC64Tile, c = a.c0 + cl;
-  const float2* E = reinterpret_cast<const float2*>(a.E);
-  double acc[2][2][4][2] = {};
-  // staging: thread = (antenna an, samples kC64Per sg ..), so each thread keeps
-  // its two antennas' gains for the whole integration
-  constexpr int kC64Per = kFxChunk * kC64Tile / 256;
-  static_assert(kC64Per == 8, "one 16-byte row segment per thread, part and level");
-  const int an = tid % kC64Tile, sg = tid / kC64Tile;
-  const int ia = a0 + an, ib = b0 + an;
-  // antennas past the last one read the last one with a zero gain (their rows
-  // are not stored)
-  auto gain_of = [&](int ant) {
-    if (ant >= na) return make_float2(0.f, 0.f);
-    return a.gains ? a.gains[static_cast<size_t>(c) * na + ant] : make_float2(1.f, 0.f);
-  };
-  const float2 gg[2] = {gain_of(ia), gain_of(ib)};
-  const size_t stride = static_cast<size_t>(a.n_chan) * na;   // samples of consecutive times
-  const float2* src[2];
+  b16x8 lv[2][3];
 #pragma unroll
-  for (int blk = 0; blk < 2; ++blk) {
-    const int ant = blk ? ib : ia;
-    src[blk] = E + static_cast<size_t>(kC64Per * sg) * stride + static_cast<size_t>(c) * na + (ant < na ? ant : na - 1);
-  }
-  float2 raw[2][kC64Per];
-  auto load_chunk = [&](int64_t t0) {   // all of a chunk's loads in flight at once
-    const size_t at = static_cast<size_t>(t0) * stride;
-    if (t0 + kFxChunk <= a.n_time) {    // uniform
+  for (int i = 0; i < PER; i += 2)
 #pragma unroll
-      for (int i = 0; i < kC64Per; ++i)
+    for (int part = 0; part < 2; ++part) {
+      f32x2 x = part ? f32x2{v[i].y, v[i + 1].y} : f32x2{v[i].x, v[i + 1].x};
 #pragma unroll
-        for (int blk = 0; blk < 2; ++blk) raw[blk][i] = src[blk][at + i * stride];
-    } else {
-#pragma unroll
-      for (int i = 0; i < kC64Per; ++i)
-#pragma unroll
-        for (int blk = 0; blk < 2; ++blk) {
-          raw[blk][i] = make_float2(0.f, 0.f);
-          if (t0 + kC64Per * sg + i < a.n_time) raw[blk][i] = src[blk][at + i * stride];
-        }
-    }
-  };
-  load_chunk(0);
-  for (int64_t t0 = 0; t0 < a.n_time; t0 += kFxChunk) {
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      b16x8 lv[2][3];
-#pragma unroll
-      for (int i = 0; i < kC64Per; i += 2) {
-        const float2 v0 = cmul(gg[blk], raw[blk][i]), v1 = cmul(gg[blk], raw[blk][i + 1]);
-#pragma unroll
-        for (int part = 0; part < 2; ++part) {
-          f32x2 x = part ? f32x2{v0.y, v1.y} : f32x2{v0.x, v1.x};
-#pragma unroll
-          for (int l = 0; l < 3; ++l) {
-            const b16x2 h = __builtin_convertvector(x, b16x2);
-            lv[part][l][i] = h[0];
-            lv[part][l][i + 1] = h[1];
-            if (l < 2) x -= __builtin_convertvector(h, f32x2);
-          }
-        }
+      for (int l = 0; l < 3; ++l) {
+        const b16x2 h = __builtin_convertvector(x, b16x2);
+        lv[part][l][i] = h[0];
+        lv[part][l][i + 1] = h[1];
+        if (l < 2) x -= __builtin_convertvector(h, f32x2);
       }
-#pragma unroll
-      for (int part = 0; part < 2; ++part)
-#pragma unroll
-        for (int l = 0; l < 3; ++l) *reinterpret_cast<b16x8*>(&pl[blk][part][l][an][kC64Per * sg]) = lv[part][l];
     }
+  __bf16* dst = reinterpret_cast<__bf16*>(a.planes + ((static_cast<size_t>(cl) * tiles + pos / kFxTile) * gridDim.x + blockIdx.x) *
+                                                         fx_block_bytes(false)) +
+                pos % kFxTile * kC64Step + PER * sg;
+#pragma unroll
+  for (int part = 0; part < 2; ++part)
+#pragma unroll
+    for (int l = 0; l < 3; ++l) *reinterpret_cast<b16x8*>(dst + (part * 3 + l) * kFxTile * kC64Step) = lv[part][l];
+}
+
+// 4+4-bit samples: the raw samples as int8, [re, im][antenna][sample]; the gains,
+// constant over the integration, are applied to the sums.  Sixteen samples of
+// one antenna per thread.
+__global__ __launch_bounds__(256) void fx_stage_i8_kernel(FxArgs a) {
+  constexpr int PER = kI8Step * kFxTile / 256;
+  static_assert(PER == 16, "one 16-byte row segment per thread and part");
+  const int na = a.n_ant, tiles = (na + kFxTile - 1) / kFxTile;
+  const int cl = blockIdx.z, sg = threadIdx.x % 4, ant = blockIdx.y * kFxTile + threadIdx.x / 4;
+  const int c = a.c0 + cl, pos = ant < na ? a.place[ant] : ant;
+  const int64_t t = a.t0 + static_cast<int64_t>(blockIdx.x) * kI8Step + PER * sg;
+  int8_t b[PER] = {};
+  if (ant < na) {
+    const int8_t* E = reinterpret_cast<const int8_t*>(a.E) + (static_cast<size_t>(t) * a.n_chan + c) * na + ant;
+    const size_t stride = static_cast<size_t>(a.n_chan) * na;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      if (t + i < a.t1) b[i] = E[i * stride];
+  }
+  uint32_t re[PER / 4] = {}, im[PER / 4] = {};
+#pragma unroll
+  for (int i = 0; i < PER; ++i) {
+    re[i / 4] |= static_cast<uint32_t>(static_cast<uint8_t>(b[i] >> 4)) << (8 * (i % 4));
+    im[i / 4] |= static_cast<uint32_t>(static_cast<uint8_t>(static_cast<int8_t>(b[i] << 4) >> 4)) << (8 * (i % 4));
+  }
+  char* dst = a.planes + ((static_cast<size_t>(cl) * tiles + pos / kFxTile) * gridDim.x + blockIdx.x) * fx_block_bytes(true) +
+              pos % kFxTile * kI8Step + PER * sg;
+  *reinterpret_cast<uint4*>(dst) = make_uint4(re[0], re[1], re[2], re[3]);
+  *reinterpret_cast<uint4*>(dst + kFxTile * kI8Step) = make_uint4(im[0], im[1], im[2], im[3]);
+}
+
+// The correlators: V_ab for a <= b (V_ba = conj V_ab, and the binning reads the
+// upper triangle only), one workgroup per (64 x 64 antenna tile on or above the
+// diagonal, channel), four waves of a 32 x 32 sub-tile each (2 x 2 blocks of
+// 16 x 16).  Per step both antenna blocks are copied into LDS, the next step's
+// copies in flight meanwhile.  A and B take their samples in the same lane
+// order, so each is summed once whatever order the instruction gives its
+// contraction index; accumulators hold D[4 (l / 16) + v][l % 16].
+
+// Tile (ta, tb) and channel of a workgroup; false for the padding ones.
+__device__ __forceinline__ bool corr_tile(const FxArgs& a, int* cl, int* ta, int* tb) {
+  const int n_tiles = (a.n_ant + kFxTile - 1) / kFxTile;
+  unsigned tri;
+  if (!xcd_channel(blockIdx.x, static_cast<unsigned>(n_tiles * (n_tiles + 1) / 2), a.n_launch, cl, &tri)) return false;
+  int t = static_cast<int>(tri);
+  *ta = 0;
+  while (*ta < n_tiles && t >= n_tiles - *ta) {
+    t -= n_tiles - *ta;
+    ++*ta;
+  }
+  *tb = *ta + t;
+  return *ta < n_tiles;
+}
+
+// Copies of one step: 16 bytes per thread and round, both blocks, into LDS rows
+// of ROW bytes at a pitch 16 bytes longer (operand reads of 16 rows then hit
+// distinct banks).
+template <int ROUNDS>
+__device__ __forceinline__ void load_step(const char* a, const char* b, i32x4 (&v)[2][ROUNDS]) {
+#pragma unroll
+  for (int r = 0; r < ROUNDS; ++r) {
+    v[0][r] = reinterpret_cast<const i32x4*>(a)[r * 256 + threadIdx.x];
+    v[1][r] = reinterpret_cast<const i32x4*>(b)[r * 256 + threadIdx.x];
+  }
+}
+template <int ROW, int ROUNDS>
+__device__ __forceinline__ void store_step(char* lds, const i32x4 (&v)[2][ROUNDS]) {   // [block][row]
+#pragma unroll
+  for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+      const int at = (r * 256 + threadIdx.x) * 16;
+      *reinterpret_cast<i32x4*>(lds + (blk * (ROUNDS * 4096 / ROW) + at / ROW) * (ROW + 16) + at % ROW) = v[blk][r];
+    }
+}
+
+// Sum of a pass, or of all: the running sums of passes before the last in Vd.
+__device__ __forceinline__ void put_visibility(const FxArgs& a, int cl, int ia, int ib, double x, double y) {
+  const size_t at = (static_cast<size_t>(cl) * a.n_ant + ia) * a.n_ant + ib;
+  if (a.Vd) {
+    if (!a.first) {
+      const double2 s = a.Vd[at];
+      x += s.x;
+      y += s.y;
+    }
+    if (!a.last) {
+      a.Vd[at] = make_double2(x, y);
+      return;
+    }
+  }
+  a.V[at] = make_float2(static_cast<float>(x), static_cast<float>(y));
+}
+
+// Complex64 samples: v_mfma_f32_16x16x32_bf16 on the levels, a product taking the
+// six terms above 2^-24 (hh, hm, mh, mm, hl, lh) with float32 accumulation: the
+// accuracy of the float32 matrix instruction at 2.7 times its rate.  With
+// e = x + i y,
+//   Re V_ab = sum x_a x_b + y_a y_b,   Im V_ab = sum y_a x_b - x_a y_b;
+// each 32-sample step is summed in float32 and the steps in float64.  At 64
+// channels x 128 samples of 1024 antennas: 438 us with the float32 instruction,
+// 294 with the levels made by every tile, ZZ here and PP for the staging; the
+// products take 87 at their peak rate.
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fx_correlate_kernel(FxArgs a) {
+  constexpr int ROW = kC64Step * 2, PITCH = ROW + 16;
+  __shared__ __attribute__((aligned(16))) char pl[2 * 6 * kFxTile * PITCH];   // [block][x, y][level][antenna]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wa = wave >> 1, wb = wave & 1, r16 = lane & 15, kk = lane >> 4;
+  const int na = a.n_ant, tiles = (na + kFxTile - 1) / kFxTile;
+  int cl, ta, tb;
+  if (!corr_tile(a, &cl, &ta, &tb)) return;
+  const int64_t steps = (a.t1 - a.t0 + kC64Step - 1) / kC64Step;
+  const char* pa = a.planes + (static_cast<size_t>(cl) * tiles + ta) * steps * fx_block_bytes(false);
+  const char* pb = a.planes + (static_cast<size_t>(cl) * tiles + tb) * steps * fx_block_bytes(false);
+  double acc[2][2][4][2] = {};
+  i32x4 next[2][6];
+  load_step(pa, pb, next);
+  for (int64_t st = 0; st < steps; ++st) {
+    store_step<ROW>(pl, next);
     __syncthreads();
-    if (t0 + kFxChunk < a.n_time) load_chunk(t0 + kFxChunk);   // in flight during the products
+    pa += fx_block_bytes(false);
+    pb += fx_block_bytes(false);
+    if (st + 1 < steps) load_step(pa, pb, next);   // in flight during the products
+    auto operand = [&](int blk, int part, int l, int row) {
+      return *reinterpret_cast<const b16x8*>(pl + (((blk * 2 + part) * 3 + l) * kFxTile + row) * PITCH + 16 * kk);
+    };
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       b16x8 A[2][3];
 #pragma unroll
       for (int part = 0; part < 2; ++part)
 #pragma unroll
-        for (int l = 0; l < 3; ++l)
-          A[part][l] = *reinterpret_cast<const b16x8*>(&pl[0][part][l][32 * wa + 16 * i + r16][8 * kk]);
+        for (int l = 0; l < 3; ++l) A[part][l] = operand(0, part, l, 32 * wa + 16 * i + r16);
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         b16x8 B[2][3];
 #pragma unroll
         for (int part = 0; part < 2; ++part)
 #pragma unroll
-          for (int l = 0; l < 3; ++l)
-            B[part][l] = *reinterpret_cast<const b16x8*>(&pl[1][part][l][32 * wb + 16 * j + r16][8 * kk]);
-        // x_a x_b + y_a y_b and y_a x_b - x_a y_b: the small terms of both
-        // products first, so that a chunk's sum rounds twice at full size
+          for (int l = 0; l < 3; ++l) B[part][l] = operand(1, part, l, 32 * wb + 16 * j + r16);
+        // the small terms of both products first, so that a step's sum rounds
+        // twice at full size
         auto terms = [&](const b16x8 (&x)[3], const b16x8 (&y)[3], f32x4 r) {
           r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[2], y[0], r, 0, 0, 0);
           r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[0], y[2], r, 0, 0, 0);
@@ -227,152 +295,66 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
     }
     __syncthreads();
   }
-  float2* V = a.V + static_cast<size_t>(cl) * na * na;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int ia = a0 + 32 * wa + 16 * i + 4 * kk + v, ib = b0 + 32 * wb + 16 * j + r16;
-        if (ia >= na || ib >= na) continue;
-        const float x = static_cast<float>(acc[i][j][v][0]), y = static_cast<float>(acc[i][j][v][1]);
-        V[static_cast<size_t>(ia) * na + ib] = make_float2(x, y);
+        const int ia = ta * kFxTile + 32 * wa + 16 * i + 4 * kk + v, ib = tb * kFxTile + 32 * wb + 16 * j + r16;
+        if (ia < na && ib < na) put_visibility(a, cl, ia, ib, acc[i][j][v][0], acc[i][j][v][1]);
       }
 }
 
 // 4+4-bit samples: the cross-products are exact integer sums, formed on the
 // matrix cores (v_mfma_i32_16x16x64_i8, int32 accumulation) from the raw
-// samples; the gains are constant over the integration and are applied once,
-// V_ab = g_a conj(g_b) sum_t E_a conj(E_b), in float64.  One workgroup per
-// (64 x 64 antenna tile on or above the diagonal, channel), four waves of a
-// 32 x 32 sub-tile each (2 x 2 blocks of 16 x 16).  Per 64-sample step the
-// real and imaginary parts of both antenna blocks are staged in LDS as int8
-// rows [antenna][sample], and each wave runs four products (re.re, im.im,
-// im.re, re.im) per block; the next step's samples are loaded into registers
-// while the current step's products run.  Samples are loaded four antennas at a
-// time (unaligned 4-byte loads) for four samples, widened as packed bytes and
-// transposed 4 x 4 in registers.  Bound by the vector work of the staging and
-// the latency of its loads, not by the products (6 % of the matrix rate): byte
-// by byte, with a bounds check and a 64-bit address per byte, it took 132 us at
-// 256 channels x 256 samples of 350 antennas, this form takes 88 (the V it
-// writes, 126 MB, about 30).  A and B take their samples in the
-// same lane order, so the sum covers each sample once whatever order the
-// instruction gives its contraction index; the accumulators hold
-// D[4 (l / 16) + j][l % 16].
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-constexpr int kI8Step = 64;                 // samples per step
-constexpr int kI8Pitch = kI8Step + 16;      // LDS row bytes: 16-byte operand reads of 16 rows hit distinct banks
-
-constexpr int kI8Blocks = 2;                          // 16 x 16 blocks per wave and side
-constexpr int kI8Tile = 32 * kI8Blocks;               // antennas per side of a tile
-
+// samples, four products (re.re, im.im, im.re, re.im) per block; the gains are
+// applied once, V_ab = g_a conj(g_b) sum_t E_a conj(E_b), in float64.  Bound by
+// what surrounds the products (6 % of the matrix rate): at 256 channels x 256
+// samples of 350 antennas 132 us with samples unpacked byte by byte for every
+// tile, ZZ here and PP for the staging (the V it writes, 126 MB, about 30).
 __global__ __launch_bounds__(256) void fx_correlate_i8_kernel(FxArgs a) {
-  __shared__ __attribute__((aligned(16))) int8_t pl[4][kI8Tile][kI8Pitch];   // re A, im A, re B, im B
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int na = a.n_ant, n_tiles = (na + kI8Tile - 1) / kI8Tile;
-  int cl;
-  unsigned tri;
-  if (!xcd_channel(blockIdx.x, static_cast<unsigned>(n_tiles * (n_tiles + 1) / 2), a.n_launch, &cl, &tri)) return;
-  int t = static_cast<int>(tri), ta = 0;      // upper-triangle tile (ta, tb), tb >= ta
-  while (ta < n_tiles && t >= n_tiles - ta) {
-    t -= n_tiles - ta;
-    ++ta;
-  }
-  if (ta >= n_tiles) return;                  // beyond the triangle (the launch has none)
-  const int a0 = ta * kI8Tile, b0 = (ta + t) * kI8Tile, c = a.c0 + cl;
-  const int8_t* E = reinterpret_cast<const int8_t*>(a.E);
-  const size_t tstride = static_cast<size_t>(a.n_chan) * na;
-  // staging: thread = (antennas 4 ag .., samples 4 sg ..) of both blocks
-  const int ag = tid % (kI8Tile / 4), sg = tid / (kI8Tile / 4);
-  // a load of four antennas' bytes ends with the row at the latest; what it
-  // shifts out are antennas of the group before, what it shifts in is zero
-  const int8_t* src[2];
-  unsigned down[2];
-  bool none[2];
-#pragma unroll
-  for (int blk = 0; blk < 2; ++blk) {
-    const int ant = (blk ? b0 : a0) + 4 * ag, from = ant <= na - 4 ? ant : na >= 4 ? na - 4 : 0;
-    none[blk] = ant >= na;
-    down[blk] = none[blk] ? 0u : 8u * static_cast<unsigned>(ant - from);
-    src[blk] = E + static_cast<size_t>(4 * sg) * tstride + static_cast<size_t>(c) * na + from;
-  }
-  // this wave's sub-tile and its operand rows
+  constexpr int ROW = kI8Step, PITCH = ROW + 16;
+  __shared__ __attribute__((aligned(16))) char pl[2 * 2 * kFxTile * PITCH];   // [block][re, im][antenna]
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int ah = w >> 1, bh = w & 1, l16 = lane & 15, g = lane >> 4;
-  i32x4 acc[kI8Blocks][kI8Blocks][4];
+  const int na = a.n_ant, tiles = (na + kFxTile - 1) / kFxTile;
+  int cl, ta, tb;
+  if (!corr_tile(a, &cl, &ta, &tb)) return;
+  const int c = a.c0 + cl;
+  const int64_t steps = (a.t1 - a.t0 + kI8Step - 1) / kI8Step;
+  const char* pa = a.planes + (static_cast<size_t>(cl) * tiles + ta) * steps * fx_block_bytes(true);
+  const char* pb = a.planes + (static_cast<size_t>(cl) * tiles + tb) * steps * fx_block_bytes(true);
+  i32x4 acc[2][2][4];
 #pragma unroll
-  for (int i = 0; i < kI8Blocks; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < kI8Blocks; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[i][j][q] = i32x4{0, 0, 0, 0};
-  uint32_t nxt[2][4];   // [block][sample], a byte per antenna
-  auto load_step = [&](int64_t t0) {
-    const size_t at = static_cast<size_t>(t0) * tstride;
-    const bool full = t0 + kI8Step <= a.n_time && na >= 4;   // uniform
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int8_t* from = src[blk] + at + i * tstride;
-        uint32_t v = 0;
-        if (full) {
-          __builtin_memcpy(&v, from, 4);
-        } else if (t0 + 4 * sg + i < a.n_time) {
-          if (na >= 4) __builtin_memcpy(&v, from, 4);
-          else
-            for (int k = 0; k < na; ++k) v |= static_cast<uint32_t>(static_cast<uint8_t>(from[k])) << (8 * k);
-        }
-        nxt[blk][i] = none[blk] ? 0u : v >> down[blk];
-      }
-  };
-  // four 4-bit two's complement values in the low nibbles, widened to bytes
-  auto widen = [](uint32_t v) {
-    v &= 0x0F0F0F0Fu;
-    const uint32_t neg = v & 0x08080808u;
-    return v | ((neg << 5) - (neg << 1));
-  };
-  // byte transpose: d[k] takes byte k of x[0..3]
-  auto transpose = [](const uint32_t (&x)[4], uint32_t (&d)[4]) {
-    const uint32_t p0 = __builtin_amdgcn_perm(x[1], x[0], 0x05010400u), p1 = __builtin_amdgcn_perm(x[1], x[0], 0x07030602u);
-    const uint32_t q0 = __builtin_amdgcn_perm(x[3], x[2], 0x05010400u), q1 = __builtin_amdgcn_perm(x[3], x[2], 0x07030602u);
-    d[0] = __builtin_amdgcn_perm(q0, p0, 0x05040100u);
-    d[1] = __builtin_amdgcn_perm(q0, p0, 0x07060302u);
-    d[2] = __builtin_amdgcn_perm(q1, p1, 0x05040100u);
-    d[3] = __builtin_amdgcn_perm(q1, p1, 0x07060302u);
-  };
-  load_step(0);
-  for (int64_t t0 = 0; t0 < a.n_time; t0 += kI8Step) {
-#pragma unroll
-    for (int blk = 0; blk < 2; ++blk) {
-      uint32_t re[4], im[4], dr[4], di[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        re[i] = widen(nxt[blk][i] >> 4);
-        im[i] = widen(nxt[blk][i]);
-      }
-      transpose(re, dr);
-      transpose(im, di);
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        *reinterpret_cast<uint32_t*>(&pl[2 * blk][4 * ag + k][4 * sg]) = dr[k];
-        *reinterpret_cast<uint32_t*>(&pl[2 * blk + 1][4 * ag + k][4 * sg]) = di[k];
-      }
-    }
+  i32x4 next[2][2];
+  load_step(pa, pb, next);
+  for (int64_t st = 0; st < steps; ++st) {
+    store_step<ROW>(pl, next);
     __syncthreads();
-    if (t0 + kI8Step < a.n_time) load_step(t0 + kI8Step);   // in flight during the products
-    i32x4 ar[kI8Blocks], ai[kI8Blocks], br[kI8Blocks], bi[kI8Blocks];
+    pa += fx_block_bytes(true);
+    pb += fx_block_bytes(true);
+    if (st + 1 < steps) load_step(pa, pb, next);   // in flight during the products
+    auto operand = [&](int blk, int part, int row) {
+      return *reinterpret_cast<const i32x4*>(pl + ((blk * 2 + part) * kFxTile + row) * PITCH + 16 * g);
+    };
+    i32x4 ar[2], ai[2], br[2], bi[2];
 #pragma unroll
-    for (int i = 0; i < kI8Blocks; ++i) {
-      ar[i] = *reinterpret_cast<const i32x4*>(&pl[0][16 * kI8Blocks * ah + 16 * i + l16][16 * g]);
-      ai[i] = *reinterpret_cast<const i32x4*>(&pl[1][16 * kI8Blocks * ah + 16 * i + l16][16 * g]);
-      br[i] = *reinterpret_cast<const i32x4*>(&pl[2][16 * kI8Blocks * bh + 16 * i + l16][16 * g]);
-      bi[i] = *reinterpret_cast<const i32x4*>(&pl[3][16 * kI8Blocks * bh + 16 * i + l16][16 * g]);
+    for (int i = 0; i < 2; ++i) {
+      ar[i] = operand(0, 0, 32 * ah + 16 * i + l16);
+      ai[i] = operand(0, 1, 32 * ah + 16 * i + l16);
+      br[i] = operand(1, 0, 32 * bh + 16 * i + l16);
+      bi[i] = operand(1, 1, 32 * bh + 16 * i + l16);
     }
 #pragma unroll
-    for (int i = 0; i < kI8Blocks; ++i)
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < kI8Blocks; ++j) {
+      for (int j = 0; j < 2; ++j) {
         acc[i][j][0] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ar[i], br[j], acc[i][j][0], 0, 0, 0);
         acc[i][j][1] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ai[i], bi[j], acc[i][j][1], 0, 0, 0);
         acc[i][j][2] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ai[i], br[j], acc[i][j][2], 0, 0, 0);
@@ -380,77 +362,99 @@ __global__ __launch_bounds__(256) void fx_correlate_i8_kernel(FxArgs a) {
       }
     __syncthreads();
   }
-  float2* V = a.V + static_cast<size_t>(cl) * na * na;
 #pragma unroll
-  for (int i = 0; i < kI8Blocks; ++i)
+  for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < kI8Blocks; ++j)
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int ia = a0 + 16 * kI8Blocks * ah + 16 * i + 4 * g + e, ib = b0 + 16 * kI8Blocks * bh + 16 * j + l16;
+        const int ia = ta * kFxTile + 32 * ah + 16 * i + 4 * g + e, ib = tb * kFxTile + 32 * bh + 16 * j + l16;
         if (ia >= na || ib >= na) continue;
         // E_a conj(E_b) = (xa xb + ya yb) + i (ya xb - xa yb)
         const double vr = static_cast<double>(acc[i][j][0][e]) + acc[i][j][1][e];
         const double vi = static_cast<double>(acc[i][j][2][e]) - acc[i][j][3][e];
         double zr = vr, zi = vi;
         if (a.gains) {
-          const float2 ga = a.gains[static_cast<size_t>(c) * na + ia], gb = a.gains[static_cast<size_t>(c) * na + ib];
+          const float2 ga = a.gains[static_cast<size_t>(c) * na + a.order[ia]];
+          const float2 gb = a.gains[static_cast<size_t>(c) * na + a.order[ib]];
           // g_a conj(g_b)
           const double gr = static_cast<double>(ga.x) * gb.x + static_cast<double>(ga.y) * gb.y;
           const double gi = static_cast<double>(ga.y) * gb.x - static_cast<double>(ga.x) * gb.y;
           zr = gr * vr - gi * vi;
           zi = gr * vi + gi * vr;
         }
-        V[static_cast<size_t>(ia) * na + ib] = make_float2(static_cast<float>(zr), static_cast<float>(zi));
+        put_visibility(a, cl, ia, ib, zr, zi);
       }
 }
 
-constexpr int kFxBinBatch = 8;   // pair loads in flight per thread of the binning
-
-// One thread per (channel, type pair, offset cell).  The thread of a cell at
-// or before its mirror (types swapped, offset negated) sums the cell's pairs
-// and writes the mirror cell as the conjugate; the thread of a later cell has
-// nothing to do.
+// The sums of one lag row, one workgroup per (summed row, channel): each of its
+// four waves adds a contiguous quarter of the row's pairs into a float64 row of
+// its own in LDS (a wave's adds to one element happen in its own order), and the
+// four are summed in order.  The row's entries are in the order of the
+// visibilities, whose antennas are sorted by cell, so that neighbouring lanes
+// read neighbouring elements of V (a thread per lag cell, with pairs scattered
+// over V, was bound by those reads: 302 us at 64 channels of 1024 antennas, BB
+// here; 84 and CC at 256 channels of 350).  Mirrors (types swapped, offset
+// negated) get the conjugates where the lag convolution reads them.
 __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
-  const int nl2 = a.NL * a.NL;
-  const size_t cells = static_cast<size_t>(a.n_types) * a.n_types * nl2;
+  extern __shared__ double fx_sums[];   // [4][2][NL]
+  const int NL = a.NL, nt = a.n_types, mid = NL / 2;
   int c;
-  unsigned blk;
-  if (!xcd_channel(blockIdx.x, static_cast<unsigned>((cells + 255) / 256), a.n_launch, &c, &blk)) return;
-  const size_t i = static_cast<size_t>(blk) * 256 + threadIdx.x;
-  if (i >= cells) return;
-  const int tp = static_cast<int>(i / nl2), off = static_cast<int>(i % nl2);
-  const size_t m = static_cast<size_t>((tp % a.n_types) * a.n_types + tp / a.n_types) * nl2 + (nl2 - 1 - off);
-  if (m < i) return;
+  unsigned r;
+  if (!xcd_channel(blockIdx.x, static_cast<unsigned>(a.n_rows), a.n_launch, &c, &r)) return;
+  const int k0 = a.row_ptr[r], n = a.row_ptr[r + 1] - k0;
+  if (n == 0 && nt == 1) return;   // (the row pass knows that it is zero)
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  for (int i = threadIdx.x; i < 8 * NL; i += 256) fx_sums[i] = 0.0;
+  __syncthreads();
   const float2* V = a.V + static_cast<size_t>(c) * a.n_ant * a.n_ant;
-  double x = 0.0, y = 0.0;
-  // Rows of short, redundant baselines hold hundreds of pairs: loads go out
-  // kFxBinBatch at a time (indices, then visibilities) and are summed in the
-  // same order as one at a time.
-  int k = a.pair_ptr[i];
-  const int k1 = a.pair_ptr[i + 1];
-  for (; k + kFxBinBatch <= k1; k += kFxBinBatch) {
-    uint32_t e[kFxBinBatch];
-    float2 v[kFxBinBatch];
+  double* sum = fx_sums + wave * 2 * NL;
+  const int k1 = k0 + static_cast<int>((wave + 1) * static_cast<int64_t>(n) / 4);
+  int k = k0 + static_cast<int>(wave * static_cast<int64_t>(n) / 4) + lane;
+  auto add = [&](uint32_t e, int dx, float2 v) {
+    unsafeAtomicAdd(sum + dx, static_cast<double>(v.x));
+    unsafeAtomicAdd(sum + NL + dx, static_cast<double>((e & kFxConjBit) ? -v.y : v.y));
+  };
+  constexpr int B = 4;   // entries in flight per lane
+  for (; k + (B - 1) * 64 < k1; k += B * 64) {
+    uint32_t e[B];
+    int dx[B];
+    float2 v[B];
 #pragma unroll
-    for (int j = 0; j < kFxBinBatch; ++j) e[j] = static_cast<uint32_t>(a.pair_ab[k + j]);
-#pragma unroll
-    for (int j = 0; j < kFxBinBatch; ++j) v[j] = V[e[j] & ~kFxConjBit];
-#pragma unroll
-    for (int j = 0; j < kFxBinBatch; ++j) {
-      x += v[j].x;
-      y += (e[j] & kFxConjBit) ? -v[j].y : v[j].y;
+    for (int j = 0; j < B; ++j) {
+      e[j] = a.pair_ab[k + j * 64];
+      dx[j] = a.pair_dx[k + j * 64];
     }
+#pragma unroll
+    for (int j = 0; j < B; ++j) v[j] = V[e[j] & ~kFxConjBit];
+#pragma unroll
+    for (int j = 0; j < B; ++j) add(e[j], dx[j], v[j]);
   }
-  for (; k < k1; ++k) {
-    const uint32_t e = static_cast<uint32_t>(a.pair_ab[k]);
-    const float2 v = V[e & ~kFxConjBit];
-    x += v.x;
-    y += (e & kFxConjBit) ? -v.y : v.y;
+  for (; k < k1; k += 64) {
+    const uint32_t e = a.pair_ab[k];
+    add(e, a.pair_dx[k], V[e & ~kFxConjBit]);
   }
-  float2* H = a.H + static_cast<size_t>(c) * cells;
-  H[i] = make_float2(static_cast<float>(x), static_cast<float>(y));
-  if (m != i) H[m] = make_float2(static_cast<float>(x), static_cast<float>(-y));
+  __syncthreads();
+  const int tp = a.rows[r] / NL, dy = a.rows[r] % NL, p = tp / nt, q = tp % nt;
+  const bool half_row = p == q && dy == mid;   // only columns up to the zero lag were summed
+  const size_t plane = static_cast<size_t>(nt == 1 ? a.L : NL) * NL;
+  float2* H = a.H + static_cast<size_t>(c) * nt * nt * plane;
+  // rows that the lag convolution reads: up to the zero lag and the responses' reach
+  const int reach = mid + a.xs;
+  for (int x = threadIdx.x; x < NL; x += 256) {
+    const int from = half_row && x > mid ? NL - 1 - x : x;
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      re += fx_sums[w * 2 * NL + from];
+      im += fx_sums[w * 2 * NL + NL + from];
+    }
+    const float2 v = make_float2(static_cast<float>(re), static_cast<float>(from == x ? im : -im));
+    if (dy <= reach) H[static_cast<size_t>(tp) * plane + static_cast<size_t>(dy) * NL + x] = v;
+    if (nt > 1 && NL - 1 - dy <= reach && !half_row)
+      H[static_cast<size_t>(q * nt + p) * plane + static_cast<size_t>(NL - 1 - dy) * NL + (NL - 1 - x)] =
+          make_float2(v.x, -v.y);
+  }
 }
 
 // One workgroup per (16 x 64 block of lag cells, channel); each thread owns
@@ -557,56 +561,6 @@ __global__ __launch_bounds__(256) void fx_lag_kernel(FxArgs a) {
   }
 }
 
-// One table type: only the cells that hold pairs are summed, and the pair
-// response is applied to the image (its transform is the table's power
-// pattern), so no lag grid is formed.  Cells are listed in cell order, those
-// at or before their mirror; LANES lanes share a cell and take its pairs in
-// turn, their float64 sums meeting in a fixed order.  (A dense lag grid of one
-// thread per cell left most threads without pairs and the others with up to
-// hundreds: 158 us for the binning, 195 for the lag convolution at 256 channels
-// of 350 redundant antennas, N = 256, where this kernel takes 84, bound by the
-// scattered 8-byte reads of V.)
-template <int LANES>
-__global__ __launch_bounds__(256) void fx_bin_cells_kernel(FxArgs a) {
-  int c;
-  unsigned blk;
-  constexpr int PER = 256 / LANES;   // cells per workgroup
-  if (!xcd_channel(blockIdx.x, static_cast<unsigned>((a.n_cells + PER - 1) / PER), a.n_launch, &c, &blk)) return;
-  const int cell = static_cast<int>(blk) * PER + threadIdx.x / LANES, sub = threadIdx.x % LANES;
-  double x = 0.0, y = 0.0;
-  if (cell < a.n_cells) {
-    const float2* V = a.V + static_cast<size_t>(c) * a.n_ant * a.n_ant;
-    const int i = a.cell_at[cell];
-    const int k1 = a.pair_ptr[i + 1];
-    int k = a.pair_ptr[i] + sub;
-    auto add = [&](uint32_t e, float2 v) {
-      x += v.x;
-      y += (e & kFxConjBit) ? -v.y : v.y;
-    };
-    for (; k + 3 * LANES < k1; k += 4 * LANES) {
-      uint32_t e[4];
-      float2 v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) e[j] = static_cast<uint32_t>(a.pair_ab[k + j * LANES]);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = V[e[j] & ~kFxConjBit];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) add(e[j], v[j]);
-    }
-    for (; k < k1; k += LANES) {
-      const uint32_t e = static_cast<uint32_t>(a.pair_ab[k]);
-      add(e, V[e & ~kFxConjBit]);
-    }
-  }
-#pragma unroll
-  for (int off = LANES / 2; off >= 1; off >>= 1) {
-    x += __shfl_down(x, off, LANES);
-    y += __shfl_down(y, off, LANES);
-  }
-  if (cell < a.n_cells && sub == 0)
-    a.H[static_cast<size_t>(c) * a.n_cells + cell] = make_float2(static_cast<float>(x), static_cast<float>(y));
-}
-
 // The lag grid's transform, N-point lines as PA x QB: pass A (job n2) takes the
 // PA-point transform of points QB n1 + n2 in registers, pass B (job q1) the
 // QB-point transform over n2 of its outputs q1 times w^(n2 q1), output
@@ -629,52 +583,35 @@ __device__ __forceinline__ float2 odd_sign(int n, float2 v) { return (n & 1) ? m
 // Row pass: one workgroup per (block of lag rows, channel).  With
 // R(-l) = conj R(l), the transform of lag row NL - 1 - ly is the conjugate of
 // that of row ly, so only rows up to the zero lag, L - 1, are transformed.
-// CELLS: a row comes from the list of cells (row L - 1: its other half is the
-// mirror), else from the lag grid.
-template <int N, bool CELLS>
+// ONE: one table type, rows of pair sums (a row without pairs is not written and
+// reads as zero); else rows of the lag grid.
+template <int N, bool ONE>
 __global__ __launch_bounds__(256) void fx_row_kernel(FxArgs a) {
   using F = FxLine<N>;
   constexpr int PA = F::PA, QB = F::QB, L = F::L, NL = F::NL, PITCH = PA * (QB + 1);
-  __shared__ float2 X[kFxLines * (PITCH > N ? PITCH : N)];
+  __shared__ float2 X[kFxLines * PITCH];
   __shared__ float2 tw[N];
   const int c = blockIdx.y, ly0 = blockIdx.x * kFxLines;
   for (int i = threadIdx.x; i < N; i += 256) tw[i] = a.tw[i];
-  if constexpr (CELLS) {
-    for (int i = threadIdx.x; i < kFxLines * N; i += 256) X[i] = make_float2(0.f, 0.f);
-    __syncthreads();
-    const int last = ly0 + kFxLines < L ? ly0 + kFxLines : L;
-    const float2* H = a.H + static_cast<size_t>(c) * a.n_cells;
-    for (int i = a.row_ptr[ly0] + threadIdx.x; i < a.row_ptr[last]; i += 256) {
-      const int at = a.cell_at[i], ly = at / NL, n = (at % NL - (L - 1)) & (N - 1);
-      const float2 v = odd_sign(n, H[i]);
-      X[(ly - ly0) * N + n] = v;
-      if (ly == L - 1 && n != 0) X[(ly - ly0) * N + (N - n)] = make_float2(v.x, -v.y);
-    }
-  }
   __syncthreads();
   constexpr int JA = (kFxLines * QB + 255) / 256;   // pass-A jobs per thread
   float2 x[JA][PA];
-  const float2* R = CELLS ? nullptr : a.R + static_cast<size_t>(c) * NL * NL;
+  const float2* R = ONE ? a.H + static_cast<size_t>(c) * L * NL : a.R + static_cast<size_t>(c) * NL * NL;
 #pragma unroll
   for (int j = 0; j < JA; ++j) {
     const int job = threadIdx.x + 256 * j, k = job / QB, n2 = job % QB, ly = ly0 + k;
     if (k >= kFxLines) continue;
+    bool row = ly < L;
+    if constexpr (ONE) row = row && a.row_ptr[ly + 1] > a.row_ptr[ly];
 #pragma unroll
     for (int n1 = 0; n1 < PA; ++n1) {
-      const int n = QB * n1 + n2;
-      if constexpr (CELLS) {
-        x[j][n1] = X[k * N + n];
-      } else {
-        const int d = n < L ? n : n - N;
-        x[j][n1] = (ly < L && d >= -(L - 1))
-                       ? odd_sign(n, R[static_cast<size_t>(ly) * NL + d + L - 1]) : make_float2(0.f, 0.f);
-      }
+      const int n = QB * n1 + n2, d = n < L ? n : n - N;
+      x[j][n1] = (row && d >= -(L - 1)) ? odd_sign(n, R[static_cast<size_t>(ly) * NL + d + L - 1]) : make_float2(0.f, 0.f);
     }
     Dft<PA>::run(x[j]);
 #pragma unroll
     for (int q1 = 1; q1 < PA; ++q1) x[j][q1] = c_mul(x[j][q1], tw[n2 * q1]);
   }
-  if constexpr (CELLS) __syncthreads();   // every line is read before it is overwritten
 #pragma unroll
   for (int j = 0; j < JA; ++j) {
     const int job = threadIdx.x + 256 * j, k = job / QB, n2 = job % QB;
@@ -701,8 +638,9 @@ __global__ __launch_bounds__(256) void fx_row_kernel(FxArgs a) {
 // transform is real and the rows up to the zero lag hold all of it: columns q
 // and q + CW go through one complex transform as Z(., q) + i Z(., q + CW), and
 // the real and imaginary parts of the result are the two image columns.
-// CELLS: times the one table's power pattern (its pair response).
-template <int N, bool CELLS>
+// ONE: times the one table's power pattern, the transform of its pair response
+// (no lag grid is formed: its convolution took 195 us at 256 channels, N = 256).
+template <int N, bool ONE>
 __global__ __launch_bounds__(256) void fx_col_kernel(FxArgs a) {
   using F = FxLine<N>;
   constexpr int PA = F::PA, QB = F::QB, L = F::L, CW = N / 2 < kFxLines ? N / 2 : kFxLines;
@@ -744,7 +682,7 @@ __global__ __launch_bounds__(256) void fx_col_kernel(FxArgs a) {
     for (int q2 = 0; q2 < QB; ++q2) {
       const size_t pix = static_cast<size_t>(q1 + PA * q2) * N + q0 + k;
       double s1 = a.scale, s2 = a.scale;
-      if constexpr (CELLS) {
+      if constexpr (ONE) {
         s1 *= a.Pp[pix];
         s2 *= a.Pp[pix + CW];
       }
@@ -756,25 +694,25 @@ __global__ __launch_bounds__(256) void fx_col_kernel(FxArgs a) {
 
 namespace {
 
-template <int N, bool CELLS>
+template <int N, bool ONE>
 hipError_t launch_fx_transform(const FxArgs& a, hipStream_t st) {
   constexpr int CW = N / 2 < kFxLines ? N / 2 : kFxLines;
-  hipLaunchKernelGGL((fx_row_kernel<N, CELLS>), dim3((N / 2 + kFxLines - 1) / kFxLines, a.n_launch), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((fx_row_kernel<N, ONE>), dim3((N / 2 + kFxLines - 1) / kFxLines, a.n_launch), dim3(256), 0, st, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((fx_col_kernel<N, CELLS>), dim3(N / (2 * CW), a.n_launch), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((fx_col_kernel<N, ONE>), dim3(N / (2 * CW), a.n_launch), dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
-template <bool CELLS>
+template <bool ONE>
 hipError_t launch_fx_transform_n(const FxArgs& a, hipStream_t st) {
   switch (a.N) {
-    case 8: return launch_fx_transform<8, CELLS>(a, st);
-    case 16: return launch_fx_transform<16, CELLS>(a, st);
-    case 32: return launch_fx_transform<32, CELLS>(a, st);
-    case 64: return launch_fx_transform<64, CELLS>(a, st);
-    case 128: return launch_fx_transform<128, CELLS>(a, st);
-    case 256: return launch_fx_transform<256, CELLS>(a, st);
+    case 8: return launch_fx_transform<8, ONE>(a, st);
+    case 16: return launch_fx_transform<16, ONE>(a, st);
+    case 32: return launch_fx_transform<32, ONE>(a, st);
+    case 64: return launch_fx_transform<64, ONE>(a, st);
+    case 128: return launch_fx_transform<128, ONE>(a, st);
+    case 256: return launch_fx_transform<256, ONE>(a, st);
     default: return hipErrorInvalidValue;
   }
 }
@@ -785,38 +723,26 @@ hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st) {
   if (a.n_ant < 1 || a.n_launch < 1 || a.n_launch > 65535 || a.c0 < 0 || a.c0 + a.n_launch > a.n_chan || a.N < 8 ||
       a.N > 256 || a.NL != 2 * a.L - 1 || a.n_types < 1 || a.n_types > kMaxTypesDev)
     return hipErrorInvalidValue;
+  const size_t nt = static_cast<size_t>((a.n_ant + kFxTile - 1) / kFxTile);
+  const int64_t steps = (a.t1 - a.t0 + fx_step(ci4) - 1) / fx_step(ci4);
+  const size_t blocks = xcd_grid(nt * (nt + 1) / 2, a.n_launch);
+  const size_t bin_blocks = xcd_grid(static_cast<size_t>(a.n_rows), a.n_launch);
+  if (steps < 1 || steps > 0x7FFFFFFF || blocks > 0x7FFFFFFFu || bin_blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
+  const dim3 stage(static_cast<unsigned>(steps), static_cast<unsigned>(nt), a.n_launch);
+  hipError_t e;
   if (ci4) {
-    const size_t nt = static_cast<size_t>((a.n_ant + kI8Tile - 1) / kI8Tile);
-    const size_t blocks = xcd_grid(nt * (nt + 1) / 2, a.n_launch);
-    if (blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fx_stage_i8_kernel, stage, dim3(256), 0, st, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(fx_correlate_i8_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
   } else {
-    const size_t nt = static_cast<size_t>((a.n_ant + kC64Tile - 1) / kC64Tile);
-    const size_t blocks = xcd_grid(nt * (nt + 1) / 2, a.n_launch);
-    if (blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(fx_stage_c64_kernel, stage, dim3(256), 0, st, a);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(fx_correlate_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
   }
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (a.n_types == 1) {
-    if (a.n_cells > 0) {
-      // sixteen lanes per cell where cells hold several pairs each (redundant
-      // arrays), else one
-      const bool many = a.n_pairs >= 8 * static_cast<int64_t>(a.n_cells);
-      const size_t per = many ? 16 : 256;
-      const size_t blocks = xcd_grid((static_cast<size_t>(a.n_cells) + per - 1) / per, a.n_launch);
-      if (blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
-      if (many) hipLaunchKernelGGL(fx_bin_cells_kernel<16>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL(fx_bin_cells_kernel<1>, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
-    }
-    return launch_fx_transform_n<true>(a, st);
-  }
-  const size_t cells = static_cast<size_t>(a.n_types) * a.n_types * a.NL * a.NL;
-  const size_t bin_blocks = xcd_grid((cells + 255) / 256, a.n_launch);
-  if (bin_blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(fx_bin_kernel, dim3(static_cast<unsigned>(bin_blocks)), dim3(256), 0, st, a);
+  if ((e = hipGetLastError()) != hipSuccess || !a.last) return e;
+  hipLaunchKernelGGL(fx_bin_kernel, dim3(static_cast<unsigned>(bin_blocks)), dim3(256), sizeof(double) * 8 * a.NL, st, a);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (a.n_types == 1) return launch_fx_transform_n<true>(a, st);
   const unsigned lag_bx = static_cast<unsigned>((a.NL + kLagCols - 1) / kLagCols);
   const unsigned lag_by = static_cast<unsigned>((a.L + kLagRows - 1) / kLagRows);   // rows 0 .. L - 1
   const size_t lag_lds =

@@ -4,6 +4,7 @@
 
 #include <algorithm>
 #include <complex>
+#include <numeric>
 
 namespace moff {
 
@@ -38,44 +39,47 @@ void build_fx_tables(const HostPlan& hp, bool keep_autos, FxTables* t) {
           dst[2 * (u * xs + v) + 1] = static_cast<float>(X[static_cast<size_t>(u) * side + v].imag());
         }
     }
-  // CSR of the ordered pairs by (type pair, offset cell), by counting sort.
-  // The pair (b, a) lands in the mirror row -- types swapped, offset negated --
-  // with the conjugate visibility, so only rows that do not follow their mirror
-  // hold entries; the device sums those and writes each mirror as the
-  // conjugate.  An entry names the upper-triangle element min(a, b) n_ant +
-  // max(a, b), with the top bit set when a > b (conjugate on reading).
-  const size_t rows = static_cast<size_t>(nt) * nt * NL * NL;
-  auto row_of = [&](int a, int b) {
-    const int tp = hp.ant_ktype[a] * nt + hp.ant_ktype[b];
-    const int dy = hp.iy0[a] - hp.iy0[b] + L - 1, dx = hp.ix0[a] - hp.ix0[b] + L - 1;
-    return (static_cast<size_t>(tp) * NL + dy) * NL + dx;
-  };
-  auto canonical = [&](int a, int b) { return row_of(a, b) <= row_of(b, a); };
-  auto keep = [&](int a, int b) { return (a != b || keep_autos) && canonical(a, b); };
-  t->ptr.assign(rows + 1, 0);
-  for (int a = 0; a < na; ++a)
-    for (int b = 0; b < na; ++b)
-      if (keep(a, b)) ++t->ptr[row_of(a, b) + 1];
-  for (size_t r = 0; r < rows; ++r) t->ptr[r + 1] += t->ptr[r];
-  t->ab.assign(static_cast<size_t>(t->ptr[rows]), 0);
-  std::vector<int32_t> fill(t->ptr.begin(), t->ptr.end() - 1);
-  for (int a = 0; a < na; ++a)
-    for (int b = 0; b < na; ++b)
-      if (keep(a, b)) {
-        const uint32_t upper = static_cast<uint32_t>(std::min(a, b)) * na + std::max(a, b);
-        t->ab[static_cast<size_t>(fill[row_of(a, b)]++)] = static_cast<int32_t>(upper | (a > b ? kFxConjBit : 0u));
-      }
-  if (nt == 1) {
-    t->row_ptr.assign(L + 1, 0);
-    for (int ly = 0; ly < L; ++ly) {
-      t->row_ptr[ly] = static_cast<int32_t>(t->cell_at.size());
-      for (int lx = 0; lx < NL; ++lx) {
-        const int i = ly * NL + lx;
-        if (t->ptr[i + 1] > t->ptr[i]) t->cell_at.push_back(i);
-      }
+  // antennas by footprint cell
+  t->order.resize(na);
+  std::iota(t->order.begin(), t->order.end(), 0);
+  std::stable_sort(t->order.begin(), t->order.end(), [&](int x, int y) {
+    return hp.iy0[x] != hp.iy0[y] ? hp.iy0[x] < hp.iy0[y] : hp.ix0[x] < hp.ix0[y];
+  });
+  // lag rows that are summed, and the entries of each, by counting sort
+  std::vector<int32_t> base(static_cast<size_t>(nt) * nt, -1);
+  for (int p = 0; p < nt; ++p)
+    for (int q = p; q < nt; ++q) {
+      base[p * nt + q] = static_cast<int32_t>(t->rows.size());
+      for (int dy = 0; dy < (p == q ? L : NL); ++dy) t->rows.push_back((p * nt + q) * NL + dy);
     }
-    t->row_ptr[L] = static_cast<int32_t>(t->cell_at.size());
-  }
+  auto row_of = [&](int a, int b, int* dx) {   // antennas; -1: the mirror is summed
+    const int p = hp.ant_ktype[a], q = hp.ant_ktype[b];
+    const int dy = hp.iy0[a] - hp.iy0[b] + L - 1;
+    *dx = hp.ix0[a] - hp.ix0[b] + L - 1;
+    if (p > q || (p == q && (dy > L - 1 || (dy == L - 1 && *dx > L - 1)))) return -1;
+    return base[p * nt + q] + dy;
+  };
+  auto each = [&](auto&& f) {
+    for (int i = 0; i < na; ++i)
+      for (int j = 0; j < na; ++j) {
+        if (i == j && !keep_autos) continue;
+        int dx = 0;
+        const int r = row_of(t->order[i], t->order[j], &dx);
+        if (r >= 0) f(i, j, r, dx);
+      }
+  };
+  t->ptr.assign(t->rows.size() + 1, 0);
+  each([&](int, int, int r, int) { ++t->ptr[r + 1]; });
+  for (size_t r = 0; r < t->rows.size(); ++r) t->ptr[r + 1] += t->ptr[r];
+  t->ab.assign(static_cast<size_t>(t->ptr.back()), 0);
+  t->dx.assign(t->ab.size(), 0);
+  std::vector<int32_t> fill(t->ptr.begin(), t->ptr.end() - 1);
+  each([&](int i, int j, int r, int dx) {
+    const uint32_t upper = static_cast<uint32_t>(std::min(i, j)) * na + std::max(i, j);
+    const size_t at = static_cast<size_t>(fill[r]++);
+    t->ab[at] = static_cast<int32_t>(upper | (i > j ? kFxConjBit : 0u));
+    t->dx[at] = static_cast<uint16_t>(dx);
+  });
 }
 
 }  // namespace moff
