@@ -159,8 +159,8 @@ __global__ __launch_bounds__(256) void fx_stage_i8_kernel(FxArgs a) {
 
 // The correlators: V_ab for a <= b (V_ba = conj V_ab, and the binning reads the
 // upper triangle only), one workgroup per (64 x 64 antenna tile on or above the
-// diagonal, channel), four waves of a 32 x 32 sub-tile each (2 x 2 blocks of
-// 16 x 16).  Per step both antenna blocks are copied into LDS, the next step's
+// diagonal, channel), four waves of a 32 x 32 sub-tile each, or eight of 32 x 16
+// (blocks of 16 x 16).  Per step both antenna blocks are copied into LDS, the next step's
 // copies in flight meanwhile.  A and B take their samples in the same lane
 // order, so each is summed once whatever order the instruction gives its
 // contraction index; accumulators hold D[4 (l / 16) + v][l % 16].
@@ -183,22 +183,22 @@ __device__ __forceinline__ bool corr_tile(const FxArgs& a, int* cl, int* ta, int
 // Copies of one step: 16 bytes per thread and round, both blocks, into LDS rows
 // of ROW bytes at a pitch 16 bytes longer (operand reads of 16 rows then hit
 // distinct banks).
-template <int ROUNDS>
+template <int NT, int ROUNDS>
 __device__ __forceinline__ void load_step(const char* a, const char* b, i32x4 (&v)[2][ROUNDS]) {
 #pragma unroll
   for (int r = 0; r < ROUNDS; ++r) {
-    v[0][r] = reinterpret_cast<const i32x4*>(a)[r * 256 + threadIdx.x];
-    v[1][r] = reinterpret_cast<const i32x4*>(b)[r * 256 + threadIdx.x];
+    v[0][r] = reinterpret_cast<const i32x4*>(a)[r * NT + threadIdx.x];
+    v[1][r] = reinterpret_cast<const i32x4*>(b)[r * NT + threadIdx.x];
   }
 }
-template <int ROW, int ROUNDS>
+template <int NT, int ROW, int ROUNDS>
 __device__ __forceinline__ void store_step(char* lds, const i32x4 (&v)[2][ROUNDS]) {   // [block][row]
 #pragma unroll
   for (int blk = 0; blk < 2; ++blk)
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
-      const int at = (r * 256 + threadIdx.x) * 16;
-      *reinterpret_cast<i32x4*>(lds + (blk * (ROUNDS * 4096 / ROW) + at / ROW) * (ROW + 16) + at % ROW) = v[blk][r];
+      const int at = (r * NT + threadIdx.x) * 16;
+      *reinterpret_cast<i32x4*>(lds + (blk * (ROUNDS * NT * 16 / ROW) + at / ROW) * (ROW + 16) + at % ROW) = v[blk][r];
     }
 }
 
@@ -226,71 +226,74 @@ __device__ __forceinline__ void put_visibility(const FxArgs& a, int cl, int ia, 
 //   Re V_ab = sum x_a x_b + y_a y_b,   Im V_ab = sum y_a x_b - x_a y_b;
 // each 32-sample step is summed in float32 and the steps in float64.  At 64
 // channels x 128 samples of 1024 antennas: 438 us with the float32 instruction,
-// 294 with the levels made by every tile, ZZ here and PP for the staging; the
-// products take 87 at their peak rate.
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void fx_correlate_kernel(FxArgs a) {
-  constexpr int ROW = kC64Step * 2, PITCH = ROW + 16;
+// 294 with the levels made by every tile, 235-258 here (eight waves; 268 with
+// four of 32 x 32) and 40 for the staging.  The products take 87 at their peak
+// rate, the LDS 109, the vector work 75, hardly overlapped.
+constexpr int kC64Threads = 512;
+
+__global__ __launch_bounds__(kC64Threads) __attribute__((amdgpu_waves_per_eu(4))) void fx_correlate_kernel(FxArgs a) {
+  constexpr int NT = kC64Threads, ROW = kC64Step * 2, PITCH = ROW + 16;
   __shared__ __attribute__((aligned(16))) char pl[2 * 6 * kFxTile * PITCH];   // [block][x, y][level][antenna]
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wa = wave >> 1, wb = wave & 1, r16 = lane & 15, kk = lane >> 4;
+  const int wa = wave >> 2, wb = wave & 3, r16 = lane & 15, kk = lane >> 4;
   const int na = a.n_ant, tiles = (na + kFxTile - 1) / kFxTile;
   int cl, ta, tb;
   if (!corr_tile(a, &cl, &ta, &tb)) return;
   const int64_t steps = (a.t1 - a.t0 + kC64Step - 1) / kC64Step;
   const char* pa = a.planes + (static_cast<size_t>(cl) * tiles + ta) * steps * fx_block_bytes(false);
   const char* pb = a.planes + (static_cast<size_t>(cl) * tiles + tb) * steps * fx_block_bytes(false);
-  double acc[2][2][4][2] = {};
-  i32x4 next[2][6];
-  load_step(pa, pb, next);
+  double acc[2][4][2] = {};
+  i32x4 next[2][3];
+  load_step<NT>(pa, pb, next);
   for (int64_t st = 0; st < steps; ++st) {
-    store_step<ROW>(pl, next);
+    store_step<NT, ROW>(pl, next);
     __syncthreads();
     pa += fx_block_bytes(false);
     pb += fx_block_bytes(false);
-    if (st + 1 < steps) load_step(pa, pb, next);   // in flight during the products
+    if (st + 1 < steps) load_step<NT>(pa, pb, next);   // in flight during the products
     auto operand = [&](int blk, int part, int l, int row) {
       return *reinterpret_cast<const b16x8*>(pl + (((blk * 2 + part) * 3 + l) * kFxTile + row) * PITCH + 16 * kk);
     };
+    b16x8 B[2][3];
+#pragma unroll
+    for (int part = 0; part < 2; ++part)
+#pragma unroll
+      for (int l = 0; l < 3; ++l) B[part][l] = operand(1, part, l, 16 * wb + r16);
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      b16x8 A[2][3];
+      // the small terms of both products first, so that a step's sum rounds
+      // twice at full size
+      f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
+      b16x8 hi[2];
 #pragma unroll
-      for (int part = 0; part < 2; ++part)
+      for (int part = 0; part < 2; ++part) {
+        b16x8 A[3];
 #pragma unroll
-        for (int l = 0; l < 3; ++l) A[part][l] = operand(0, part, l, 32 * wa + 16 * i + r16);
+        for (int l = 0; l < 3; ++l) A[l] = operand(0, part, l, 32 * wa + 16 * i + r16);
+        hi[part] = A[0];
+        const b16x8(&X)[3] = B[part];       // x_a x_b, y_a y_b
+        const b16x8(&Y)[3] = B[1 - part];   // - x_a y_b, y_a x_b
+        auto sign = [&](b16x8 v) { return part == 0 ? -v : v; };
+        auto mm = [](b16x8 x, b16x8 y, f32x4 r) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x, y, r, 0, 0, 0); };
+        re = mm(A[2], X[0], re);
+        im = mm(A[2], sign(Y[0]), im);
+        re = mm(A[0], X[2], re);
+        im = mm(A[0], sign(Y[2]), im);
+        re = mm(A[1], X[1], re);
+        im = mm(A[1], sign(Y[1]), im);
+        re = mm(A[1], X[0], re);
+        im = mm(A[1], sign(Y[0]), im);
+        re = mm(A[0], X[1], re);
+        im = mm(A[0], sign(Y[1]), im);
+      }
+      re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi[0], B[0][0], re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi[1], B[0][0], im, 0, 0, 0);
+      re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi[1], B[1][0], re, 0, 0, 0);
+      im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(hi[0], -B[1][0], im, 0, 0, 0);
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        b16x8 B[2][3];
-#pragma unroll
-        for (int part = 0; part < 2; ++part)
-#pragma unroll
-          for (int l = 0; l < 3; ++l) B[part][l] = operand(1, part, l, 32 * wb + 16 * j + r16);
-        // the small terms of both products first, so that a step's sum rounds
-        // twice at full size
-        auto terms = [&](const b16x8 (&x)[3], const b16x8 (&y)[3], f32x4 r) {
-          r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[2], y[0], r, 0, 0, 0);
-          r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[0], y[2], r, 0, 0, 0);
-          r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[1], y[1], r, 0, 0, 0);
-          r = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[1], y[0], r, 0, 0, 0);
-          return __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[0], y[1], r, 0, 0, 0);
-        };
-        b16x8 N[3];   // - y_b
-#pragma unroll
-        for (int l = 0; l < 3; ++l) N[l] = -B[1][l];
-        f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
-        re = terms(A[0], B[0], re);
-        im = terms(A[1], B[0], im);
-        re = terms(A[1], B[1], re);
-        im = terms(A[0], N, im);
-        re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[0][0], B[0][0], re, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[1][0], B[0][0], im, 0, 0, 0);
-        re = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[1][0], B[1][0], re, 0, 0, 0);
-        im = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[0][0], N[0], im, 0, 0, 0);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          acc[i][j][v][0] += re[v];
-          acc[i][j][v][1] += im[v];
-        }
+      for (int v = 0; v < 4; ++v) {
+        acc[i][v][0] += re[v];
+        acc[i][v][1] += im[v];
       }
     }
     __syncthreads();
@@ -298,12 +301,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int ia = ta * kFxTile + 32 * wa + 16 * i + 4 * kk + v, ib = tb * kFxTile + 32 * wb + 16 * j + r16;
-        if (ia < na && ib < na) put_visibility(a, cl, ia, ib, acc[i][j][v][0], acc[i][j][v][1]);
-      }
+    for (int v = 0; v < 4; ++v) {
+      const int ia = ta * kFxTile + 32 * wa + 16 * i + 4 * kk + v, ib = tb * kFxTile + 16 * wb + r16;
+      if (ia < na && ib < na) put_visibility(a, cl, ia, ib, acc[i][v][0], acc[i][v][1]);
+    }
 }
 
 // 4+4-bit samples: the cross-products are exact integer sums, formed on the
@@ -312,7 +313,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void f
 // applied once, V_ab = g_a conj(g_b) sum_t E_a conj(E_b), in float64.  Bound by
 // what surrounds the products (6 % of the matrix rate): at 256 channels x 256
 // samples of 350 antennas 132 us with samples unpacked byte by byte for every
-// tile, ZZ here and PP for the staging (the V it writes, 126 MB, about 30).
+// tile, 55 here and 31 for the staging (the V it writes, 126 MB, about 30).
 __global__ __launch_bounds__(256) void fx_correlate_i8_kernel(FxArgs a) {
   constexpr int ROW = kI8Step, PITCH = ROW + 16;
   __shared__ __attribute__((aligned(16))) char pl[2 * 2 * kFxTile * PITCH];   // [block][re, im][antenna]
@@ -333,13 +334,13 @@ __global__ __launch_bounds__(256) void fx_correlate_i8_kernel(FxArgs a) {
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[i][j][q] = i32x4{0, 0, 0, 0};
   i32x4 next[2][2];
-  load_step(pa, pb, next);
+  load_step<256>(pa, pb, next);
   for (int64_t st = 0; st < steps; ++st) {
-    store_step<ROW>(pl, next);
+    store_step<256, ROW>(pl, next);
     __syncthreads();
     pa += fx_block_bytes(true);
     pb += fx_block_bytes(true);
-    if (st + 1 < steps) load_step(pa, pb, next);   // in flight during the products
+    if (st + 1 < steps) load_step<256>(pa, pb, next);   // in flight during the products
     auto operand = [&](int blk, int part, int row) {
       return *reinterpret_cast<const i32x4*>(pl + ((blk * 2 + part) * kFxTile + row) * PITCH + 16 * g);
     };
@@ -393,8 +394,8 @@ __global__ __launch_bounds__(256) void fx_correlate_i8_kernel(FxArgs a) {
 // four are summed in order.  The row's entries are in the order of the
 // visibilities, whose antennas are sorted by cell, so that neighbouring lanes
 // read neighbouring elements of V (a thread per lag cell, with pairs scattered
-// over V, was bound by those reads: 302 us at 64 channels of 1024 antennas, BB
-// here; 84 and CC at 256 channels of 350).  Mirrors (types swapped, offset
+// over V, was bound by those reads: 302 us at 64 channels of 1024 antennas, 148
+// here; 84 and 48 at 256 channels of 350).  Mirrors (types swapped, offset
 // negated) get the conjugates where the lag convolution reads them.
 __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
   extern __shared__ double fx_sums[];   // [4][2][NL]
@@ -566,7 +567,7 @@ __global__ __launch_bounds__(256) void fx_lag_kernel(FxArgs a) {
 // QB-point transform over n2 of its outputs q1 times w^(n2 q1), output
 // q1 + PA q2; one exchange through LDS in between.  (Radix-2 stages in LDS, a
 // barrier each, took 60 and 97 us for the row and the column pass at 256
-// channels, N = 256; these take 17 and 34.)
+// channels, N = 256; these take 26 and 33.)
 //
 // Lag d = j - (L - 1) of a lag-grid line is point n = d mod N with the factor
 // (-1)^d, so that the transform's output index is the pixel index:
@@ -737,7 +738,7 @@ hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st) {
   } else {
     hipLaunchKernelGGL(fx_stage_c64_kernel, stage, dim3(256), 0, st, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(fx_correlate_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL(fx_correlate_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kC64Threads), 0, st, a);
   }
   if ((e = hipGetLastError()) != hipSuccess || !a.last) return e;
   hipLaunchKernelGGL(fx_bin_kernel, dim3(static_cast<unsigned>(bin_blocks)), dim3(256), sizeof(double) * 8 * a.NL, st, a);
