@@ -19,6 +19,14 @@
 using moff::GatherEntry;
 using moff::HostPlan;
 
+// Work items per time slice, LDS bytes and resident workgroups of a variant.
+struct KernelFootprint {
+  int per_slice;
+  size_t lds;
+  int resident;
+  int threads;
+};
+
 struct moff_plan_s {
   HostPlan hp;
   int device = -1;
@@ -62,6 +70,8 @@ struct moff_plan_s {
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // fused launch configuration (heuristic default, or chosen by the autotuner)
   int cu_count = 0;
+  KernelFootprint footprints[moff::kMaxVariants + 1] = {};   // of every variant (queried at creation)
+  int adj_blocks[moff::kMaxVariants][4] = {};   // fused adjoint: workgroups per CU by variant and waves per SIMD (0: unfit)
   int variant = 0;          // index into hp.variants
   int slices = 0;           // time slices; 0 = heuristic
   bool tuned = false;
@@ -209,15 +219,9 @@ bool is_split(const HostPlan& hp, int variant) {
   return hp.split.on && variant == static_cast<int>(hp.variants.size());
 }
 
-// Work items per time slice, LDS bytes and resident workgroups of a variant.
-struct KernelFootprint {
-  int per_slice;
-  size_t lds;
-  int resident;
-  int threads;
-};
-
-KernelFootprint footprint(moff_plan p, int variant) {
+// The footprint of a variant, from the plan's device (an occupancy query of
+// several microseconds, so plans keep the answers).
+KernelFootprint query_footprint(moff_plan p, int variant) {
   const HostPlan& hp = p->hp;
   const bool ci4 = hp.flags & MOFF_IN_CI4;
   KernelFootprint f{};
@@ -241,6 +245,8 @@ KernelFootprint footprint(moff_plan p, int variant) {
   }
   return f;
 }
+
+const KernelFootprint& footprint(moff_plan p, int variant) { return p->footprints[variant]; }
 
 int n_variants(const HostPlan& hp) {
   return is_mfma(hp) ? 1 : static_cast<int>(hp.variants.size()) + (hp.split.on ? 1 : 0);
@@ -564,12 +570,11 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
   const int av = std::min<int>(p->adj_variant, static_cast<int>(hp.variants.size()) - 1);
   const HostPlan::Variant& AV = hp.variants[av];
   const size_t lds = moff::fused_lds_bytes(hp.N, av, AV.n_weights(), hp.n_ant);
-  if (!force_staged && p->d_adj_slots[av] && lds <= size_t(159) * 1024 &&
-      moff::adjoint_fused_blocks_per_cu(hp.N, av, ci4, p->adj_waves, lds) > 0) {
+  const int adj_blocks = p->adj_blocks[av][p->adj_waves];
+  if (!force_staged && p->d_adj_slots[av] && lds <= size_t(159) * 1024 && adj_blocks > 0) {
     // fused: every frame's grid, field and adjoint stay in LDS
     const int per_slice = AV.shape.SX * hp.n_chan;
-    const int resident =
-        std::max(1, moff::adjoint_fused_blocks_per_cu(hp.N, av, ci4, p->adj_waves, lds)) * std::max(1, p->cu_count);
+    const int resident = adj_blocks * std::max(1, p->cu_count);
     const int slices = static_cast<int>(
         std::max<int64_t>(1, std::min<int64_t>({(2 * resident + per_slice - 1) / per_slice, n_time, 64})));
     const int parts = slices * AV.shape.SX;
@@ -719,14 +724,8 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
       up(upload(&p->d_split_coef, T.coef.data(), sizeof(uint16_t) * T.coef.size()));
       p->variant = static_cast<int>(hp.variants.size());
     }
-    // Where the second FFT shape at N = 256 fits its LDS, its two classes of 512
-    // threads beat the four of 256 (23.3 against 28.7 ms at 1024 channels x 256
-    // samples of 350 antennas, 60 against 69 us at 4 x 23 of 578).
-    if (hp.N == 256 && hp.variants.size() > 1 &&
-        moff::fused_lds_bytes(hp.N, 1, hp.variants[1].n_weights(), hp.n_ant) <= size_t(159) * 1024)
-      p->variant = 1;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, hip_device) == hipSuccess) p->cu_count = prop.multiProcessorCount;
+    if (hipDeviceGetAttribute(&p->cu_count, hipDeviceAttributeMultiprocessorCount, hip_device) != hipSuccess)
+      p->cu_count = 0;
     if (hip_device < kMaxDevices) {
       void* sp = nullptr;
       up(noalloc_scratch(hip_device, &sp));
@@ -753,6 +752,22 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
       up(upload(&p->d_ktype_off, hp.ktype_off.data(), sizeof(int) * hp.ktype_off.size()));
     }
     if (s != MOFF_OK) return s;
+    for (int v = 0; v < n_variants(hp); ++v) p->footprints[v] = query_footprint(p, v);
+    for (size_t v = 0; v < hp.variants.size(); ++v) {
+      const size_t lds = moff::fused_lds_bytes(hp.N, static_cast<int>(v), hp.variants[v].n_weights(), hp.n_ant);
+      if (!p->d_adj_slots[v] || lds > size_t(159) * 1024) continue;
+      for (int w = 1; w <= moff::adjoint_waves_max(hp.N); ++w)
+        p->adj_blocks[v][w] = std::max(
+            0, moff::adjoint_fused_blocks_per_cu(hp.N, static_cast<int>(v), hp.flags & MOFF_IN_CI4, w, lds));
+    }
+    // Where the second FFT shape at N = 256 fits its LDS, its two classes of 512
+    // threads beat the four of 256 (image 23.3 against 28.7 ms at 1024 channels x
+    // 256 samples of 350 antennas, 60 against 69 us at 4 x 23 of 578), and so
+    // they do for the gradient (7.4 against 16.7 ms at 256 x 128 of 1024).
+    if (hp.N == 256 && hp.variants.size() > 1 && !is_mfma(hp)) {
+      if (p->footprints[1].lds <= size_t(159) * 1024) p->variant = 1;
+      if (p->adj_blocks[1][p->adj_waves] > 0) p->adj_variant = 1;
+    }
   }
   return MOFF_OK;
 }
@@ -1041,7 +1056,7 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
       const size_t alds = moff::fused_lds_bytes(hp.N, av, hp.variants[av].n_weights(), hp.n_ant);
       if (!p->d_adj_slots[av] || alds > size_t(159) * 1024) continue;
       for (int wv = 1; wv <= wmax && result == MOFF_OK; ++wv) {
-        if (moff::adjoint_fused_blocks_per_cu(hp.N, av, ci4, wv, alds) <= 0) continue;
+        if (p->adj_blocks[av][wv] <= 0) continue;
         p->adj_variant = av;
         p->adj_waves = wv;
         result = gain_vjp(p, E, n_time, gains, img, grad, st, false);   // warm-up (and workspace)

@@ -60,3 +60,28 @@ def test_fx_sample_scale(torch, moff, scale):
     w = synth.random_case(8, 20, 32, 1, 40, _tables(8, False, 1), extent_m=9.0, cell_m=1.0)
     w.E = (w.E * np.float32(scale)).astype(np.complex64)
     _check(torch, moff, w, f"scale {scale}")
+
+
+def test_fx_long_integration_in_passes(torch, moff):
+    """Staged samples that do not fit the workspace (about 2 GiB for eight
+    channels): the integration runs in two passes over time, the second ragged,
+    its visibilities summed in float64.  Two antennas give V = e_0 conj(e_1) and
+    an image that is its fringe, so the reference is one float64 sum."""
+    T, C = 400_003, 8
+    w = synth.random_case(1, 2, 8, C, 8, [np.ones((1, 1), np.complex64)], extent_m=2.0, cell_m=1.0)
+    rng = np.random.default_rng(0)
+    E = (rng.standard_normal((T, C, 2)) + 1j * rng.standard_normal((T, C, 2))).astype(np.complex64)
+    E[:, :, 1] += E[:, :, 0]
+    with moff.Plan.from_geometry(w.geom, device=0) as p:
+        got = p.image_fx(to_dev(torch, E), to_dev(torch, w.gains))
+        torch.cuda.synchronize()
+        got = got.cpu().numpy().astype(np.float64)
+    for c in (0, C - 1):
+        e = E[:, c].astype(np.complex128) * w.gains[c]
+        # one sample with the same product e_0 conj(e_1) has the same image
+        v = np.mean(e[:, 0] * np.conj(e[:, 1]))
+        one = np.array([[[v, 1.0]]])
+        g1 = synth.random_case(1, 2, 8, 1, 1, [np.ones((1, 1), np.complex64)], extent_m=2.0, cell_m=1.0).geom
+        ref = oracle.moff_channel(g1, one, None, 0)
+        assert np.abs(got[c] - ref).max() <= 1e-5 * np.abs(e).max() ** 2
+        assert np.abs(got[c] - ref).max() <= 1e-5 * np.mean(np.abs(e) ** 2) * 4
