@@ -106,61 +106,72 @@ __device__ __forceinline__ float2 rot(float2 a) {
   }
 }
 
-// Dense R-point DFT in registers (R = 1, 2, 4, 8, 16): radix-2 decimation in
-// time above a hand-written radix-4 leaf.
-template <int R>
+// Butterflies with the multiplication folded into their additions: with
+// w = c (1 + i t), t = tan(arg w), e +- w o = e +- c p for p = o + i t o, six
+// fused multiply-adds instead of the eight operations of a product and two sums
+// (Linzer and Feig, "Implementation of efficient FFT algorithms on fused
+// multiply-add architectures", 1993).  Past 45 degrees w = s (u + i) with the
+// cotangent u.  Each output is rounded once and p once.
+__device__ __forceinline__ float2 lf_tan(float2 o, float t) { return make_float2(fmaf(-o.y, t, o.x), fmaf(o.x, t, o.y)); }
+__device__ __forceinline__ float2 lf_cot(float2 o, float u) { return make_float2(fmaf(o.x, u, -o.y), fmaf(o.y, u, o.x)); }
+__device__ __forceinline__ float2 c_fma(float m, float2 p, float2 e) { return make_float2(fmaf(m, p.x, e.x), fmaf(m, p.y, e.y)); }
+
+// a = e + exp(2 pi i K / 32) o, b = e - exp(2 pi i K / 32) o.
+template <int K>
+__device__ __forceinline__ void butterfly(float2 e, float2 o, float2& a, float2& b) {
+  if constexpr (K % 8 == 0) {
+    const float2 t = rot16<K / 2>(o);
+    a = c_add(e, t);
+    b = c_sub(e, t);
+  } else {
+    constexpr float c = Root32::re(K), s = Root32::im(K);
+    constexpr bool cot = (c < 0 ? -c : c) < (s < 0 ? -s : s);
+    constexpr float m = cot ? s : c;
+    constexpr float q = static_cast<float>(cot ? static_cast<double>(c) / s : static_cast<double>(s) / c);
+    const float2 p = cot ? lf_cot(o, q) : lf_tan(o, q);
+    a = c_fma(m, p, e);
+    b = c_fma(-m, p, e);
+  }
+}
+
+// Dense R-point DFT in registers (R = 1, 2, 4, 8, 16) of x[n] exp(2 pi i n T / 32)
+// (T = 0: the plain DFT): radix-2 decimation in time, each level's butterflies
+// taking the twist of their own sub-sequence.
+template <int R, int T = 0>
 struct Dft {
   __device__ __forceinline__ static void run(float2* x) {
-    if constexpr (R == 1) {
-      return;
-    } else if constexpr (R == 2) {
-      float2 a = x[0], b = x[1];
-      x[0] = c_add(a, b);
-      x[1] = c_sub(a, b);
-    } else if constexpr (R == 4) {
-      float2 s02 = c_add(x[0], x[2]), d02 = c_sub(x[0], x[2]);
-      float2 s13 = c_add(x[1], x[3]), d13 = c_mul_i(c_sub(x[1], x[3]));
-      x[0] = c_add(s02, s13);
-      x[2] = c_sub(s02, s13);
-      x[1] = c_add(d02, d13);
-      x[3] = c_sub(d02, d13);
-    } else {
+    if constexpr (R > 1) {
       float2 e[R / 2], o[R / 2];
 #pragma unroll
       for (int m = 0; m < R / 2; ++m) {
         e[m] = x[2 * m];
         o[m] = x[2 * m + 1];
       }
-      Dft<R / 2>::run(e);
-      Dft<R / 2>::run(o);
+      Dft<R / 2, 2 * T % 32>::run(e);
+      Dft<R / 2, 2 * T % 32>::run(o);
       static_for<0, R / 2>([&](auto kc) {
         constexpr int k = decltype(kc)::value;
-        float2 t = rot<R, k>(o[k]);
-        x[k] = c_add(e[k], t);
-        x[k + R / 2] = c_sub(e[k], t);
+        butterfly<(T + k * (32 / R)) % 32>(e[k], o[k], x[k], x[k + R / 2]);
       });
     }
   }
 };
 
-// R-point DFT whose inputs x[n] are zero for n >= NZ (NZ a power of two <= R).
-// Decimation in frequency removes the zero half:
-//   X[2k]   = DFT_{R/2}(x[n])[k],  X[2k+1] = DFT_{R/2}(x[n] w_R^n)[k].
-// Only x[0 .. NZ-1] is read.
-template <int R, int NZ>
+// R-point DFT of x[n] exp(2 pi i n T / 32) whose inputs are zero for n >= NZ (NZ a
+// power of two <= R).  Decimation in frequency removes the zero half: the even
+// outputs are the R/2-point DFT of the same inputs, the odd ones that of the
+// inputs twisted by one more R-th root.  Only x[0 .. NZ-1] is read.
+template <int R, int NZ, int T = 0>
 __device__ __forceinline__ void dft_pruned(float2* x) {
   static_assert(NZ >= 1 && NZ <= R && (NZ & (NZ - 1)) == 0, "NZ must be a power of two <= R");
   if constexpr (NZ == R) {
-    Dft<R>::run(x);
+    Dft<R, T>::run(x);
   } else {
     float2 e[R / 2], o[R / 2];
-    static_for<0, NZ>([&](auto nc) {
-      constexpr int n = decltype(nc)::value;
-      e[n] = x[n];
-      o[n] = rot<R, n>(x[n]);
-    });
-    dft_pruned<R / 2, NZ>(e);
-    dft_pruned<R / 2, NZ>(o);
+#pragma unroll
+    for (int n = 0; n < NZ; ++n) e[n] = o[n] = x[n];
+    dft_pruned<R / 2, NZ, T>(e);
+    dft_pruned<R / 2, NZ, (T + 32 / R) % 32>(o);
 #pragma unroll
     for (int k = 0; k < R / 2; ++k) {
       x[2 * k] = e[k];
@@ -168,6 +179,68 @@ __device__ __forceinline__ void dft_pruned(float2* x) {
     }
   }
 }
+
+// A twisted DFT, X[k] = sum_n x[n] w_N^{n b} exp(2 pi i n k / R), with a twist b
+// known only at run time, 0 <= b R < N: six operations for every butterfly and none
+// for the twiddles, 192 at R = 16 where 15 twiddles and a plain DFT take 208 (at R = 8
+// 72 and 80).  Against 64 bits the power of a pruned 256-point column (16 x 16) comes
+// out at 1.20e-7 with it and 1.23e-7 with twiddles, but that of a 128-point one
+// (16 x 8) at 1.14e-7 and 1.09e-7: it is used at R = 16 only.
+// It takes R/2 factors, the level that joins sub-transforms to S points S/4 of them
+// (k and k + S/4 differ by a factor of i), one at S = 2.  Their angles lie below
+// 2 pi (k + 1) / S, so whether a factor is kept as (cosine, tangent) or (sine,
+// cotangent) is known beforehand (twist_cot); S = 2 reaches both ends and keeps
+// (cosine, sine).
+constexpr int twist_level(int R, int i) {
+  int S = R, off = 0;
+  while (S >= 4 && i >= off + S / 4) {
+    off += S / 4;
+    S /= 2;
+  }
+  return S;
+}
+constexpr int twist_offset(int R, int S) { return S == 2 ? R / 2 - 1 : R / 2 - S / 2; }
+constexpr bool twist_cot(int S, int k) { return 8 * k >= S && S > 4; }
+// Factor i of the R-point DFT twisted by b, from the table of w_N^k.
+template <int N>
+__device__ __forceinline__ float2 twist_factor(const float2* __restrict__ tw, int R, int i, int b) {
+  const int S = twist_level(R, i), k = i - twist_offset(R, S);
+  const float2 w = tw[(b * (R / S) + k * (N / S)) & (N - 1)];
+  if (S == 2) return w;
+  if (twist_cot(S, k)) return make_float2(w.y, static_cast<float>(static_cast<double>(w.x) / w.y));
+  return make_float2(w.x, static_cast<float>(static_cast<double>(w.y) / w.x));
+}
+
+template <int R, int TOP = R>
+struct TwistedDft {
+  __device__ __forceinline__ static void run(float2* x, const float2* f) {
+    if constexpr (R > 1) {
+      float2 e[R / 2], o[R / 2];
+#pragma unroll
+      for (int m = 0; m < R / 2; ++m) {
+        e[m] = x[2 * m];
+        o[m] = x[2 * m + 1];
+      }
+      TwistedDft<R / 2, TOP>::run(e, f);
+      TwistedDft<R / 2, TOP>::run(o, f);
+      if constexpr (R == 2) {   // (no tangent holds over a half turn: the difference from the sum)
+        const float2 w = f[twist_offset(TOP, 2)];
+        x[0] = make_float2(fmaf(o[0].x, w.x, fmaf(-o[0].y, w.y, e[0].x)), fmaf(o[0].x, w.y, fmaf(o[0].y, w.x, e[0].y)));
+        x[1] = make_float2(fmaf(2.f, e[0].x, -x[0].x), fmaf(2.f, e[0].y, -x[0].y));
+      } else {
+#pragma unroll
+        for (int k = 0; k < R / 2; ++k) {
+          const int kq = k % (R / 4);
+          const float2 w = f[twist_offset(TOP, R) + kq];
+          const float2 oi = k < R / 4 ? o[k] : c_mul_i(o[k]);
+          const float2 p = twist_cot(R, kq) ? lf_cot(oi, w.y) : lf_tan(oi, w.y);
+          x[k] = c_fma(w.x, p, e[k]);
+          x[k + R / 2] = c_fma(-w.x, p, e[k]);
+        }
+      }
+    }
+  }
+};
 
 // Inverse-direction R-point DFT, X[k] = sum_n x[n] exp(-2 pi i n k / R), through
 // conjugation: conj(DFT(conj(x))).

@@ -64,6 +64,7 @@ struct FT {
   static constexpr int GRID = L * P;             // folded grid, complex elements
   static constexpr int TWR = PR * QR;            // row twiddle table [q1][n2]
   static constexpr int TWC = PC * QC;            // column twiddle table [q1][n2]
+  static constexpr bool TWIST = QC == 16;        // col_stage takes the column twiddles as twists (dft.h)
   static constexpr int NACC = CSTEPS * 2 * JB * QC;
   static_assert(PR * QR == M && PC * QC == N, "bad factorisation");
   static_assert(PH * QC == L, "column half-round must fill the L slots");
@@ -76,16 +77,23 @@ struct FT {
 //                        factor is the part of the fold twiddle w_N^{n' w},
 //                        n' = QR n1 + n2, that does not depend on n1)
 //   twc[q1 * QC + n2] = w_N^{n2 q1}               (column pass-A outputs)
-template <int N, int V>
+// or, for col_stage where it twists (COL),
+//   twc[q1 * QC/2 + i]: factors of the column's pass-B DFT twisted by q1.
+template <int N, int V, bool COL>
 __device__ __forceinline__ void build_twiddles(const float2* __restrict__ tw_global, int w, float2* twr, float2* twc) {
   using C = FT<N, V>;
   for (int i = threadIdx.x; i < C::TWR; i += C::NT) {
     const int q1 = i / C::QR, n2 = i % C::QR;
     twr[i] = tw_global[(C::SX * n2 * q1 + n2 * w) & (N - 1)];
   }
-  for (int i = threadIdx.x; i < C::TWC; i += C::NT) {
-    const int q1 = i / C::QC, n2 = i % C::QC;
-    twc[i] = tw_global[(n2 * q1) & (N - 1)];
+  if constexpr (COL && C::TWIST) {
+    for (int i = threadIdx.x; i < C::TWC / 2; i += C::NT)
+      twc[i] = twist_factor<N>(tw_global, C::QC, i % (C::QC / 2), i / (C::QC / 2));
+  } else {
+    for (int i = threadIdx.x; i < C::TWC; i += C::NT) {
+      const int q1 = i / C::QC, n2 = i % C::QC;
+      twc[i] = tw_global[(n2 * q1) & (N - 1)];
+    }
   }
 }
 
@@ -150,12 +158,14 @@ __device__ __forceinline__ void row_stage(float2* G, const float2* twr, const fl
 
 // Row stage of column class W known at compile time: the same transform as
 // row_stage, with the fold factor of input n1, w_N^{QR n1 W} =
-// exp(+2 pi i n1 W / (N / QR)), applied as a constant rotation (none for
-// class 0, whose per-lane fold twiddle is 1 as well).
+// exp(+2 pi i n1 W / (N / QR)), taken as a constant twist of the pass-A DFT (none
+// for class 0, whose per-lane fold twiddle is 1 as well).
 template <int N, int V, int W>
 __device__ __forceinline__ void row_stage_w(float2* G, const float2* twr) {
   using C = FT<N, V>;
   constexpr bool kFold = C::SX > 1 && W != 0;
+  static_assert(!kFold || 32 % (N / C::QR) == 0, "the fold factors must be 32nd roots");
+  constexpr int kTwist = kFold ? W * (32 * C::QR / N) % 32 : 0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / C::RPW;
   const float2* twrl = twr + sub;   // twrl[q1 QR + LPR ja] = twr[q1 QR + n2]
@@ -167,14 +177,11 @@ __device__ __forceinline__ void row_stage_w(float2* G, const float2* twr) {
     float2 x[C::JAR][C::PR];
 #pragma unroll
     for (int ja = 0; ja < C::JAR; ++ja)
-      static_for<0, C::PRNZ>([&](auto nc) {
-        constexpr int n1 = decltype(nc)::value;
-        x[ja][n1] = R[sub + C::LPR * ja + C::QR * n1];
-        if constexpr (kFold) x[ja][n1] = rot<N / C::QR, n1 * W>(x[ja][n1]);
-      });
+#pragma unroll
+      for (int n1 = 0; n1 < C::PRNZ; ++n1) x[ja][n1] = R[sub + C::LPR * ja + C::QR * n1];
 #pragma unroll
     for (int ja = 0; ja < C::JAR; ++ja) {
-      dft_pruned<C::PR, C::PRNZ>(x[ja]);
+      dft_pruned<C::PR, C::PRNZ, kTwist>(x[ja]);
 #pragma unroll
       for (int q1 = (kFold ? 0 : 1); q1 < C::PR; ++q1) x[ja][q1] = c_mul(x[ja][q1], twrl[q1 * C::QR + C::LPR * ja]);
     }
@@ -203,15 +210,20 @@ __device__ __forceinline__ void row_stage_w(float2* G, const float2* twr) {
 // Column stage: Y[r][m] = sum_{iy < L} Z[iy][m] w_N^{iy r} for r < N, in place,
 // handing every output to sink(acc_index, r, m, value) with acc_index in [0, NACC).
 // Pass A (job n2): the pruned radix-PC DFT over rows QC n1 + n2, split by the
-// parity s of its output q1 = 2 j + s into two half-rounds whose PH outputs are
-// stored at rows j QC + n2; pass B (job j): radix-QC DFT over n2, output row
-// r = q1 + PC q2.
+// parity s of its output q1 = 2 j + s into two half-rounds (the odd one's DFT
+// twisted by a PC-th root) whose PH outputs are stored at rows j QC + n2; pass B
+// (job j): radix-QC DFT over n2, output row r = q1 + PC q2.  The twiddles between
+// the passes multiply pass A's outputs or twist pass B's DFT (TWIST).  At N = 256,
+// where the vector units are busy 81 % of the time, the twists and the fused
+// butterflies take 23.2 ms to 21.4 at 1024 channels x 256 samples of the HERA
+// shape (variant 0: 28.7 to 26.9), and the calibration shape's 3.51 to 3.21.
 template <int N, int V, class Sink>
 __device__ __forceinline__ void col_stage(float2* G, const float2* twc, Sink&& sink) {
   using C = FT<N, V>;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int sub = lane / C::CPW;
   const float2* twl = twc + sub;   // twl[q1 QC + LPC ja] = twc[q1 QC + n2]
+  const float2* twf = twc + sub * C::QC;   // TWIST: twf[(2 LPC jb + s) QC/2 + i] = twc[q1 QC/2 + i]
 #pragma unroll
   for (int cs = 0; cs < C::CSTEPS; ++cs) {
     const int col = (cs * C::NW + wave) * C::CPW + lane % C::CPW;
@@ -228,37 +240,50 @@ __device__ __forceinline__ void col_stage(float2* G, const float2* twc, Sink&& s
 #pragma unroll
       for (int ja = 0; ja < C::JA; ++ja) {
         float2 u[C::PH];
-        static_for<0, C::PH>([&](auto nc) {
-          constexpr int n1 = decltype(nc)::value;
-          if constexpr (s == 0) u[n1] = z[ja][n1];
-          else u[n1] = rot<C::PC, n1>(z[ja][n1]);
-        });
-        Dft<C::PH>::run(u);
+#pragma unroll
+        for (int n1 = 0; n1 < C::PH; ++n1) u[n1] = z[ja][n1];
+        Dft<C::PH, s * (32 / C::PC)>::run(u);
 #pragma unroll
         for (int j = 0; j < C::PH; ++j) {
           const int q1 = 2 * j + s;
-          if (q1 != 0) u[j] = c_mul(u[j], twl[q1 * C::QC + C::LPC * ja]);
+          if (!C::TWIST && q1 != 0) u[j] = c_mul(u[j], twl[q1 * C::QC + C::LPC * ja]);
           Zc[(C::LPC * ja + j * C::QC) * C::P] = u[j];
         }
       }
       wave_sync();
       float2 v[C::JB][C::QC];
       const float2* Zb = G + col + sub * C::QC * C::P;   // row (sub QC) of this column
-#pragma unroll
-      for (int jb = 0; jb < C::JB; ++jb)
+      auto load = [&](int jb) {
 #pragma unroll
         for (int k = 0; k < C::QC; ++k) v[jb][k] = Zb[(C::LPC * jb * C::QC + k) * C::P];
-      wave_sync();
+      };
+      if constexpr (!C::TWIST) {
+#pragma unroll
+        for (int jb = 0; jb < C::JB; ++jb) load(jb);
+        wave_sync();
+      }
 #pragma unroll
       for (int jb = 0; jb < C::JB; ++jb) {
         const int j = sub + C::LPC * jb;
-        Dft<C::QC>::run(v[jb]);
+        if constexpr (C::TWIST) {
+          // (one job's inputs and factors in registers at a time: with the next
+          // ones requested early, the 256 of a wave of two per SIMD ran out)
+          __builtin_amdgcn_sched_barrier(0);
+          load(jb);
+          float2 f[C::QC / 2];
+#pragma unroll
+          for (int i = 0; i < C::QC / 2; ++i) f[i] = twf[(2 * C::LPC * jb + s) * (C::QC / 2) + i];
+          TwistedDft<C::QC>::run(v[jb], f);
+        } else {
+          Dft<C::QC>::run(v[jb]);
+        }
 #pragma unroll
         for (int q2 = 0; q2 < C::QC; ++q2) {
           const int r = 2 * j + s + C::PC * q2;
           sink(((cs * 2 + s) * C::JB + jb) * C::QC + q2, r, col, v[jb][q2]);
         }
       }
+      if constexpr (C::TWIST) wave_sync();
     });
   }
 }
@@ -398,12 +423,9 @@ __device__ __forceinline__ void col_stage_roundtrip(float2* G, const float2* twc
 #pragma unroll
       for (int ja = 0; ja < C::JA; ++ja) {
         float2 u[C::PH];
-        static_for<0, C::PH>([&](auto nc) {
-          constexpr int n1 = decltype(nc)::value;
-          if constexpr (s == 0) u[n1] = z[ja][n1];
-          else u[n1] = rot<C::PC, n1>(z[ja][n1]);
-        });
-        Dft<C::PH>::run(u);
+#pragma unroll
+        for (int n1 = 0; n1 < C::PH; ++n1) u[n1] = z[ja][n1];
+        Dft<C::PH, s * (32 / C::PC)>::run(u);
 #pragma unroll
         for (int j = 0; j < C::PH; ++j) {
           const int q1 = 2 * j + s;

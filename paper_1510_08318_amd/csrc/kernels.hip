@@ -155,10 +155,11 @@ constexpr int kGatherSub = 4;
 
 // Waves per SIMD the fused kernel's registers are sized for: at N = 128,
 // shape variant 0 fits four (128 registers), which several workgroups per CU
-// need to hide one another's gather latency.
+// need to hide one another's gather latency; at N = 256 it fits two (left to
+// itself the compiler took 264 registers for some forms, and half the rate).
 template <int N, int V>
 constexpr int fused_waves_per_simd() {
-  return (N == 128 && V == 0) ? 4 : 1;
+  return V != 0 ? 1 : N == 128 ? 4 : N == 256 ? 2 : 1;
 }
 
 // Whether workgroups of a shape can share a CU (its LDS leaves room for a
@@ -170,8 +171,8 @@ constexpr bool shares_cu(int N, int V) { return !(N == 256 && V == 1); }
 // slice of time samples.  ONE: every lane ingests at most one antenna
 // (n_ant <= NT), so a lane's self power is one float64 sum, given its type
 // after the frame loop, instead of one running sum per antenna type (8 fewer
-// registers held through the loop: at the HERA shape 1 spilled register
-// instead of 24).  The sums are the same either way.
+// registers held through the loop: at the HERA shape no spilled register
+// instead of 5).  The sums are the same either way.
 template <int N, int V, bool CI4, int W, bool ONE>
 __device__ __forceinline__ void fused_item(const FusedArgs& a, float2* lds, double* Atot, int c, int slice,
                                            int item) {
@@ -193,7 +194,7 @@ __device__ __forceinline__ void fused_item(const FusedArgs& a, float2* lds, doub
   const size_t frame_stride = static_cast<size_t>(a.n_chan) * a.n_ant;
   const size_t img_stride = static_cast<size_t>(N) * N;
 
-  build_twiddles<N, V>(a.tw, W, twr, twc);
+  build_twiddles<N, V, true>(a.tw, W, twr, twc);
   for (int i = tid; i < a.n_weights; i += NT) Wt[i] = a.weights[static_cast<size_t>(W) * a.n_weights + i];
   for (int i = tid; i < a.n_ant; i += NT)
     gl[i] = a.gains ? a.gains[static_cast<size_t>(c) * a.n_ant + i] : make_float2(1.f, 0.f);
@@ -401,7 +402,7 @@ __device__ __forceinline__ void adjoint_item(const AdjFusedArgs& a, float2* lds,
   float2* gl = Wt + a.n_weights;            // [n_ant] gains of the current channel
   float2* e = gl + a.n_ant;                 // [n_ant + 1], last slot stays zero
 
-  build_twiddles<N, V>(a.tw, W, twr, twc);
+  build_twiddles<N, V, false>(a.tw, W, twr, twc);
   for (int i = tid; i < a.n_weights; i += NT) Wt[i] = a.weights[static_cast<size_t>(W) * a.n_weights + i];
   for (int i = tid; i < a.n_ant; i += NT)
     gl[i] = a.gains ? a.gains[static_cast<size_t>(c) * a.n_ant + i] : make_float2(1.f, 0.f);
@@ -826,7 +827,7 @@ __global__ __launch_bounds__((FT<N, 0>::NT)) void fft2_kernel(Fft2Args a) {
   float2* twc = twr + C::TWR;
   const int w = blockIdx.x % C::SX;
   const int64_t f = blockIdx.x / C::SX;
-  build_twiddles<N, 0>(a.tw, w, twr, twc);
+  build_twiddles<N, 0, true>(a.tw, w, twr, twc);
   float2 fin[C::PRNZ];
   fold_factors<N, 0>(a.tw, w, fin);
   const float2* src = a.Eg + static_cast<size_t>(f) * C::L * C::L;
@@ -906,7 +907,7 @@ __global__ __launch_bounds__((FT<N, 0>::NT)) void adjoint_fft2_kernel(AdjFftArgs
   const int w = blockIdx.x % C::SX;
   const int64_t f = blockIdx.x / C::SX;
   const int c = static_cast<int>(f % a.n_chan);
-  build_twiddles<N, 0>(a.tw, w, twr, twc);
+  build_twiddles<N, 0, false>(a.tw, w, twr, twc);
   float2 fin[C::PRNZ];
   fold_factors<N, 0>(a.tw, w, fin);
   __syncthreads();
