@@ -617,12 +617,10 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
       if (hipEventRecord(p->ev1, st) != hipSuccess) return MOFF_ERR_HIP;
       p->timed = true;
     }
-    if (moff::launch_adjoint_reduce(Dp, parts, hp.n_chan, hp.n_ant, D, st) != hipSuccess) return MOFF_ERR_HIP;
-    if (moff::launch_antenna_power(E, ci4, n_time, hp.n_chan, hp.n_ant, Q, st) != hipSuccess) return MOFF_ERR_HIP;
     gf.D = D;
     gf.Q = Q;
     gf.rho = Q + na;
-    return hip_status(moff::launch_grad_final(gf, st));
+    return hip_status(moff::launch_grad_final(gf, E, ci4, n_time, Dp, parts, st));
   }
 
   // staged: per time chunk, grids, fields and adjoint grids through HBM
@@ -683,7 +681,7 @@ moff_status gain_vjp(moff_plan p, const void* E, int64_t n_time, const float* ga
   gf.D = D;
   gf.Q = Q;
   gf.rho = reinterpret_cast<double*>(ws + d_bytes + q_bytes + eg_bytes + y_bytes + gp_bytes);
-  return hip_status(moff::launch_grad_final(gf, st));
+  return hip_status(moff::launch_grad_final(gf, nullptr, ci4, 0, nullptr, 0, st));
 }
 
 // Host plan, then the device tables.  On an error the caller frees whatever

@@ -130,8 +130,8 @@ struct DegridArgs {
 constexpr int kRhoParts = 16;   // workgroups per channel that sum rho_p = <R, P_p>
 
 struct GradFinalArgs {
-  const double2* D;
-  const double* Q;
+  double2* D;
+  double* Q;
   const float* R;              // [C][N][N]
   const double* Pp;            // [types][N][N]
   const float2* gains;         // [C][n_ant] or nullptr
@@ -248,14 +248,20 @@ int adjoint_fused_blocks_per_cu(int N, int V, bool ci4, int wps, size_t lds);
 size_t fused_lane_values(int N, int V);
 // Rl [C][fused_lane_values(N, V)] for shape variant V from R [C][N][N].
 hipError_t launch_adjoint_sensitivity(const float* R, int N, int V, int n_chan, float* Rl, hipStream_t st);
-// Q[c][a] = sum_t |E[t][c][a]|^2 (float64); D[c][a] = sum_k Dp[k][c][a] over `parts` partials.
-hipError_t launch_antenna_power(const void* E, bool ci4, int64_t n_time, int n_chan, int n_ant, double* Q,
-                                hipStream_t st);
-hipError_t launch_adjoint_reduce(const double2* Dp, int parts, int n_chan, int n_ant, double2* D, hipStream_t st);
-
 hipError_t launch_adjoint_fft2(const AdjFftArgs& a, int N, int64_t n_frames, hipStream_t st);
 hipError_t launch_degrid(const DegridArgs& a, bool ci4, hipStream_t st);
-hipError_t launch_grad_final(const GradFinalArgs& a, hipStream_t st);
+// grad from the sums D and Q and rho, which this computes first.  With partials
+// Dp [parts][C][n_ant] also D[c][a] = sum_k Dp[k][c][a] and, where it is subtracted,
+// Q[c][a] = sum_t |E[t][c][a]|^2; with Dp null both are given.
+struct GradTermsArgs {
+  const void* E;
+  int64_t n_time;
+  const double2* Dp;
+  int parts;
+  int q_blocks, rho_blocks, d_blocks;   // workgroups per channel
+};
+hipError_t launch_grad_final(const GradFinalArgs& a, const void* E, bool ci4, int64_t n_time, const double2* Dp,
+                             int parts, hipStream_t st);
 
 // Fused kernel of grid size N, shape variant V (shape.h), one work item
 // (column class, channel, time slice) per workgroup of a `grid`-sized launch.

@@ -551,80 +551,6 @@ __global__ __launch_bounds__(256) void adjoint_sensitivity_kernel(const float* R
   Rl[i] = v;
 }
 
-// Q = sum_t |E|^2 per (channel, antenna) in float64: 64 antennas per workgroup
-// and kPowerGroups contiguous ranges of time, one per wave, summed in order.
-// Bound by the samples' bytes; a single range per antenna left too few loads in
-// flight (12 channels x 61 antennas x 75 complex64 samples: 10.1 -> 4.6 us).
-constexpr int kPowerGroups = 8;
-
-template <bool CI4>
-__global__ __launch_bounds__(64 * kPowerGroups) void antenna_power_kernel(const void* E, int64_t n_time, int n_chan,
-                                                                          int n_ant, double* Q) {
-  __shared__ double part[kPowerGroups][64];
-  const int c = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const int ant = blockIdx.x * 64 + lane;
-  double q = 0.0;
-  if (ant < n_ant) {
-    const int64_t t0 = g * n_time / kPowerGroups, t1 = (g + 1) * n_time / kPowerGroups;
-    const size_t stride = static_cast<size_t>(n_chan) * n_ant;
-    size_t at = static_cast<size_t>(t0) * stride + static_cast<size_t>(c) * n_ant + ant;
-    auto add = [&](float2 v) { q += static_cast<double>(v.x) * v.x + static_cast<double>(v.y) * v.y; };
-    int64_t t = t0;
-    for (; t + 8 <= t1; t += 8, at += 8 * stride) {
-      float2 v[8];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = load_sample(E, at + k * stride, CI4);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) add(v[k]);
-    }
-    for (; t < t1; ++t, at += stride) add(load_sample(E, at, CI4));
-  }
-  part[g][lane] = q;
-  __syncthreads();
-  if (g == 0 && ant < n_ant) {
-    double s = part[0][lane];
-#pragma unroll
-    for (int k = 1; k < kPowerGroups; ++k) s += part[k][lane];
-    Q[static_cast<size_t>(c) * n_ant + ant] = s;
-  }
-}
-
-// D = sum of the per-(slice, class) partial sums: 64 (channel, antenna) values
-// per workgroup, four contiguous ranges of partials each, in order.
-__global__ __launch_bounds__(256) void adjoint_reduce_kernel(const double2* Dp, int parts, size_t n, double2* D) {
-  __shared__ double2 part[4][64];
-  const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
-  const size_t i = static_cast<size_t>(blockIdx.x) * 64 + lane;
-  double x = 0.0, y = 0.0;
-  if (i < n) {
-    const int k1 = (g + 1) * parts / 4;
-    int k = g * parts / 4;
-    for (; k + 4 <= k1; k += 4) {
-      double2 v[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) v[j] = Dp[static_cast<size_t>(k + j) * n + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        x += v[j].x;
-        y += v[j].y;
-      }
-    }
-    for (; k < k1; ++k) {
-      x += Dp[static_cast<size_t>(k) * n + i].x;
-      y += Dp[static_cast<size_t>(k) * n + i].y;
-    }
-  }
-  part[g][lane] = make_double2(x, y);
-  __syncthreads();
-  if (g == 0 && i < n) {
-    for (int j = 1; j < 4; ++j) {
-      x += part[j][lane].x;
-      y += part[j][lane].y;
-    }
-    D[i] = make_double2(x, y);
-  }
-}
-
 // Sum per-slice partials (pixel order) in a fixed order, four pixels per
 // thread (N^2 is a multiple of 4); then remove self power and average
 // (MODE_FINAL) or add into the caller's running sums (MODE_ACCUM).
@@ -971,26 +897,91 @@ __global__ __launch_bounds__(256) void degrid_kernel(DegridArgs a) {
   a.Q[i] += Q;
 }
 
-// rho_p = sum_pix R P_p of one channel: kRhoParts workgroups per channel, one
-// contiguous range of pixels each, summed by grad_final_kernel in order.
-__global__ __launch_bounds__(256) void grad_rho_kernel(GradFinalArgs a) {
+// The three sums of the gain gradient that wait for nothing but the frames, one
+// launch: grid (q_blocks + rho_blocks + d_blocks, n_chan), each workgroup one of
+//   Q = sum_t |E|^2 of 64 antennas in float64, a contiguous range of time per wave;
+//   rho_p = sum_pix R P_p over one of kRhoParts contiguous ranges of pixels;
+//   D = sum of the per-(slice, class) partial sums of 64 antennas, a contiguous
+//       range of partials per wave;
+// waves' sums are added in order.  Bound by the bytes they read, or on a small
+// array by latency: a single range per antenna left too few loads in flight (12
+// channels x 61 antennas x 75 complex64 samples: Q 10.1 us, D 17.1 of a kernel of
+// their own each, 4.6 and 4.7 split in ranges), and there a launch more or less is
+// 5 us of the host's time.
+constexpr int kTermWaves = 8;
+
+template <bool CI4>
+__global__ __launch_bounds__(64 * kTermWaves) void grad_terms_kernel(GradTermsArgs a, GradFinalArgs f) {
+  __shared__ double2 part[kTermWaves][64];
   __shared__ double rho[kMaxTypesDev];
-  const int c = blockIdx.y;
-  const size_t npix = static_cast<size_t>(a.N) * a.N;
-  const size_t i0 = blockIdx.x * npix / kRhoParts, i1 = (blockIdx.x + 1) * npix / kRhoParts;
-  const float* R = a.R + static_cast<size_t>(c) * npix;
-  double part[kMaxTypesDev] = {0.0, 0.0, 0.0, 0.0};
+  const int c = blockIdx.y, lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+  int b = blockIdx.x;
+  double x = 0.0, y = 0.0;
+  if (b >= a.q_blocks && b < a.q_blocks + a.rho_blocks) {   // uniform
+    b -= a.q_blocks;
+    const size_t npix = static_cast<size_t>(f.N) * f.N;
+    const size_t i0 = b * npix / kRhoParts, i1 = (b + 1) * npix / kRhoParts;
+    const float* R = f.R + static_cast<size_t>(c) * npix;
+    double sums[kMaxTypesDev] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-  for (int p = 0; p < kMaxTypesDev; ++p) {
-    if (p >= a.n_types) break;   // uniform
-    double s = 0.0;
+    for (int p = 0; p < kMaxTypesDev; ++p) {
+      if (p >= f.n_types) break;   // uniform
+      double s = 0.0;
 #pragma unroll 4
-    for (size_t i = i0 + threadIdx.x; i < i1; i += 256) s += static_cast<double>(R[i]) * a.Pp[p * npix + i];
-    part[p] = s;
+      for (size_t i = i0 + threadIdx.x; i < i1; i += 64 * kTermWaves) s += static_cast<double>(R[i]) * f.Pp[p * npix + i];
+      sums[p] = s;
+    }
+    block_sum4<64 * kTermWaves>(sums, rho);
+    if (threadIdx.x < kMaxTypesDev)
+      f.rho[(static_cast<size_t>(c) * kRhoParts + b) * kMaxTypesDev + threadIdx.x] = rho[threadIdx.x];
+    return;
   }
-  block_sum4<256>(part, rho);
-  if (threadIdx.x < kMaxTypesDev)
-    a.rho[(static_cast<size_t>(c) * kRhoParts + blockIdx.x) * kMaxTypesDev + threadIdx.x] = rho[threadIdx.x];
+  const bool power = b < a.q_blocks;   // uniform
+  const int ant = (power ? b : b - a.q_blocks - a.rho_blocks) * 64 + lane;
+  const size_t ca = static_cast<size_t>(c) * f.n_ant + ant, stride = static_cast<size_t>(f.n_chan) * f.n_ant;
+  if (power && ant < f.n_ant) {
+    int64_t t = g * a.n_time / kTermWaves;
+    const int64_t t1 = (g + 1) * a.n_time / kTermWaves;
+    size_t at = static_cast<size_t>(t) * stride + ca;
+    auto add = [&](float2 v) { x += static_cast<double>(v.x) * v.x + static_cast<double>(v.y) * v.y; };
+    for (; t + 8 <= t1; t += 8, at += 8 * stride) {
+      float2 v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = load_sample(a.E, at + k * stride, CI4);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) add(v[k]);
+    }
+    for (; t < t1; ++t, at += stride) add(load_sample(a.E, at, CI4));
+  } else if (ant < f.n_ant) {
+    const int k1 = (g + 1) * a.parts / kTermWaves;
+    int k = g * a.parts / kTermWaves;
+    for (; k + 4 <= k1; k += 4) {
+      double2 v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = a.Dp[static_cast<size_t>(k + j) * stride + ca];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        x += v[j].x;
+        y += v[j].y;
+      }
+    }
+    for (; k < k1; ++k) {
+      const double2 v = a.Dp[static_cast<size_t>(k) * stride + ca];
+      x += v.x;
+      y += v.y;
+    }
+  }
+  part[g][lane] = make_double2(x, y);
+  __syncthreads();
+  if (g == 0 && ant < f.n_ant) {
+#pragma unroll
+    for (int j = 1; j < kTermWaves; ++j) {
+      x += part[j][lane].x;
+      y += part[j][lane].y;
+    }
+    if (power) f.Q[ca] = x;
+    else f.D[ca] = make_double2(x, y);
+  }
 }
 
 // grad = scale (D - rho_{p(a)} g Q), one thread per (channel, antenna).  (With
@@ -1217,21 +1208,6 @@ int adjoint_fused_blocks_per_cu(int N, int V, bool ci4, int wps, size_t lds) {
   return n;
 }
 
-hipError_t launch_antenna_power(const void* E, bool ci4, int64_t n_time, int n_chan, int n_ant, double* Q,
-                                hipStream_t st) {
-  const dim3 grid((n_ant + 63) / 64, n_chan), block(64 * kPowerGroups);
-  if (ci4) hipLaunchKernelGGL(antenna_power_kernel<true>, grid, block, 0, st, E, n_time, n_chan, n_ant, Q);
-  else hipLaunchKernelGGL(antenna_power_kernel<false>, grid, block, 0, st, E, n_time, n_chan, n_ant, Q);
-  return hipGetLastError();
-}
-
-hipError_t launch_adjoint_reduce(const double2* Dp, int parts, int n_chan, int n_ant, double2* D, hipStream_t st) {
-  const size_t n = static_cast<size_t>(n_chan) * n_ant;
-  hipLaunchKernelGGL(adjoint_reduce_kernel, dim3(static_cast<unsigned>((n + 63) / 64)), dim3(256), 0, st, Dp, parts,
-                     n, D);
-  return hipGetLastError();
-}
-
 int fused_blocks_per_cu(int N, int V, bool ci4, size_t lds) {
   // (both antenna variants are sized for the same waves per SIMD)
   const void* k = fused_kernel_symbol(N, V, ci4, false);
@@ -1335,9 +1311,21 @@ hipError_t launch_degrid(const DegridArgs& a, bool ci4, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_grad_final(const GradFinalArgs& a, hipStream_t st) {
-  if (a.subtract) {
-    hipLaunchKernelGGL(grad_rho_kernel, dim3(kRhoParts, a.n_chan), dim3(256), 0, st, a);
+hipError_t launch_grad_final(const GradFinalArgs& a, const void* E, bool ci4, int64_t n_time, const double2* Dp,
+                             int parts, hipStream_t st) {
+  const int ant_blocks = (a.n_ant + 63) / 64;
+  GradTermsArgs t{};
+  t.E = E;
+  t.n_time = n_time;
+  t.Dp = Dp;
+  t.parts = parts;
+  t.q_blocks = Dp && a.subtract ? ant_blocks : 0;
+  t.rho_blocks = a.subtract ? kRhoParts : 0;
+  t.d_blocks = Dp ? ant_blocks : 0;
+  const dim3 grid(t.q_blocks + t.rho_blocks + t.d_blocks, a.n_chan), block(64 * kTermWaves);
+  if (grid.x > 0) {
+    if (ci4) hipLaunchKernelGGL(grad_terms_kernel<true>, grid, block, 0, st, t, a);
+    else hipLaunchKernelGGL(grad_terms_kernel<false>, grid, block, 0, st, t, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
