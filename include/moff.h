@@ -239,7 +239,9 @@ moff_status moff_plan_mfma_tables(moff_plan plan, uint32_t* prog, uint16_t* dft,
 /*
  * Launch configuration of the fused path.  The frame transform has one or two
  * shape variants per grid size (how output columns are split across
- * workgroups, threads per workgroup); a launch also chooses the number of time
+ * workgroups, threads per workgroup) and, in float32 at grid_n 64 and 128, one
+ * more on the matrix cores, the last and the default there where its tables fit
+ * (at grid_n 256 the default is variant 1); a launch also chooses the number of time
  * slices: each (column class, channel, slice) is one workgroup, and per-slice
  * partial sums are reduced afterwards in a fixed order.
  *
@@ -256,7 +258,7 @@ moff_status moff_plan_mfma_tables(moff_plan plan, uint32_t* prog, uint16_t* dft,
  * budget it is built with (see moff_plan_set_adjoint_waves), on the same
  * samples and gains with the tuned image as the pixel sensitivities, and
  * keeps the fastest.  moff_plan_set_config forces a choice (slices = 0:
- * heuristic) and gives the adjoint the same shape variant; moff_plan_get_config
+ * heuristic) and gives the adjoint the same shape variant where it has it; moff_plan_get_config
  * reports the configuration a call with n_time samples would use.  Any output
  * of get_config may be NULL.
  */
@@ -429,16 +431,20 @@ moff_status moff_image_staged(moff_plan plan, const void* E_dev, int64_t n_time,
  * moff_image's default image to rounding.  MOFF_AUTOCORR_UV and the
  * MOFF_MFMA_* flags do not apply here.  Arithmetic: 4+4-bit cross-products
  * are summed exactly in int32; complex64 cross-products are summed in float32
- * over chunks of 32 samples on the matrix cores and in float64 across chunks;
- * each pair's lag response is summed in float32, and binning, pair
- * combination and the transform's sums are float64.
+ * over steps of 32 samples on the matrix cores (each sample as three bfloat16
+ * numbers, all 24 bits of it) and in float64 across steps; binning and the
+ * combination of pairs are float64, each pair's lag response and the transform
+ * float32.
  * MOFF_NORM_PAIRS scales as for moff_image.
  * Cost: O(n_chan (n_time n_ant^2 + n_ant^2 + N^2 log N)) work.  Channels run in
- * chunks whose workspace, 8 (n_ant^2 + (n_types^2 + 1) (2L - 1)^2 + (2L - 1) N)
- * bytes per channel, stays within about 2 GiB (at least one channel); it is
- * owned by the plan and shared with the plan's other entry points.  The pair
- * tables (about 2 n_ant^2 bytes: each unordered pair once) are built and
- * uploaded on the first call.
+ * chunks whose workspace stays within about 2 GiB (at least one channel): per
+ * channel 8 n_ant^2 + 8 L N bytes, 8 L (2L - 1) with one table type or
+ * 8 (n_types^2 + 1) (2L - 1)^2 with several, and the staged samples, 2 bytes each
+ * (4+4-bit) or 12 (complex64).  Where the samples leave no room for eight channels
+ * they are taken in passes over time, with 16 n_ant^2 bytes for the sums between
+ * them.  The workspace is owned by the plan and shared with the plan's other entry
+ * points.  The pair tables (about 3 n_ant^2 bytes: each unordered pair once) are
+ * built and uploaded on the first call.
  * Errors: MOFF_ERR_INVALID_ARG for null or misaligned pointers or n_time < 1;
  * MOFF_ERR_UNSUPPORTED for a plan without a device, or 4+4-bit samples with
  * n_time > 2^24 (their cross-products are exact int32 sums on the matrix

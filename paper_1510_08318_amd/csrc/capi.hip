@@ -73,6 +73,7 @@ struct moff_plan_s {
   KernelFootprint footprints[moff::kMaxVariants + 1] = {};   // of every variant (queried at creation)
   int adj_blocks[moff::kMaxVariants][4] = {};   // fused adjoint: workgroups per CU by variant and waves per SIMD (0: unfit)
   int variant = 0;          // index into hp.variants
+  int short_variant = -1;   // untuned calls of few samples: their variant (-1: the same)
   int slices = 0;           // time slices; 0 = heuristic
   bool tuned = false;
   int adj_waves = 1;        // fused adjoint: waves per SIMD its registers are sized for
@@ -307,7 +308,10 @@ int default_slices(const HostPlan& hp, const KernelFootprint& f, bool matrix, in
 LaunchConfig launch_config(moff_plan p, int64_t n_time) {
   const HostPlan& hp = p->hp;
   LaunchConfig lc{};
-  lc.variant = std::min<int>(p->variant, n_variants(hp) - 1);
+  // (a call of fewer than eight samples of few antennas at N = 256 is mostly what a
+  // workgroup does once, less with 256 threads than with 512: 30.0 against 31.2 us at
+  // 3 channels x 6 samples of 68 antennas, 36.9 against 38.6 at 20 x 3 of 100)
+  lc.variant = std::min<int>(p->short_variant >= 0 && n_time < 8 ? p->short_variant : p->variant, n_variants(hp) - 1);
   int slices = p->slices;
   if (slices <= 0)
     slices = default_slices(hp, footprint(p, lc.variant), is_mfma(hp) || is_split(hp, lc.variant), n_time);
@@ -762,8 +766,15 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
     // threads beat the four of 256 (image 23.3 against 28.7 ms at 1024 channels x
     // 256 samples of 350 antennas, 60 against 69 us at 4 x 23 of 578), and so
     // they do for the gradient (7.4 against 16.7 ms at 256 x 128 of 1024).
+    // Not for an image of few antennas with complex tables, whose weights are looked
+    // up in LDS (0.95-0.99 of the first shape's speed at 6 x 30 and 64 x 9, 40-250
+    // antennas; 1.10 and more where the tables are real or the antennas 600).
     if (hp.N == 256 && hp.variants.size() > 1 && !is_mfma(hp)) {
-      if (p->footprints[1].lds <= size_t(159) * 1024) p->variant = 1;
+      const bool few = hp.n_ant <= hp.variants[0].shape.NT;
+      if (p->footprints[1].lds <= size_t(159) * 1024 && !(few && !p->d_progw[1])) {
+        p->variant = 1;
+        p->short_variant = few ? 0 : 1;
+      }
       if (p->adj_blocks[1][p->adj_waves] > 0) p->adj_variant = 1;
     }
   }
@@ -914,6 +925,7 @@ moff_status moff_plan_mfma_tables(moff_plan p, uint32_t* prog, uint16_t* dft, in
 moff_status moff_plan_set_config(moff_plan p, int32_t variant, int32_t slices) {
   if (!p || variant < 0 || variant >= n_variants(p->hp) || slices < 0 || slices > 256) return MOFF_ERR_INVALID_ARG;
   p->variant = variant;
+  p->short_variant = -1;
   p->adj_variant = variant;
   p->slices = slices;
   p->tuned = false;
@@ -952,7 +964,8 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
     (void)hipFree(img);
     return MOFF_ERR_HIP;
   }
-  const int saved_v = p->variant, saved_s = p->slices;
+  const int saved_v = p->variant, saved_s = p->slices, saved_short = p->short_variant;
+  p->short_variant = -1;
   const bool saved_timing = p->timing;
   p->timing = false;
   float best = 1e30f;
@@ -1085,6 +1098,7 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
   p->timing = saved_timing;
   if (result != MOFF_OK) {
     p->variant = saved_v;
+    p->short_variant = saved_short;
     p->slices = saved_s;
     p->adj_waves = 1;
     p->adj_variant = saved_v;

@@ -654,30 +654,35 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
 // ---------------------------------------------------------------------------
 
 // Calibrate a frame into LDS, then every aperture cell sums its CSR row
-// (antenna-ascending) and writes Eg.  One workgroup per 256 x kGridCells cells
-// of a frame: each thread walks its cells' rows side by side, so that the loads
-// of all of them are in flight at once (a cell at a time, one workgroup per
-// frame, was a chain of loads per cell: 23 us became 18 at 768 frames of 256
-// antennas, N = 128, whose grids take 25 MB).
-constexpr int kGridCells = 8;
+// (antenna-ascending) and writes Eg.  One workgroup per 256 x 8 cells of a frame:
+// each thread walks eight cells' rows side by side, so that the loads of all of
+// them are in flight at once (a cell at a time, one workgroup per frame, was a
+// chain of loads per cell: 23 us became 18 at 768 frames of 256 antennas, N = 128,
+// whose grids take 25 MB; 54 became 26 at 520 frames, N = 256).  A grid of fewer
+// cells keeps one workgroup per frame that takes them one at a time: eight left
+// seven eighths of it idle at N = 32 and half at N = 64 (39 us against 21 and 26
+// at 6760 frames), four at N = 64 took 29.
+constexpr int grid_cells(int L) { return L * L >= 256 * 8 ? 8 : 1; }
 
-template <bool CI4>
+template <bool CI4, int CELLS>
 __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
   extern __shared__ float2 lds[];
   float2* e = lds;               // [n_ant]
   float2* K = e + a.n_ant;       // [n_taps]
-  const int ncell = a.L * a.L, parts = (ncell + 256 * kGridCells - 1) / (256 * kGridCells);
+  const int ncell = a.L * a.L, parts = CELLS == 1 ? 1 : (ncell + 256 * CELLS - 1) / (256 * CELLS);
   const int64_t f = blockIdx.x / parts;  // frame = t * n_chan + c
   const int c = static_cast<int>(f % a.n_chan);
-  const int cell0 = static_cast<int>(blockIdx.x % parts) * 256 * kGridCells + threadIdx.x;
-  int k0[kGridCells], k1[kGridCells];
+  const int cell0 = static_cast<int>(blockIdx.x % parts) * 256 * CELLS + threadIdx.x;
+  int k0[CELLS], k1[CELLS];
+  if constexpr (CELLS > 1) {   // (requested before the samples)
 #pragma unroll
-  for (int i = 0; i < kGridCells; ++i) {
-    const int cell = cell0 + 256 * i;
-    k0[i] = k1[i] = 0;
-    if (cell < ncell) {
-      k0[i] = a.csr_ptr[cell];
-      k1[i] = a.csr_ptr[cell + 1];
+    for (int i = 0; i < CELLS; ++i) {
+      const int cell = cell0 + 256 * i;
+      k0[i] = k1[i] = 0;
+      if (cell < ncell) {
+        k0[i] = a.csr_ptr[cell];
+        k1[i] = a.csr_ptr[cell + 1];
+      }
     }
   }
   const size_t base = static_cast<size_t>(f) * a.n_ant;
@@ -687,32 +692,43 @@ __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
   }
   for (int i = threadIdx.x; i < a.n_taps; i += 256) K[i] = a.ktab[i];
   __syncthreads();
-  float2 s[kGridCells];
-#pragma unroll
-  for (int i = 0; i < kGridCells; ++i) s[i] = make_float2(0.f, 0.f);
-  for (bool more = true; more;) {
-    more = false;
-    int ant[kGridCells], tap[kGridCells];
-#pragma unroll
-    for (int i = 0; i < kGridCells; ++i)
-      if (k0[i] < k1[i]) {
-        ant[i] = a.csr_ant[k0[i]];
-        tap[i] = a.csr_tap[k0[i]];
-      }
-#pragma unroll
-    for (int i = 0; i < kGridCells; ++i)
-      if (k0[i] < k1[i]) {
-        const float2 ev = e[ant[i]], kv = K[tap[i]];
-        s[i].x = fmaf(ev.x, kv.x, fmaf(-ev.y, kv.y, s[i].x));
-        s[i].y = fmaf(ev.x, kv.y, fmaf(ev.y, kv.x, s[i].y));
-        ++k0[i];
-        more = more || k0[i] < k1[i];
-      }
-  }
   float2* out = a.Eg + static_cast<size_t>(f) * ncell;
+  auto add = [&](float2& s, int ant, int tap) {
+    const float2 ev = e[ant], kv = K[tap];
+    s.x = fmaf(ev.x, kv.x, fmaf(-ev.y, kv.y, s.x));
+    s.y = fmaf(ev.x, kv.y, fmaf(ev.y, kv.x, s.y));
+  };
+  if constexpr (CELLS == 1) {
+    for (int cell = cell0; cell < ncell; cell += 256) {
+      float2 s = make_float2(0.f, 0.f);
+      for (int k = a.csr_ptr[cell]; k < a.csr_ptr[cell + 1]; ++k) add(s, a.csr_ant[k], a.csr_tap[k]);
+      out[cell] = s;
+    }
+  } else {
+    float2 s[CELLS];
 #pragma unroll
-  for (int i = 0; i < kGridCells; ++i)
-    if (cell0 + 256 * i < ncell) out[cell0 + 256 * i] = s[i];
+    for (int i = 0; i < CELLS; ++i) s[i] = make_float2(0.f, 0.f);
+    for (bool more = true; more;) {
+      more = false;
+      int ant[CELLS], tap[CELLS];
+#pragma unroll
+      for (int i = 0; i < CELLS; ++i)
+        if (k0[i] < k1[i]) {
+          ant[i] = a.csr_ant[k0[i]];
+          tap[i] = a.csr_tap[k0[i]];
+        }
+#pragma unroll
+      for (int i = 0; i < CELLS; ++i)
+        if (k0[i] < k1[i]) {
+          add(s[i], ant[i], tap[i]);
+          ++k0[i];
+          more = more || k0[i] < k1[i];
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < CELLS; ++i)
+      if (cell0 + 256 * i < ncell) out[cell0 + 256 * i] = s[i];
+  }
 }
 
 // One workgroup per channel: A[c][p] += sum_t sum_{a of type p} |g E|^2.
@@ -737,13 +753,16 @@ __global__ __launch_bounds__(256) void self_power_kernel(GridArgs a) {
 }
 
 // One workgroup per (row class, frame): load and fold the aperture grid,
-// transform, store the complex image field in pixel order.  As in the fused
-// kernel the transform runs on the transposed aperture, so that a workgroup owns
-// whole image rows; a lane's outputs of the two half-rounds are adjacent pixels
-// and leave as one 16-byte store, four lanes to 64 bytes of a row.  (With
-// classes of columns each 8-byte store touched every other pixel of a row: 51 us
-// became 45 at 768 frames, N = 128, whose 126 MB take about 25 at the rate of a
-// copy; one and a half rounds of four workgroups per CU are the rest.)
+// transform, store the complex image field in pixel order.  With several classes
+// the transform runs on the transposed aperture, as in the fused kernel, so that a
+// workgroup owns whole image rows; a lane's outputs of the two half-rounds are
+// adjacent pixels and leave as one 16-byte store, four lanes to 64 bytes of a row.
+// (With classes of columns each 8-byte store touched every other pixel of a row: 51
+// us became 45 at 768 frames, N = 128, whose 126 MB take about 25 at the rate of a
+// copy; one and a half rounds of four workgroups per CU are the rest.  520 frames
+// at N = 256: 307 -> 221.)  A single class has whole rows either way: 16 lanes store
+// 16 adjacent pixels as they come, and no output waits in a register (6760 frames
+// transposed and held: 78 us against 48 at N = 64, 21 against 13 at N = 32).
 template <int N>
 __global__ __launch_bounds__((FT<N, 0>::NT)) void fft2_kernel(Fft2Args a) {
   using C = FT<N, 0>;
@@ -758,18 +777,29 @@ __global__ __launch_bounds__((FT<N, 0>::NT)) void fft2_kernel(Fft2Args a) {
   fold_factors<N, 0>(a.tw, w, fin);
   const float2* src = a.Eg + static_cast<size_t>(f) * C::L * C::L;
   for (int cell = threadIdx.x; cell < C::L * C::NZR; cell += C::NT) {
-    const int n = cell / C::L, ix = cell % C::L;
-    float2 v = make_float2(0.f, 0.f);
-    for (int j = 0; j * C::M + n < C::L; ++j) {
-      const float2 x = quarter_rot(src[(n + j * C::M) * C::L + ix], j * w, C::SX);
-      v = c_add(v, x);
+    if constexpr (C::SX == 1) {
+      static_assert(C::SX > 1 || C::NZR == C::L, "a single class folds nothing");
+      G[cell / C::L * C::P + cell % C::L] = src[cell];
+    } else {
+      const int n = cell / C::L, ix = cell % C::L;
+      float2 v = make_float2(0.f, 0.f);
+      for (int j = 0; j * C::M + n < C::L; ++j) {
+        const float2 x = quarter_rot(src[(n + j * C::M) * C::L + ix], j * w, C::SX);
+        v = c_add(v, x);
+      }
+      G[ix * C::P + n] = v;
     }
-    G[ix * C::P + n] = v;
   }
   __syncthreads();
   row_stage<N, 0>(G, twr, fin);
   __syncthreads();
   float2* dst = a.Y + static_cast<size_t>(f) * N * N;
+  if constexpr (C::SX == 1) {
+    col_stage<N, 0>(G, twc, [&](int, int r, int col, float2 v) {
+      dst[((r + N / 2) & (N - 1)) * N + ((col + N / 2) & (N - 1))] = v;
+    });
+    return;
+  }
   float2 y[C::NACC];
   col_stage<N, 0>(G, twc, [&](int idx, int, int, float2 v) { y[idx] = v; });
   const bool aligned = (reinterpret_cast<uintptr_t>(dst) & 15) == 0;   // uniform
@@ -1231,15 +1261,19 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_grid(const GridArgs& a, bool ci4, hipStream_t st) {
+template <int CELLS>
+hipError_t launch_grid_cells(const GridArgs& a, bool ci4, hipStream_t st) {
   const size_t lds = sizeof(float2) * (a.n_ant + a.n_taps);
-  const int64_t parts = (static_cast<int64_t>(a.L) * a.L + 256 * kGridCells - 1) / (256 * kGridCells);
+  const int64_t parts = CELLS == 1 ? 1 : (static_cast<int64_t>(a.L) * a.L + 256 * CELLS - 1) / (256 * CELLS);
   const int64_t blocks = a.n_time * a.n_chan * parts;   // frames checked < 2^31 by the caller
-  if (ci4)
-    hipLaunchKernelGGL(grid_kernel<true>, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, a);
-  else
-    hipLaunchKernelGGL(grid_kernel<false>, dim3(static_cast<unsigned>(blocks)), dim3(256), lds, st, a);
+  const dim3 grid(static_cast<unsigned>(blocks));
+  if (ci4) hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<true, CELLS>), grid, dim3(256), lds, st, a);
+  else hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<false, CELLS>), grid, dim3(256), lds, st, a);
   return hipGetLastError();
+}
+
+hipError_t launch_grid(const GridArgs& a, bool ci4, hipStream_t st) {
+  return grid_cells(a.L) == 8 ? launch_grid_cells<8>(a, ci4, st) : launch_grid_cells<1>(a, ci4, st);
 }
 
 hipError_t launch_self_power(const GridArgs& a, bool ci4, hipStream_t st) {
