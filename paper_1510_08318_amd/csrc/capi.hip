@@ -73,7 +73,8 @@ struct moff_plan_s {
   KernelFootprint footprints[moff::kMaxVariants + 1] = {};   // of every variant (queried at creation)
   int adj_blocks[moff::kMaxVariants][4] = {};   // fused adjoint: workgroups per CU by variant and waves per SIMD (0: unfit)
   int variant = 0;          // index into hp.variants
-  int short_variant = -1;   // untuned calls of few samples: their variant (-1: the same)
+  int short_variant = -1;   // untuned calls of at most short_time samples: their variant (-1: the same)
+  int64_t short_time = 0;
   int slices = 0;           // time slices; 0 = heuristic
   bool tuned = false;
   int adj_waves = 1;        // fused adjoint: waves per SIMD its registers are sized for
@@ -220,6 +221,15 @@ bool is_split(const HostPlan& hp, int variant) {
   return hp.split.on && variant == static_cast<int>(hp.variants.size());
 }
 
+// Workgroups of `lds` bytes a compute unit holds: what the runtime's query says, but
+// its 160 KB are handed out in pieces of 1280 bytes, which the query leaves out (134
+// antennas at N = 32: 20 of 8 KB by the query, 18 in truth, and 20 slices of 253
+// channels ran a second round, 418 us against 302 with 16).
+int held(int query, size_t lds) {
+  const size_t pieces = (lds + 32 + 1279) / 1280;   // (and 32 static bytes)
+  return std::max(1, std::min<int>(query, static_cast<int>(size_t(160) * 1024 / 1280 / pieces)));
+}
+
 // The footprint of a variant, from the plan's device (an occupancy query of
 // several microseconds, so plans keep the answers).
 KernelFootprint query_footprint(moff_plan p, int variant) {
@@ -235,13 +245,13 @@ KernelFootprint query_footprint(moff_plan p, int variant) {
   } else if (is_split(hp, variant)) {
     f.per_slice = hp.n_chan;
     f.lds = static_cast<size_t>(moff::split_layout(hp.N, hp.n_ant).end);
-    f.resident = std::max(1, moff::split_blocks_per_cu(hp.N, ci4, !hp.split.real, hp.n_ant)) * std::max(1, p->cu_count);
+    f.resident = held(moff::split_blocks_per_cu(hp.N, ci4, !hp.split.real, hp.n_ant), f.lds) * std::max(1, p->cu_count);
     f.threads = moff::split_shape(hp.N).NW * 64;
   } else {
     const HostPlan::Variant& V = hp.variants[variant];
     f.per_slice = V.shape.SX * hp.n_chan;
     f.lds = moff::fused_lds_bytes(hp.N, variant, V.n_weights(), hp.n_ant);
-    f.resident = std::max(1, moff::fused_blocks_per_cu(hp.N, variant, ci4, f.lds)) * std::max(1, p->cu_count);
+    f.resident = held(moff::fused_blocks_per_cu(hp.N, variant, ci4, f.lds), f.lds) * std::max(1, p->cu_count);
     f.threads = V.shape.NT;
   }
   return f;
@@ -308,10 +318,8 @@ int default_slices(const HostPlan& hp, const KernelFootprint& f, bool matrix, in
 LaunchConfig launch_config(moff_plan p, int64_t n_time) {
   const HostPlan& hp = p->hp;
   LaunchConfig lc{};
-  // (a call of fewer than eight samples of few antennas at N = 256 is mostly what a
-  // workgroup does once, less with 256 threads than with 512: 30.0 against 31.2 us at
-  // 3 channels x 6 samples of 68 antennas, 36.9 against 38.6 at 20 x 3 of 100)
-  lc.variant = std::min<int>(p->short_variant >= 0 && n_time < 8 ? p->short_variant : p->variant, n_variants(hp) - 1);
+  const bool brief = p->short_variant >= 0 && n_time <= p->short_time;
+  lc.variant = std::min<int>(brief ? p->short_variant : p->variant, n_variants(hp) - 1);
   int slices = p->slices;
   if (slices <= 0)
     slices = default_slices(hp, footprint(p, lc.variant), is_mfma(hp) || is_split(hp, lc.variant), n_time);
@@ -762,6 +770,14 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
         p->adj_blocks[v][w] = std::max(
             0, moff::adjoint_fused_blocks_per_cu(hp.N, static_cast<int>(v), hp.flags & MOFF_IN_CI4, w, lds));
     }
+    // A call too short to give every compute unit a frame: at N = 128 the FFT's two
+    // classes of a frame run on two of them (23.2 against 26.7 us at 1 channel x 16
+    // samples of 359 antennas, 26.8 against 31.3 at 8 x 16, 33.6 against 36.6 at 2 x
+    // 128; 40.6 against 40.9 at 24 x 16).  At N = 64 there is one class.
+    if (hp.N == 128 && hp.split.on && p->footprints[0].lds <= size_t(159) * 1024) {
+      p->short_variant = 0;
+      p->short_time = std::max(1, p->cu_count) / hp.n_chan;
+    }
     // Where the second FFT shape at N = 256 fits its LDS, its two classes of 512
     // threads beat the four of 256 (image 23.3 against 28.7 ms at 1024 channels x
     // 256 samples of 350 antennas, 60 against 69 us at 4 x 23 of 578), and so
@@ -773,7 +789,11 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
       const bool few = hp.n_ant <= hp.variants[0].shape.NT;
       if (p->footprints[1].lds <= size_t(159) * 1024 && !(few && !p->d_progw[1])) {
         p->variant = 1;
-        p->short_variant = few ? 0 : 1;
+        // (a call of fewer than eight samples of few antennas is mostly what a
+        // workgroup does once, less with 256 threads than with 512: 30.0 against
+        // 31.2 us at 3 channels x 6 samples of 68, 36.9 against 38.6 at 20 x 3 of 100)
+        p->short_variant = few ? 0 : -1;
+        p->short_time = 7;
       }
       if (p->adj_blocks[1][p->adj_waves] > 0) p->adj_variant = 1;
     }
