@@ -80,6 +80,7 @@ struct GridArgs {
   double* A;                   // [C][types]
   int n_ant, n_chan, n_taps, n_types, L;
   int64_t n_time;
+  int parts;                   // workgroups per frame of the gridding (set by launch_grid)
 };
 
 struct Fft2Args {
@@ -139,6 +140,7 @@ struct GradFinalArgs {
   float2* grad;                // [C][n_ant]
   double* rho;                 // [C][kRhoParts][kMaxTypes] scratch
   int N, n_ant, n_chan, n_types, subtract;
+  int rho_parts;               // ranges rho is summed in (set by launch_grad_final)
   double scale;                // 2 s / T
 };
 

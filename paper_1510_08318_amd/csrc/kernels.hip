@@ -654,7 +654,9 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
 // ---------------------------------------------------------------------------
 
 // Calibrate a frame into LDS, then every aperture cell sums its CSR row
-// (antenna-ascending) and writes Eg.  One workgroup per 256 x 8 cells of a frame:
+// (antenna-ascending) and writes Eg.  One workgroup per 256 x 8 cells of a frame, or
+// one per frame where those alone fill the card several times (each calibrates all
+// antennas: 2288 frames of 673 at N = 128 297 us with two, 282 with the form before):
 // each thread walks eight cells' rows side by side, so that the loads of all of
 // them are in flight at once (a cell at a time, one workgroup per frame, was a
 // chain of loads per cell: 23 us became 18 at 768 frames of 256 antennas, N = 128,
@@ -662,6 +664,7 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
 // cells keeps one workgroup per frame that takes them one at a time: eight left
 // seven eighths of it idle at N = 32 and half at N = 64 (39 us against 21 and 26
 // at 6760 frames), four at N = 64 took 29.
+constexpr int64_t kGridFrames = 2048;   // eight workgroups of 256 threads to each of 256 compute units
 constexpr int grid_cells(int L) { return L * L >= 256 * 8 ? 8 : 1; }
 
 template <bool CI4, int CELLS>
@@ -669,12 +672,12 @@ __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
   extern __shared__ float2 lds[];
   float2* e = lds;               // [n_ant]
   float2* K = e + a.n_ant;       // [n_taps]
-  const int ncell = a.L * a.L, parts = CELLS == 1 ? 1 : (ncell + 256 * CELLS - 1) / (256 * CELLS);
-  const int64_t f = blockIdx.x / parts;  // frame = t * n_chan + c
+  const int ncell = a.L * a.L;
+  const int64_t f = blockIdx.x / a.parts;  // frame = t * n_chan + c
   const int c = static_cast<int>(f % a.n_chan);
-  const int cell0 = static_cast<int>(blockIdx.x % parts) * 256 * CELLS + threadIdx.x;
+  int cell0 = static_cast<int>(blockIdx.x % a.parts) * 256 * CELLS + threadIdx.x;
   int k0[CELLS], k1[CELLS];
-  if constexpr (CELLS > 1) {   // (requested before the samples)
+  auto rows = [&] {
 #pragma unroll
     for (int i = 0; i < CELLS; ++i) {
       const int cell = cell0 + 256 * i;
@@ -684,7 +687,8 @@ __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
         k1[i] = a.csr_ptr[cell + 1];
       }
     }
-  }
+  };
+  if constexpr (CELLS > 1) rows();   // (requested before the samples)
   const size_t base = static_cast<size_t>(f) * a.n_ant;
   for (int i = threadIdx.x; i < a.n_ant; i += 256) {
     const float2 g = a.gains ? a.gains[static_cast<size_t>(c) * a.n_ant + i] : make_float2(1.f, 0.f);
@@ -705,29 +709,33 @@ __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
       out[cell] = s;
     }
   } else {
-    float2 s[CELLS];
+    for (;; rows()) {
+      float2 s[CELLS];
 #pragma unroll
-    for (int i = 0; i < CELLS; ++i) s[i] = make_float2(0.f, 0.f);
-    for (bool more = true; more;) {
-      more = false;
-      int ant[CELLS], tap[CELLS];
+      for (int i = 0; i < CELLS; ++i) s[i] = make_float2(0.f, 0.f);
+      for (bool more = true; more;) {
+        more = false;
+        int ant[CELLS], tap[CELLS];
+#pragma unroll
+        for (int i = 0; i < CELLS; ++i)
+          if (k0[i] < k1[i]) {
+            ant[i] = a.csr_ant[k0[i]];
+            tap[i] = a.csr_tap[k0[i]];
+          }
+#pragma unroll
+        for (int i = 0; i < CELLS; ++i)
+          if (k0[i] < k1[i]) {
+            add(s[i], ant[i], tap[i]);
+            ++k0[i];
+            more = more || k0[i] < k1[i];
+          }
+      }
 #pragma unroll
       for (int i = 0; i < CELLS; ++i)
-        if (k0[i] < k1[i]) {
-          ant[i] = a.csr_ant[k0[i]];
-          tap[i] = a.csr_tap[k0[i]];
-        }
-#pragma unroll
-      for (int i = 0; i < CELLS; ++i)
-        if (k0[i] < k1[i]) {
-          add(s[i], ant[i], tap[i]);
-          ++k0[i];
-          more = more || k0[i] < k1[i];
-        }
+        if (cell0 + 256 * i < ncell) out[cell0 + 256 * i] = s[i];
+      cell0 += a.parts * 256 * CELLS;
+      if (cell0 - static_cast<int>(threadIdx.x) >= ncell) break;   // uniform
     }
-#pragma unroll
-    for (int i = 0; i < CELLS; ++i)
-      if (cell0 + 256 * i < ncell) out[cell0 + 256 * i] = s[i];
   }
 }
 
@@ -930,7 +938,8 @@ __global__ __launch_bounds__(256) void degrid_kernel(DegridArgs a) {
 // The three sums of the gain gradient that wait for nothing but the frames, one
 // launch: grid (q_blocks + rho_blocks + d_blocks, n_chan), each workgroup one of
 //   Q = sum_t |E|^2 of 64 antennas in float64, a contiguous range of time per wave;
-//   rho_p = sum_pix R P_p over one of kRhoParts contiguous ranges of pixels;
+//   rho_p = sum_pix R P_p over one of rho_parts contiguous ranges of pixels (2048 or
+//       more each, at most kRhoParts: 16 of an image of 1024 idled most of their lanes);
 //   D = sum of the per-(slice, class) partial sums of 64 antennas, a contiguous
 //       range of partials per wave;
 // waves' sums are added in order.  Bound by the bytes they read, or on a small
@@ -950,7 +959,7 @@ __global__ __launch_bounds__(64 * kTermWaves) void grad_terms_kernel(GradTermsAr
   if (b >= a.q_blocks && b < a.q_blocks + a.rho_blocks) {   // uniform
     b -= a.q_blocks;
     const size_t npix = static_cast<size_t>(f.N) * f.N;
-    const size_t i0 = b * npix / kRhoParts, i1 = (b + 1) * npix / kRhoParts;
+    const size_t i0 = b * npix / f.rho_parts, i1 = (b + 1) * npix / f.rho_parts;
     const float* R = f.R + static_cast<size_t>(c) * npix;
     double sums[kMaxTypesDev] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -1023,7 +1032,7 @@ __global__ __launch_bounds__(256) void grad_final_kernel(GradFinalArgs a) {
   if (a.subtract) {
     if (threadIdx.x < kMaxTypesDev) {
       double s = 0.0;
-      for (int k = 0; k < kRhoParts; ++k)
+      for (int k = 0; k < a.rho_parts; ++k)
         s += a.rho[(static_cast<size_t>(c) * kRhoParts + k) * kMaxTypesDev + threadIdx.x];
       rho[threadIdx.x] = s;
     }
@@ -1262,10 +1271,12 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {
 }
 
 template <int CELLS>
-hipError_t launch_grid_cells(const GridArgs& a, bool ci4, hipStream_t st) {
+hipError_t launch_grid_cells(const GridArgs& args, bool ci4, hipStream_t st) {
+  GridArgs a = args;
   const size_t lds = sizeof(float2) * (a.n_ant + a.n_taps);
-  const int64_t parts = CELLS == 1 ? 1 : (static_cast<int64_t>(a.L) * a.L + 256 * CELLS - 1) / (256 * CELLS);
-  const int64_t blocks = a.n_time * a.n_chan * parts;   // frames checked < 2^31 by the caller
+  const int64_t frames = a.n_time * a.n_chan;   // checked < 2^31 by the caller
+  a.parts = CELLS == 1 || frames >= kGridFrames ? 1 : (a.L * a.L + 256 * CELLS - 1) / (256 * CELLS);
+  const int64_t blocks = frames * a.parts;
   const dim3 grid(static_cast<unsigned>(blocks));
   if (ci4) hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<true, CELLS>), grid, dim3(256), lds, st, a);
   else hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<false, CELLS>), grid, dim3(256), lds, st, a);
@@ -1345,8 +1356,10 @@ hipError_t launch_degrid(const DegridArgs& a, bool ci4, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_grad_final(const GradFinalArgs& a, const void* E, bool ci4, int64_t n_time, const double2* Dp,
+hipError_t launch_grad_final(const GradFinalArgs& args, const void* E, bool ci4, int64_t n_time, const double2* Dp,
                              int parts, hipStream_t st) {
+  GradFinalArgs a = args;
+  a.rho_parts = std::max(1, std::min(kRhoParts, a.N * a.N / 2048));
   const int ant_blocks = (a.n_ant + 63) / 64;
   GradTermsArgs t{};
   t.E = E;
@@ -1354,7 +1367,7 @@ hipError_t launch_grad_final(const GradFinalArgs& a, const void* E, bool ci4, in
   t.Dp = Dp;
   t.parts = parts;
   t.q_blocks = Dp && a.subtract ? ant_blocks : 0;
-  t.rho_blocks = a.subtract ? kRhoParts : 0;
+  t.rho_blocks = a.subtract ? a.rho_parts : 0;
   t.d_blocks = Dp ? ant_blocks : 0;
   const dim3 grid(t.q_blocks + t.rho_blocks + t.d_blocks, a.n_chan), block(64 * kTermWaves);
   if (grid.x > 0) {
