@@ -779,7 +779,7 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
       p->short_time = std::max(1, p->cu_count) / hp.n_chan;
     }
     // Where the second FFT shape at N = 256 fits its LDS, its two classes of 512
-    // threads beat the four of 256 (image 23.3 against 28.7 ms at 1024 channels x
+    // threads beat the four of 256 (image 21.3 against 26.9 ms at 1024 channels x
     // 256 samples of 350 antennas, 60 against 69 us at 4 x 23 of 578), and so
     // they do for the gradient (7.4 against 16.7 ms at 256 x 128 of 1024).
     // Not for an image of few antennas with complex tables, whose weights are looked
