@@ -41,9 +41,13 @@
 // Two workgroup barriers per frame.
 //
 // Scale: samples are scaled by a power of two so that folded values stay at or
-// below 2^kSplitField.  4+4-bit samples have a fixed bound; for complex64 the
-// scale follows the largest sample component seen so far (a frame that exceeds
-// it rescales the running sums, a rare uniform branch).
+// below 2^kSplitField.  4+4-bit samples have a fixed bound, 8 times the largest
+// gain among the antennas with a sample other than zero in the slice (looked up
+// beyond its first frame only where that leaves out a larger gain: a bound on all
+// gains followed a dead antenna's, whatever it was, and at a gain of 1e6 the
+// relative error of the others' image came to 1e-2); for complex64 the scale
+// follows the largest sample component seen so far (a frame that exceeds it
+// rescales the running sums, a rare uniform branch).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -158,7 +162,7 @@ void split_kernel(SplitArgs a) {
   constexpr int NACC = NW * 2 * 4 * 2;  // accumulators per lane: row block, base / partner column, row, base / partner row
   extern __shared__ uint4 lds_split[];
   __shared__ double Atot[kMaxTypesDev];
-  __shared__ float wave_max[NW];
+  __shared__ float2 wave_max[NW];
   __shared__ int exceeded;
   char* lds = reinterpret_cast<char*>(lds_split);
   const SplitLayout lay = split_layout(N, a.n_ant);
@@ -177,14 +181,27 @@ void split_kernel(SplitArgs a) {
   if (item >= a.n_chan * a.slices) return;
   const int c = item % a.n_chan, slice = item / a.n_chan;
 
+  const int64_t T = a.n_time;
+  const int64_t t0 = slice * T / a.slices, t1 = (slice + 1) * T / a.slices;
+  const size_t frame_stride = static_cast<size_t>(a.n_chan) * a.n_ant;
+  const size_t chan0 = static_cast<size_t>(c) * a.n_ant;
+
+  // the samples of the first kPre antennas per lane are loaded a frame ahead
+  constexpr int kPre = 2;
+  float2 raw[kPre];
+  auto load_raw = [&](int64_t t) {
+    const size_t base = static_cast<size_t>(t) * frame_stride + chan0;
+#pragma unroll
+    for (int q = 0; q < kPre; ++q)
+      if (tid + q * NT < a.n_ant) raw[q] = load_sample(a.E, base + tid + q * NT, CI4);
+  };
+  if (CI4 && t0 < t1) load_raw(t0);
+
   for (int i = tid; i < L * GP * 8 / 16; i += NT) lds_split[i] = make_uint4(0u, 0u, 0u, 0u);
-  float gmax = 0.f;   // largest |Re g| + |Im g| of this lane's antennas (finite ones)
   for (int i = tid; i < a.n_ant; i += NT) {
     const float2 gv = a.gains ? a.gains[static_cast<size_t>(c) * a.n_ant + i] : make_float2(1.f, 0.f);
     gl[i] = gv;
     pw[i] = 0.0;
-    const float m = fabsf(gv.x) + fabsf(gv.y);
-    if (m < __builtin_huge_valf()) gmax = fmaxf(gmax, m);
   }
   if (tid == 0) {
     e[a.n_ant] = make_float2(0.f, 0.f);
@@ -215,11 +232,6 @@ void split_kernel(SplitArgs a) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[s][i >> 3][(i >> 1) & 3][i & 1] = 0.f;
 
-  const int64_t T = a.n_time;
-  const int64_t t0 = slice * T / a.slices, t1 = (slice + 1) * T / a.slices;
-  const size_t frame_stride = static_cast<size_t>(a.n_chan) * a.n_ant;
-  const size_t chan0 = static_cast<size_t>(c) * a.n_ant;
-
   // scale 2^sk; `limit` is the largest sample component it allows
   int sk = 0;
   float scale = 1.f, limit = 0.f;
@@ -231,32 +243,65 @@ void split_kernel(SplitArgs a) {
     scale = ldexpf(1.f, sk);
     limit = ldexpf(1.f, ex);
   };
-  auto wg_max = [&](float v) {       // largest value over the workgroup (contains barriers)
+  auto wg_max = [&](float u, float v) {   // largest values over the workgroup (contains barriers); v: 4+4-bit only
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
-    if (lane == 0) wave_max[w] = v;
+    for (int off = 32; off >= 1; off >>= 1) {
+      u = fmaxf(u, __shfl_xor(u, off, 64));
+      if constexpr (CI4) v = fmaxf(v, __shfl_xor(v, off, 64));
+    }
+    if (lane == 0) wave_max[w] = make_float2(u, v);
     __syncthreads();
-    float r = wave_max[0];
+    u = wave_max[0].x, v = wave_max[0].y;
 #pragma unroll
-    for (int i = 1; i < NW; ++i) r = fmaxf(r, wave_max[i]);
+    for (int i = 1; i < NW; ++i) {
+      u = fmaxf(u, wave_max[i].x);
+      if constexpr (CI4) v = fmaxf(v, wave_max[i].y);
+    }
     __syncthreads();
-    return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(r)));
+    auto uniform = [](float x) { return __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(x))); };
+    return make_float2(uniform(u), CI4 ? uniform(v) : 0.f);
   };
   if constexpr (CI4) {
-    const float m = 8.f * wg_max(gmax);
-    if (m > 0.f && m < __builtin_huge_valf()) set_scale(m);
+    // |Re g| + |Im g| of antenna i, zero where it is not finite
+    auto gain = [&](int i) {
+      const float m = fabsf(gl[i].x) + fabsf(gl[i].y);
+      return m < __builtin_huge_valf() ? m : 0.f;
+    };
+    auto sample = [&](int64_t t, int i) {
+      return reinterpret_cast<const uint8_t*>(a.E)[static_cast<size_t>(t) * frame_stride + chan0 + i];
+    };
+    auto use = [&](float m) {
+      if (m > 0.f && m < __builtin_huge_valf()) set_scale(m);
+    };
+    float seen = 0.f, all = 0.f;   // largest gain where the first frame has a sample, and of all
+    auto see = [&](int i, bool on) {
+      const float m = gain(i);
+      all = fmaxf(all, m);
+      if (on) seen = fmaxf(seen, m);
+    };
+    if (t0 < t1) {
+#pragma unroll
+      for (int q = 0; q < kPre; ++q)
+        if (tid + q * NT < a.n_ant) see(tid + q * NT, raw[q].x != 0.f || raw[q].y != 0.f);
+      for (int i = tid + kPre * NT; i < a.n_ant; i += NT) see(i, sample(t0, i) != 0);
+    }
+    const float2 most = wg_max(seen, all);
+    use(8.f * most.x);
+    if (8.f * most.y > limit) {
+      for (int i = tid; i < a.n_ant; i += NT) {
+        const float m = gain(i);
+        if (!(m > most.x)) continue;
+        uint32_t any = 0;
+        for (int64_t t = t0; t < t1 && any == 0; t += 8)
+#pragma unroll
+          for (int k = 0; k < 8; ++k) any |= sample(t + k < t1 ? t + k : t1 - 1, i);
+        if (any != 0) seen = fmaxf(seen, m);
+      }
+      use(8.f * wg_max(seen, 0.f).x);
+    }
   }
 
-  // ingest of frame t: e = g E scaled, self power per antenna in float64.  The
-  // samples of the first kPre antennas per lane are loaded a frame ahead.
-  constexpr int kPre = 2;
-  float2 raw[kPre];
-  auto load_raw = [&](int64_t t) {
-    const size_t base = static_cast<size_t>(t) * frame_stride + chan0;
-#pragma unroll
-    for (int q = 0; q < kPre; ++q)
-      if (tid + q * NT < a.n_ant) raw[q] = load_sample(a.E, base + tid + q * NT, CI4);
-  };
+  // ingest of frame t: e = g E scaled, self power per antenna in float64
   auto ingest = [&](int64_t t) {
     bool over = false;
     auto take = [&](int i, float2 r) {
@@ -287,7 +332,7 @@ void split_kernel(SplitArgs a) {
         const float m = fmaxf(fabsf(v.x), fabsf(v.y));
         if (m < __builtin_huge_valf()) mx = fmaxf(mx, m);
       }
-      mx = wg_max(mx);
+      mx = wg_max(mx, 0.f).x;
       const int old = sk;
       set_scale(fminf(4.f * mx, 3.0e38f));   // with headroom: later frames seldom exceed it
       for (int i = tid; i < a.n_ant; i += NT) {
@@ -317,7 +362,7 @@ void split_kernel(SplitArgs a) {
   int in_block = 0;
 
   if (t0 < t1) {
-    load_raw(t0);
+    if constexpr (!CI4) load_raw(t0);
     __syncthreads();
     ingest(t0);
     if (t0 + 1 < t1) load_raw(t0 + 1);
