@@ -245,7 +245,7 @@ KernelFootprint query_footprint(moff_plan p, int variant) {
   } else if (is_split(hp, variant)) {
     f.per_slice = hp.n_chan;
     f.lds = static_cast<size_t>(moff::split_layout(hp.N, hp.n_ant).end);
-    f.resident = held(moff::split_blocks_per_cu(hp.N, ci4, !hp.split.real, hp.n_ant), f.lds) * std::max(1, p->cu_count);
+    f.resident = held(moff::split_blocks_per_cu(hp.N, ci4, !hp.split.real, uv_rule(hp), hp.n_ant), f.lds) * std::max(1, p->cu_count);
     f.threads = moff::split_shape(hp.N).NW * 64;
   } else {
     const HostPlan::Variant& V = hp.variants[variant];
@@ -395,6 +395,7 @@ moff::SplitArgs split_args(moff_plan p, const void* E, int64_t n_time, const flo
   a.Pp = p->d_Pp;
   a.subtract = (hp.flags & MOFF_AUTOCORR_NONE) ? 0 : 1;
   a.minus_one = -1.f;
+  a.third = uv_rule(hp) ? 1 : 0;
   return a;
 }
 

@@ -191,10 +191,11 @@ struct SplitArgs {
   int mode;
   double* acc64;               // [items][N^2] running sums when a slice is longer than kBlockFrames
   float minus_one;             // -1 (see split2)
+  int third;                   // images under the uv-plane rule (see kSplitParts)
 };
 // grid: workgroups, a multiple of kXcds covering every (channel, slice)
 hipError_t launch_split(const SplitArgs& a, int N, bool ci4, int grid, hipStream_t st);
-int split_blocks_per_cu(int N, bool ci4, bool cw, int n_ant);
+int split_blocks_per_cu(int N, bool ci4, bool cw, bool third, int n_ant);
 
 size_t mfma_lds_bytes(int N, int n_taps, int n_ant, int prog_len, bool prog_in_lds);
 bool mfma_prog_in_lds(int N, int n_taps, int n_ant, int prog_len);

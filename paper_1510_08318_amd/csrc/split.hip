@@ -4,15 +4,16 @@
 // binary16 numbers: every float32 value x is held as hi + lo with
 // hi = binary16(x), lo = binary16(x - hi), which keeps 22 bits or more of it
 // (absolute floor 2^-25 below operands of up to 2^15), and a product takes
-// hi.hi + hi.lo + lo.hi with float32 accumulation (v_mfma_f32_16x16x32_f16).
+// hi.hi + hi.lo + lo.hi with float32 accumulation (v_mfma_f32_16x16x32_f16); at
+// N = 64 also lo.lo, and some phase factors are three numbers (kSplitParts).
 // The 16-bit matrix rate is 16 times the float32 vector rate.  Relative 2-norm
-// error against 64 bits, FFT kernel -> this one: 2.5e-7 -> 2.2e-7 (256 antennas
-// of 3 x 3 tables, N = 128, 1000 samples), 2.8e-7 -> 1.8e-7 (61 antennas, N =
-// 64), 1.0e-7 -> 0.4e-7 (110 of 7 x 7, N = 128); 1.1e-7 -> 1.1e-7 and 1.4e-7 ->
-// 1.6e-7 on two inputs of 203 antennas of dense complex tables at N = 64.
+// error against 64 bits, FFT kernel -> this one, 5 channels x 257 samples of 203
+// antennas: dense complex tables 2.5e-7 -> 0.5e-7 at N = 64, 3.3e-7 -> 1.5e-7 at
+// 128; under the uv-plane rule 1.5e-7 -> 1.0e-7 and 1.6e-7 -> 1.4e-7; 3 x 3 real
+// tables 1.2e-7 -> 0.3e-7 and 1.8e-7 -> 0.8e-7.
 //
 // Time: 128 channels x 1000 samples of 256 antennas at N = 128 2.22 -> 1.22 ms,
-// 33 x 257 of 203 at N = 64 88 -> 69 us (launch and merge included).  Bound by
+// 33 x 257 of 203 at N = 64 148 -> 67 us (launch and merge included).  Bound by
 // issue: the matrix products take 0.48 ms of the 1.22 at their peak rate, the
 // vector instructions (fold and split, pair combinations, |Y|^2, gather) 0.6,
 // and little of the two runs side by side with two waves per SIMD.
@@ -90,11 +91,13 @@ struct Coef {
 };
 
 // data . coef over K, data as the A operand (rows) or the B operand (columns);
-// the small products first.
+// the small products first.  `third` is the phase factors' third number, if any.
 template <int K, bool DataIsA>
-__device__ __forceinline__ f4 contract(const Data<K>& d, const Coef& c) {
+__device__ __forceinline__ f4 contract(const Data<K>& d, const Coef& c, const h8* third) {
   auto mul = [](h8 x, h8 y, f4 z) { return DataIsA ? mm(x, y, z) : mm(y, x, z); };
-  f4 r = mul(d.v[0], c.lo, f4{0.f, 0.f, 0.f, 0.f});
+  f4 r = {0.f, 0.f, 0.f, 0.f};
+  if (third) r = mul(d.v[0], *third, r);
+  r = mul(d.v[0], c.lo, r);
   if constexpr (K == 32) r = mul(d.v[1], c.hi, r);
   return mul(d.v[0], c.hi, r);
 }
@@ -152,7 +155,9 @@ __device__ __forceinline__ void gather_wave(const uint4* __restrict__ prog, cons
 // N = 64 half of that, three.
 constexpr int split_waves_per_simd(int N) { return N == 128 ? 2 : 3; }
 
-template <int N, bool CI4, bool CW>
+// RT: the row stage takes the phase factors' third number (N = 64 always does, in
+// both stages).
+template <int N, bool CI4, bool CW, bool RT>
 __global__ __launch_bounds__((split_shape(N).NW * 64)) __attribute__((amdgpu_waves_per_eu(split_waves_per_simd(N))))
 void split_kernel(SplitArgs a) {
   constexpr SplitShape S = split_shape(N);
@@ -210,16 +215,23 @@ void split_kernel(SplitArgs a) {
 
   // phase factors, row blocks in the order this wave takes them (its own first:
   // those are the row stage's factors too)
+  constexpr bool CT = split_third_always(N);
   Coef cs[NW], sn[NW];
+  h8 cs3[CT ? NW : 1], sn3[CT ? NW : 1];   // third numbers
   {
     const h8* src = reinterpret_cast<const h8*>(a.coef);
 #pragma unroll
     for (int s = 0; s < NW; ++s) {
       const int rb = (w + s) % NW;
-      cs[s].hi = src[((rb * 2 + 0) * 2 + 0) * 64 + lane];
-      cs[s].lo = src[((rb * 2 + 0) * 2 + 1) * 64 + lane];
-      sn[s].hi = src[((rb * 2 + 1) * 2 + 0) * 64 + lane];
-      sn[s].lo = src[((rb * 2 + 1) * 2 + 1) * 64 + lane];
+      auto part = [&](int trig, int q) { return src[((rb * 2 + trig) * kSplitParts + q) * 64 + lane]; };
+      cs[s].hi = part(0, 0);
+      cs[s].lo = part(0, 1);
+      sn[s].hi = part(1, 0);
+      sn[s].lo = part(1, 1);
+      if constexpr (CT) {
+        cs3[s] = part(0, 2);
+        sn3[s] = part(1, 2);
+      }
     }
   }
   const float m1 = a.minus_one;
@@ -334,7 +346,7 @@ void split_kernel(SplitArgs a) {
       }
       mx = wg_max(mx, 0.f).x;
       const int old = sk;
-      set_scale(fminf(4.f * mx, 3.0e38f));   // with headroom: later frames seldom exceed it
+      set_scale(fminf(2.f * mx, 3.0e38f));   // with headroom: later frames seldom exceed it
       for (int i = tid; i < a.n_ant; i += NT) {
         const float2 v = c_mul(gl[i], load_sample(a.E, base + i, CI4));
         e[i] = make_float2(v.x * scale, v.y * scale);
@@ -376,6 +388,15 @@ void split_kernel(SplitArgs a) {
     // gaps (at 128 channels x 1000 samples of 256 antennas, N = 128: 1.31 ms
     // without priorities, 1.22 with).
     __builtin_amdgcn_s_setprio(2);
+    if constexpr (RT && !CT) {
+      // (requested anew each frame: held through the loop, these 8 registers were
+      // spilled with 15 more, 1.41 ms instead of 1.28 at the shape above)
+      int zero;
+      asm volatile("s_mov_b32 %0, 0" : "=s"(zero));
+      const h8* src = reinterpret_cast<const h8*>(a.coef) + zero + w * 2 * kSplitParts * 64 + lane;
+      cs3[0] = src[2 * 64];
+      sn3[0] = src[(kSplitParts + 2) * 64];
+    }
     gather_wave<CW>(prog, progi, ends, n_steps, reinterpret_cast<const char*>(e), Gw);
     wave_sync();
     {
@@ -441,8 +462,9 @@ void split_kernel(SplitArgs a) {
           if constexpr (K == 32) d.v[1] = *reinterpret_cast<const h8*>(row + p * 2 * K + K);
           return d;
         };
-        const f4 P1 = contract<K, true>(operand(0), cs[0]), P4 = contract<K, true>(operand(1), cs[0]);
-        const f4 P3 = contract<K, true>(operand(2), sn[0]), P2 = contract<K, true>(operand(3), sn[0]);
+        const h8 *c3 = RT ? cs3 : nullptr, *s3 = RT ? sn3 : nullptr;
+        const f4 P1 = contract<K, true>(operand(0), cs[0], c3), P4 = contract<K, true>(operand(1), cs[0], c3);
+        const f4 P3 = contract<K, true>(operand(2), sn[0], s3), P2 = contract<K, true>(operand(3), sn[0], s3);
         float v[2][2][4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -485,8 +507,9 @@ void split_kernel(SplitArgs a) {
       const Data<K> sre = column(0, b, 0), sim = column(0, b, 1), dre = column(1, b, 0), dim = column(1, b, 1);
 #pragma unroll
       for (int s = 0; s < NW; ++s) {
-        const f4 P1 = contract<K, false>(sre, cs[s]), P4 = contract<K, false>(sim, cs[s]);
-        const f4 P3 = contract<K, false>(dre, sn[s]), P2 = contract<K, false>(dim, sn[s]);
+        const h8 *c3 = CT ? cs3 + s : nullptr, *s3 = CT ? sn3 + s : nullptr;
+        const f4 P1 = contract<K, false>(sre, cs[s], c3), P4 = contract<K, false>(sim, cs[s], c3);
+        const f4 P3 = contract<K, false>(dre, sn[s], s3), P2 = contract<K, false>(dim, sn[s], s3);
         const float s0 = (w + s) % NW == 0 ? sr : 1.f;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -542,7 +565,7 @@ void split_kernel(SplitArgs a) {
     }
     block_sum4<NT>(p, Atot);   // (its barriers also end every use of the grids)
   }
-  const double un = ldexp(1.0, -2 * sk), unc = ldexp(1.0, -4 * kSplitCoef);
+  const double un = ldexp(1.0, -2 * sk), unc = ldexp(1.0, -4 * split_coef(N));
   const size_t img_stride = static_cast<size_t>(N) * N;
   float* stage = reinterpret_cast<float*>(lds);   // [N][N], groups of 16 columns XORed by row / 4
   static_assert(N * N * 4 <= L * GP * 8 + 2 * K * FP, "staging must fit in the grids");
@@ -590,22 +613,24 @@ void split_kernel(SplitArgs a) {
 
 namespace {
 
-template <int N>
+template <int N, bool RT>
 const void* split_symbol_n(bool ci4, bool cw) {
-  return ci4 ? (cw ? reinterpret_cast<const void*>(split_kernel<N, true, true>)
-                   : reinterpret_cast<const void*>(split_kernel<N, true, false>))
-             : (cw ? reinterpret_cast<const void*>(split_kernel<N, false, true>)
-                   : reinterpret_cast<const void*>(split_kernel<N, false, false>));
+  return ci4 ? (cw ? reinterpret_cast<const void*>(split_kernel<N, true, true, RT>)
+                   : reinterpret_cast<const void*>(split_kernel<N, true, false, RT>))
+             : (cw ? reinterpret_cast<const void*>(split_kernel<N, false, true, RT>)
+                   : reinterpret_cast<const void*>(split_kernel<N, false, false, RT>));
 }
 
-const void* split_symbol(int N, bool ci4, bool cw) {
-  return N == 64 ? split_symbol_n<64>(ci4, cw) : N == 128 ? split_symbol_n<128>(ci4, cw) : nullptr;
+const void* split_symbol(int N, bool ci4, bool cw, bool third) {
+  if (N == 64) return split_symbol_n<64, true>(ci4, cw);
+  if (N == 128) return third ? split_symbol_n<128, true>(ci4, cw) : split_symbol_n<128, false>(ci4, cw);
+  return nullptr;
 }
 
 }  // namespace
 
 hipError_t launch_split(const SplitArgs& a, int N, bool ci4, int grid, hipStream_t st) {
-  const void* k = split_symbol(N, ci4, a.progi != nullptr);
+  const void* k = split_symbol(N, ci4, a.progi != nullptr, a.third != 0);
   if (!k || grid <= 0 || grid % kXcds != 0 || static_cast<int64_t>(grid) < static_cast<int64_t>(a.n_chan) * a.slices)
     return hipErrorInvalidValue;
   const int lds = split_layout(N, a.n_ant).end;
@@ -615,8 +640,8 @@ hipError_t launch_split(const SplitArgs& a, int N, bool ci4, int grid, hipStream
   return hipLaunchKernel(k, dim3(grid), dim3(split_shape(N).NW * 64), args, lds, st);
 }
 
-int split_blocks_per_cu(int N, bool ci4, bool cw, int n_ant) {
-  const void* k = split_symbol(N, ci4, cw);
+int split_blocks_per_cu(int N, bool ci4, bool cw, bool third, int n_ant) {
+  const void* k = split_symbol(N, ci4, cw, third);
   int n = 0;
   if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, split_shape(N).NW * 64, split_layout(N, n_ant).end) !=
                 hipSuccess)

@@ -61,10 +61,27 @@ constexpr SplitLayout split_layout(int N, int n_ant) {
   return m;
 }
 
-// Phase factors are scaled by 2^kSplitCoef and folded grid values kept at or
+// Phase factors are scaled by 2^split_coef and folded grid values kept at or
 // below 2^kSplitField, so that a row-stage result, at most
-// 2 K 2^kSplitField 2^kSplitCoef <= 2^15, fits binary16.
-constexpr int kSplitCoef = 4;
-constexpr int kSplitField = 5;
+// 2 K 2^kSplitField 2^split_coef = 2^15, fits binary16.  The bound on the folded
+// values is that of the cell with the most table weight and of every sample at its
+// largest, so they lie far below it, the more so where a few antennas or frames are
+// loud; their low halves meet the floor of binary16 (2^-25) first, and take what
+// the phase factors can spare (2^8 and 2^1: an antenna 1e4 times as loud as 203
+// others, seven samples, N = 64: relative error 3.8e-7 with 2^5 and 2^4, 1.1e-7).
+constexpr int kSplitField = 8;
+constexpr int split_coef(int N) { return N == 64 ? 2 : 1; }
+
+// binary16 numbers per phase factor.  Two keep 22 bits or more, but their rounding
+// is the same in every frame and does not average out as the samples' does: with
+// two the error of an image under the uv-plane rule, which takes out the part
+// proportional to the image, came to 1.1 times the FFT kernel's at N = 64 and 0.9
+// to 1.05 at N = 128 (203 antennas of dense complex tables; without that rule to
+// 0.5 and less).  At N = 64, where the gather bounds the kernel, both stages take a
+// third (33 bits): 0.65.  At N = 128 the row stage takes it, for images under that
+// rule only: 0.8 to 1.0 for 5 % more time; the column stage has 4 times as many
+// products and no registers left.
+constexpr int kSplitParts = 3;
+constexpr bool split_third_always(int N) { return N == 64; }
 
 }  // namespace moff

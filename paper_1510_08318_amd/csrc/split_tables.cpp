@@ -17,8 +17,9 @@ void build_split_tables(HostPlan& P) {
   const int L = S.L, K = S.K, NW = S.NW;
   if (split_layout(P.N, P.n_ant).end > kMfmaLdsMax) return;
 
-  // ---- phase factors, [block of 16 base outputs][cos, sin][high, low][lane][8]
-  T.coef.assign(static_cast<size_t>(NW) * 2 * 2 * 64 * 8, 0);
+  // ---- phase factors, [block of 16 base outputs][cos, sin][part, high first][lane][8]
+  const int parts = kSplitParts;
+  T.coef.assign(static_cast<size_t>(NW) * 2 * parts * 64 * 8, 0);
   for (int b = 0; b < NW; ++b)
     for (int part = 0; part < 2; ++part)
       for (int lane = 0; lane < 64; ++lane)
@@ -28,16 +29,17 @@ void build_split_tables(HostPlan& P) {
           // angle pi (2 i - L + 1) p / N, reduced modulo 2 N units of pi / N
           const long long u = (static_cast<long long>(2 * i - L + 1) * p) % (2 * P.N);
           const double a = 3.14159265358979323846264338327950288 * static_cast<double>(u) / P.N;
-          const double v = std::ldexp(part == 0 ? std::cos(a) : std::sin(a), kSplitCoef);
-          const uint16_t hi = to_binary16(v);
-          const uint16_t lo = to_binary16(v - from_binary16(hi));
-          for (int hl = 0; hl < 2; ++hl)
+          double left = std::ldexp(part == 0 ? std::cos(a) : std::sin(a), split_coef(P.N));
+          for (int q = 0; q < parts; ++q) {
+            const uint16_t bits = to_binary16(left);
+            left -= from_binary16(bits);
             for (int copy = 0; copy < (K == 16 ? 2 : 1); ++copy) {
               // K = 16: both halves of the data meet the same factor
               const int pos = split_pos(K, i, copy) - (K == 32 ? 32 * copy : 0);
               if (pos / 8 != lane / 16) continue;
-              T.coef[(((static_cast<size_t>(b) * 2 + part) * 2 + hl) * 64 + lane) * 8 + pos % 8] = hl ? lo : hi;
+              T.coef[(((static_cast<size_t>(b) * 2 + part) * parts + q) * 64 + lane) * 8 + pos % 8] = bits;
             }
+          }
         }
 
   // ---- gather programs, one per wave: the non-empty cells of its row pairs,
