@@ -438,12 +438,13 @@ moff_status moff_image_staged(moff_plan plan, const void* E_dev, int64_t n_time,
  * float32.
  * MOFF_NORM_PAIRS scales as for moff_image.
  * Cost: O(n_chan (n_time n_ant^2 + n_ant^2 + N^2 log N)) work.  Channels run in
- * chunks whose workspace stays within about 2 GiB (at least one channel): per
+ * chunks whose workspace stays within about 2 GiB (4 GiB at 4000 antennas, as
+ * much as eight channels take; fewer channels where that cannot be allocated): per
  * channel 8 n_ant^2 + 8 L N bytes, 8 L (2L - 1) with one table type or
  * 8 (n_types^2 + 1) (2L - 1)^2 with several, and the staged samples, 2 bytes each
  * (4+4-bit) or 12 (complex64).  Where the samples leave no room for eight channels
- * they are taken in passes over time, with 16 n_ant^2 bytes for the sums between
- * them.  The workspace is owned by the plan and shared with the plan's other entry
+ * they are taken in passes over time of at least 8 n_ant^2 bytes of samples, with
+ * 16 n_ant^2 bytes for the sums between them.  The workspace is owned by the plan and shared with the plan's other entry
  * points.  The pair tables (about 3 n_ant^2 bytes: each unordered pair once) are
  * built and uploaded on the first call.
  * Errors: MOFF_ERR_INVALID_ARG for null or misaligned pointers or n_time < 1;

@@ -164,7 +164,11 @@ moff_status grow(void** buf, size_t* have, size_t bytes) {
     *buf = nullptr;
     *have = 0;
   }
-  if (hipMalloc(buf, bytes) != hipSuccess) return MOFF_ERR_NOMEM;
+  if (hipMalloc(buf, bytes) != hipSuccess) {
+    (void)hipGetLastError();   // (a later launch would report it as its own)
+    *buf = nullptr;
+    return MOFF_ERR_NOMEM;
+  }
   *have = bytes;
   return MOFF_OK;
 }
@@ -1376,34 +1380,15 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
     p->fx_xs = t.xs;
   }
   const int NL = p->fx_NL, NTP = hp.n_ktypes * hp.n_ktypes;
-  // Workspace per channel; channels run in chunks that keep it within ~2 GiB.
-  // The staged samples of a long integration are taken in passes over time
-  // where fewer than eight channels (one per XCD) would fit otherwise; the
-  // visibilities are then summed over the passes in float64.
+  // Workspace per channel
   const bool ci4 = hp.flags & MOFF_IN_CI4, one_type = hp.n_ktypes == 1;
-  const size_t budget = size_t(2) << 30, pairs = static_cast<size_t>(hp.n_ant) * hp.n_ant;
-  const size_t v_per = sizeof(float2) * pairs;
+  const size_t v_per = sizeof(float2) * static_cast<size_t>(hp.n_ant) * hp.n_ant;
   const size_t h_per = sizeof(float2) * (one_type ? static_cast<size_t>(hp.L) : static_cast<size_t>(NTP) * NL) * NL;
   const size_t r_per = one_type ? 0 : sizeof(float2) * NL * NL;
   const size_t z_per = sizeof(float2) * hp.L * hp.N;
-  size_t per_chan = v_per + h_per + r_per + z_per, d_per = 0, s_per = moff::fx_plane_bytes(ci4, hp.n_ant, n_time);
-  int64_t pass = n_time;
-  const size_t few = static_cast<size_t>(std::min(hp.n_chan, 8));
-  if ((per_chan + s_per) * few > budget) {
-    d_per = sizeof(double2) * pairs;
-    const size_t step = moff::fx_plane_bytes(ci4, hp.n_ant, 1);
-    const size_t room = budget / few > per_chan + d_per ? budget / few - per_chan - d_per : 0;
-    pass = static_cast<int64_t>(std::max<size_t>(1, room / step)) * moff::fx_step(ci4);
-    if (pass >= n_time) {
-      pass = n_time;
-      d_per = 0;
-    }
-    s_per = moff::fx_plane_bytes(ci4, hp.n_ant, pass);
-  }
-  per_chan = (per_chan + d_per + s_per + 255) / 256 * 256;
-  const int chunk = static_cast<int>(
-      std::max<size_t>(1, std::min<size_t>({static_cast<size_t>(hp.n_chan), budget / per_chan, size_t(65535)})));
-  s = ensure_workspace(p, per_chan * chunk);
+  const moff::FxChunks cut = moff::fx_chunks(ci4, hp.n_ant, hp.n_chan, n_time, v_per + h_per + r_per + z_per);
+  int chunk = cut.channels;
+  while ((s = ensure_workspace(p, cut.per_channel * chunk)) == MOFF_ERR_NOMEM && chunk > 1) chunk = (chunk + 1) / 2;
   if (s != MOFF_OK) return s;
   char* ws = static_cast<char*>(p->d_ws);
   moff::FxArgs a{};
@@ -1433,9 +1418,9 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   a.tw = p->d_tw;
   // (the parts with the strictest alignment first)
   a.planes = ws;
-  ws += s_per * chunk;
-  a.Vd = d_per ? reinterpret_cast<double2*>(ws) : nullptr;
-  ws += d_per * chunk;
+  ws += cut.samples * chunk;
+  a.Vd = cut.sums ? reinterpret_cast<double2*>(ws) : nullptr;
+  ws += cut.sums * chunk;
   a.V = reinterpret_cast<float2*>(ws);
   ws += v_per * chunk;
   a.H = reinterpret_cast<float2*>(ws);
@@ -1448,9 +1433,9 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   for (int c0 = 0; c0 < hp.n_chan; c0 += chunk) {
     a.c0 = c0;
     a.n_launch = std::min(chunk, hp.n_chan - c0);
-    for (int64_t t0 = 0; t0 < n_time; t0 += pass) {
+    for (int64_t t0 = 0; t0 < n_time; t0 += cut.pass) {
       a.t0 = t0;
-      a.t1 = std::min(t0 + pass, n_time);
+      a.t1 = std::min(t0 + cut.pass, n_time);
       a.first = t0 == 0;
       a.last = a.t1 == n_time;
       if (moff::launch_fx(a, ci4, static_cast<hipStream_t>(stream)) != hipSuccess) return MOFF_ERR_HIP;

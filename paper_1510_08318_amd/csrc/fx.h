@@ -6,6 +6,8 @@
 
 #include <cstdint>
 
+#include "fx_tables.h"
+
 namespace moff {
 
 // Visibility-route (FX) image of one integration, for cross-checks of the MOFF
@@ -45,15 +47,6 @@ struct FxArgs {
   double scale;
 };
 
-// Staged blocks: 4+4-bit samples as int8 planes (re, im) of 64 samples;
-// complex64 samples, calibrated, as three bfloat16 levels of x and of y, of 32.
-constexpr int kFxTile = 64;
-constexpr int fx_step(bool ci4) { return ci4 ? 64 : 32; }
-constexpr size_t fx_block_bytes(bool ci4) { return static_cast<size_t>(kFxTile) * (ci4 ? 64 * 2 : 32 * 2 * 6); }
-inline size_t fx_plane_bytes(bool ci4, int n_ant, int64_t n_time) {   // of one channel
-  return fx_block_bytes(ci4) * ((n_ant + kFxTile - 1) / kFxTile) *
-         static_cast<size_t>((n_time + fx_step(ci4) - 1) / fx_step(ci4));
-}
 // One pass over samples t0 .. t1 (a.last: then the image).
 hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st);
 }  // namespace moff
