@@ -259,7 +259,11 @@ moff_status moff_plan_mfma_tables(moff_plan plan, uint32_t* prog, uint16_t* dft,
  * budget it is built with (see moff_plan_set_adjoint_waves), on the same
  * samples and gains with the tuned image as the pixel sensitivities, and
  * keeps the fastest.  moff_plan_set_config forces a choice (slices = 0:
- * heuristic) and gives the adjoint the same shape variant where it has it; moff_plan_get_config
+ * heuristic) and gives the adjoint the same shape variant, or leaves the
+ * adjoint's as it is for the variant on the matrix cores, which it does not have;
+ * variant 0 is the FFT in float32 throughout (its matrix-core counterpart holds
+ * operands to 22 bits or more of 24, at an error against 64 bits that measures no
+ * larger).  A failed autotune leaves every choice as it was; moff_plan_get_config
  * reports the configuration a call with n_time samples would use.  Any output
  * of get_config may be NULL.
  */

@@ -951,7 +951,7 @@ moff_status moff_plan_set_config(moff_plan p, int32_t variant, int32_t slices) {
   if (!p || variant < 0 || variant >= n_variants(p->hp) || slices < 0 || slices > 256) return MOFF_ERR_INVALID_ARG;
   p->variant = variant;
   p->short_variant = -1;
-  p->adj_variant = variant;
+  if (variant < static_cast<int32_t>(p->hp.variants.size())) p->adj_variant = variant;
   p->slices = slices;
   p->tuned = false;
   return MOFF_OK;
@@ -990,6 +990,7 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
     return MOFF_ERR_HIP;
   }
   const int saved_v = p->variant, saved_s = p->slices, saved_short = p->short_variant;
+  const int saved_w = p->adj_waves, saved_av = p->adj_variant;
   p->short_variant = -1;
   const bool saved_timing = p->timing;
   p->timing = false;
@@ -1125,8 +1126,8 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
     p->variant = saved_v;
     p->short_variant = saved_short;
     p->slices = saved_s;
-    p->adj_waves = 1;
-    p->adj_variant = saved_v;
+    p->adj_waves = saved_w;
+    p->adj_variant = saved_av;
     return result;
   }
   p->variant = bv;
