@@ -654,41 +654,45 @@ __global__ __launch_bounds__(256) void reduce_kernel(ReduceArgs a) {
 // ---------------------------------------------------------------------------
 
 // Calibrate a frame into LDS, then every aperture cell sums its CSR row
-// (antenna-ascending) and writes Eg.  One workgroup per 256 x 8 cells of a frame, or
-// one per frame where those alone fill the card several times (each calibrates all
-// antennas: 2288 frames of 673 at N = 128 297 us with two, 282 with the form before):
-// each thread walks eight cells' rows side by side, so that the loads of all of
-// them are in flight at once (a cell at a time, one workgroup per frame, was a
-// chain of loads per cell: 23 us became 18 at 768 frames of 256 antennas, N = 128,
-// whose grids take 25 MB; 54 became 26 at 520 frames, N = 256).  A grid of fewer
-// cells keeps one workgroup per frame that takes them one at a time: eight left
-// seven eighths of it idle at N = 32 and half at N = 64 (39 us against 21 and 26
-// at 6760 frames), four at N = 64 took 29.
-constexpr int64_t kGridFrames = 2048;   // eight workgroups of 256 threads to each of 256 compute units
-constexpr int grid_cells(int L) { return L * L >= 256 * 8 ? 8 : 1; }
-
-template <bool CI4, int CELLS>
+// (antenna-ascending) and writes Eg; a thread takes one cell at a time, four of its
+// entries in flight.  Bound by the chain of dependent loads (a cell's bounds, its
+// entries, their samples in LDS) and by rows of unequal length within a wave.
+// Grids of more than 1024 cells (WIDE) have the next two cells' bounds requested while
+// two are summed, and where few frames would leave the card idle a.parts workgroups
+// to a frame, which take blocks of 256 cells in turn (each calibrates all antennas).
+//   768 frames of 256 antennas, 3 x 3 tables, N = 128 (grids of 25 MB): 15.1 us with
+//     an entry at a time and one workgroup per frame, 11.2 here;
+//   520 frames, N = 256: 41.8, 18.8;
+//   1292 frames of 1360 antennas, 5 x 5, N = 128: 118, 50;  3300 frames of 203
+//     antennas, 3 x 3 and 5 x 5, N = 64: 27.4, 20.0;
+//   1462 frames of 421 antennas, 3 x 3, N = 128: 23.2, 23.9 (the only kind that lost).
+// (Eight cells side by side with an entry of each in flight were as fast where rows
+// are alike, but at 1720 frames of 1833 antennas crowded in the aperture's centre,
+// rows of up to 428 entries, took 1970 us against 495 before and 228 here.)
+template <bool CI4, bool WIDE>
 __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
   extern __shared__ float2 lds[];
   float2* e = lds;               // [n_ant]
   float2* K = e + a.n_ant;       // [n_taps]
+  constexpr int AHEAD = 2;
   const int ncell = a.L * a.L;
-  const int64_t f = blockIdx.x / a.parts;  // frame = t * n_chan + c
-  const int c = static_cast<int>(f % a.n_chan);
-  int cell0 = static_cast<int>(blockIdx.x % a.parts) * 256 * CELLS + threadIdx.x;
-  int k0[CELLS], k1[CELLS];
-  auto rows = [&] {
+  const uint32_t parts = WIDE ? a.parts : 1;
+  const uint32_t f = WIDE && parts > 1 ? blockIdx.x / parts : blockIdx.x;  // frame = t * n_chan + c
+  const uint32_t c = f % static_cast<uint32_t>(a.n_chan);
+  const int stride = 256 * static_cast<int>(parts);
+  int cell = 256 * static_cast<int>(blockIdx.x - f * parts) + static_cast<int>(threadIdx.x);
+  int k0[AHEAD], k1[AHEAD];
+  auto bounds = [&](int at) {
 #pragma unroll
-    for (int i = 0; i < CELLS; ++i) {
-      const int cell = cell0 + 256 * i;
+    for (int i = 0; i < AHEAD; ++i) {
       k0[i] = k1[i] = 0;
-      if (cell < ncell) {
-        k0[i] = a.csr_ptr[cell];
-        k1[i] = a.csr_ptr[cell + 1];
+      if (at + stride * i < ncell) {
+        k0[i] = a.csr_ptr[at + stride * i];
+        k1[i] = a.csr_ptr[at + stride * i + 1];
       }
     }
   };
-  if constexpr (CELLS > 1) rows();   // (requested before the samples)
+  if constexpr (WIDE) bounds(cell);   // (requested before the samples)
   const size_t base = static_cast<size_t>(f) * a.n_ant;
   for (int i = threadIdx.x; i < a.n_ant; i += 256) {
     const float2 g = a.gains ? a.gains[static_cast<size_t>(c) * a.n_ant + i] : make_float2(1.f, 0.f);
@@ -697,45 +701,43 @@ __global__ __launch_bounds__(256) void grid_kernel(GridArgs a) {
   for (int i = threadIdx.x; i < a.n_taps; i += 256) K[i] = a.ktab[i];
   __syncthreads();
   float2* out = a.Eg + static_cast<size_t>(f) * ncell;
-  auto add = [&](float2& s, int ant, int tap) {
-    const float2 ev = e[ant], kv = K[tap];
-    s.x = fmaf(ev.x, kv.x, fmaf(-ev.y, kv.y, s.x));
-    s.y = fmaf(ev.x, kv.y, fmaf(ev.y, kv.x, s.y));
-  };
-  if constexpr (CELLS == 1) {
-    for (int cell = cell0; cell < ncell; cell += 256) {
-      float2 s = make_float2(0.f, 0.f);
-      for (int k = a.csr_ptr[cell]; k < a.csr_ptr[cell + 1]; ++k) add(s, a.csr_ant[k], a.csr_tap[k]);
-      out[cell] = s;
-    }
-  } else {
-    for (;; rows()) {
-      float2 s[CELLS];
+  auto row = [&](int k, int end) {
+    float2 s = make_float2(0.f, 0.f);
+    auto add = [&](int ant, int tap) {
+      const float2 ev = e[ant], kv = K[tap];
+      s.x = fmaf(ev.x, kv.x, fmaf(-ev.y, kv.y, s.x));
+      s.y = fmaf(ev.x, kv.y, fmaf(ev.y, kv.x, s.y));
+    };
+    for (; k + 4 <= end; k += 4) {
+      int ant[4], tap[4];
 #pragma unroll
-      for (int i = 0; i < CELLS; ++i) s[i] = make_float2(0.f, 0.f);
-      for (bool more = true; more;) {
-        more = false;
-        int ant[CELLS], tap[CELLS];
-#pragma unroll
-        for (int i = 0; i < CELLS; ++i)
-          if (k0[i] < k1[i]) {
-            ant[i] = a.csr_ant[k0[i]];
-            tap[i] = a.csr_tap[k0[i]];
-          }
-#pragma unroll
-        for (int i = 0; i < CELLS; ++i)
-          if (k0[i] < k1[i]) {
-            add(s[i], ant[i], tap[i]);
-            ++k0[i];
-            more = more || k0[i] < k1[i];
-          }
+      for (int j = 0; j < 4; ++j) {
+        ant[j] = a.csr_ant[k + j];
+        tap[j] = a.csr_tap[k + j];
       }
 #pragma unroll
-      for (int i = 0; i < CELLS; ++i)
-        if (cell0 + 256 * i < ncell) out[cell0 + 256 * i] = s[i];
-      cell0 += a.parts * 256 * CELLS;
-      if (cell0 - static_cast<int>(threadIdx.x) >= ncell) break;   // uniform
+      for (int j = 0; j < 4; ++j) add(ant[j], tap[j]);
     }
+    for (; k < end; ++k) add(a.csr_ant[k], a.csr_tap[k]);
+    return s;
+  };
+  if constexpr (WIDE) {
+    for (; cell - static_cast<int>(threadIdx.x) < ncell; cell += stride * AHEAD) {
+      int n0[AHEAD], n1[AHEAD];
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        n0[i] = k0[i];
+        n1[i] = k1[i];
+      }
+      bounds(cell + stride * AHEAD);
+#pragma unroll
+      for (int i = 0; i < AHEAD; ++i) {
+        const float2 s = row(n0[i], n1[i]);
+        if (cell + stride * i < ncell) out[cell + stride * i] = s;
+      }
+    }
+  } else {
+    for (; cell < ncell; cell += 256) out[cell] = row(a.csr_ptr[cell], a.csr_ptr[cell + 1]);
   }
 }
 
@@ -1270,21 +1272,25 @@ hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-template <int CELLS>
-hipError_t launch_grid_cells(const GridArgs& args, bool ci4, hipStream_t st) {
+hipError_t launch_grid(const GridArgs& args, bool ci4, hipStream_t st) {
   GridArgs a = args;
   const size_t lds = sizeof(float2) * (a.n_ant + a.n_taps);
   const int64_t frames = a.n_time * a.n_chan;   // checked < 2^31 by the caller
-  a.parts = CELLS == 1 || frames >= kGridFrames ? 1 : (a.L * a.L + 256 * CELLS - 1) / (256 * CELLS);
-  const int64_t blocks = frames * a.parts;
-  const dim3 grid(static_cast<unsigned>(blocks));
-  if (ci4) hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<true, CELLS>), grid, dim3(256), lds, st, a);
-  else hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<false, CELLS>), grid, dim3(256), lds, st, a);
+  const int cells = a.L * a.L;
+  // Up to 1024 frames (four workgroups of 256 threads to each of 256 compute units)
+  // a workgroup takes eight cells per thread: 1000 frames at N = 256 26.3 us, 38.3
+  // with one workgroup per frame; at N = 128 900 frames 13.4 and 14.4, but 1275
+  // frames 29.3 and 26.4, and 4000 at N = 256 328 and 275.
+  a.parts = frames <= 1024 ? std::max(1, cells / (256 * 8)) : 1;
+  const dim3 grid(static_cast<unsigned>(frames * a.parts));
+  if (cells > 1024) {
+    if (ci4) hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<true, true>), grid, dim3(256), lds, st, a);
+    else hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<false, true>), grid, dim3(256), lds, st, a);
+  } else {
+    if (ci4) hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<true, false>), grid, dim3(256), lds, st, a);
+    else hipLaunchKernelGGL(HIP_KERNEL_NAME(grid_kernel<false, false>), grid, dim3(256), lds, st, a);
+  }
   return hipGetLastError();
-}
-
-hipError_t launch_grid(const GridArgs& a, bool ci4, hipStream_t st) {
-  return grid_cells(a.L) == 8 ? launch_grid_cells<8>(a, ci4, st) : launch_grid_cells<1>(a, ci4, st);
 }
 
 hipError_t launch_self_power(const GridArgs& a, bool ci4, hipStream_t st) {
