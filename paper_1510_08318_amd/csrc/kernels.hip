@@ -772,10 +772,13 @@ __global__ __launch_bounds__(256) void self_power_kernel(GridArgs a) {
 // copy; one and a half rounds of four workgroups per CU are the rest.  520 frames
 // at N = 256: 307 -> 221.)  A single class has whole rows either way: 16 lanes store
 // 16 adjacent pixels as they come, and no output waits in a register (6760 frames
-// transposed and held: 78 us against 48 at N = 64, 21 against 13 at N = 32).
-template <int N>
+// transposed and held: 78 us against 48 at N = 64, 21 against 13 at N = 32); nor where
+// a launch has so few workgroups that one's time is the call's (PAIRS false, see
+// launch_fft2).
+template <int N, bool PAIRS>
 __global__ __launch_bounds__((FT<N, 0>::NT)) void fft2_kernel(Fft2Args a) {
   using C = FT<N, 0>;
+  static_assert(PAIRS == false || C::SX > 1, "pairs of pixels come from transposed classes");
   extern __shared__ float2 lds[];
   float2* G = lds;
   float2* twr = G + C::GRID;
@@ -791,22 +794,24 @@ __global__ __launch_bounds__((FT<N, 0>::NT)) void fft2_kernel(Fft2Args a) {
       static_assert(C::SX > 1 || C::NZR == C::L, "a single class folds nothing");
       G[cell / C::L * C::P + cell % C::L] = src[cell];
     } else {
-      const int n = cell / C::L, ix = cell % C::L;
+      const int n = PAIRS ? cell / C::L : cell % C::NZR, other = PAIRS ? cell % C::L : cell / C::NZR;
       float2 v = make_float2(0.f, 0.f);
       for (int j = 0; j * C::M + n < C::L; ++j) {
-        const float2 x = quarter_rot(src[(n + j * C::M) * C::L + ix], j * w, C::SX);
+        const int m = n + j * C::M;
+        const float2 x = quarter_rot(src[PAIRS ? m * C::L + other : other * C::L + m], j * w, C::SX);
         v = c_add(v, x);
       }
-      G[ix * C::P + n] = v;
+      G[other * C::P + n] = v;
     }
   }
   __syncthreads();
   row_stage<N, 0>(G, twr, fin);
   __syncthreads();
   float2* dst = a.Y + static_cast<size_t>(f) * N * N;
-  if constexpr (C::SX == 1) {
+  if constexpr (!PAIRS) {
     col_stage<N, 0>(G, twc, [&](int, int r, int col, float2 v) {
-      dst[((r + N / 2) & (N - 1)) * N + ((col + N / 2) & (N - 1))] = v;
+      const int q = C::SX * col + w;
+      dst[((r + N / 2) & (N - 1)) * N + ((q + N / 2) & (N - 1))] = v;
     });
     return;
   }
@@ -1104,11 +1109,11 @@ const void* fused_kernel_symbol(int N, int V, bool ci4, bool one) {
   }
 }
 
-template <int N>
+template <int N, bool PAIRS = false>
 hipError_t launch_fft2_t(const Fft2Args& a, int64_t n_frames, hipStream_t st) {
   const FrameShape S = frame_shape(N);
   const size_t lds = sizeof(float2) * (static_cast<size_t>(N / 2) * grid_pitch(N / S.SX) + N / S.SX + N);
-  auto k = fft2_kernel<N>;
+  auto k = fft2_kernel<N, PAIRS>;
   hipError_t err = hipFuncSetAttribute(reinterpret_cast<const void*>(k),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds));
   if (err != hipSuccess) return err;
@@ -1307,8 +1312,11 @@ hipError_t launch_fft2(const Fft2Args& a, int N, int64_t n_frames, hipStream_t s
     case 16: return launch_fft2_t<16>(a, n_frames, st);
     case 32: return launch_fft2_t<32>(a, n_frames, st);
     case 64: return launch_fft2_t<64>(a, n_frames, st);
-    case 128: return launch_fft2_t<128>(a, n_frames, st);
-    case 256: return launch_fft2_t<256>(a, n_frames, st);
+    // Few frames: 4 at N = 128 take 7.5 us without pairs and 10.1 with, 150 14.9 and
+    // 17.7, 200 16.8 and 17.8, but 250 21.2 and 19.1; at N = 256 3 take 16.2 and 23.8,
+    // 12 18.8 and 24.4, 20 24.8 and 25.0, 30 28.5 and 25.8.
+    case 128: return n_frames <= 200 ? launch_fft2_t<128>(a, n_frames, st) : launch_fft2_t<128, true>(a, n_frames, st);
+    case 256: return n_frames <= 20 ? launch_fft2_t<256>(a, n_frames, st) : launch_fft2_t<256, true>(a, n_frames, st);
     default: return hipErrorInvalidValue;
   }
 }
