@@ -5,7 +5,8 @@
 // hi = binary16(x), lo = binary16(x - hi), which keeps 22 bits or more of it
 // (absolute floor 2^-25 below operands of up to 2^15), and a product takes
 // hi.hi + hi.lo + lo.hi with float32 accumulation (v_mfma_f32_16x16x32_f16); at
-// N = 64 also lo.lo, and some phase factors are three numbers (kSplitParts).
+// N = 64 also lo.lo, and under the uv-plane rule the phase factors are three
+// numbers (kSplitParts).
 // The 16-bit matrix rate is 16 times the float32 vector rate.  Relative 2-norm
 // error against 64 bits, FFT kernel -> this one, 5 channels x 257 samples of 203
 // antennas: dense complex tables 2.5e-7 -> 0.5e-7 at N = 64, 3.3e-7 -> 1.5e-7 at
@@ -155,8 +156,7 @@ __device__ __forceinline__ void gather_wave(const uint4* __restrict__ prog, cons
 // N = 64 half of that, three.
 constexpr int split_waves_per_simd(int N) { return N == 128 ? 2 : 3; }
 
-// RT: the row stage takes the phase factors' third number (N = 64 always does, in
-// both stages).
+// RT: the row stage takes the phase factors' third number, at N = 64 both stages.
 template <int N, bool CI4, bool CW, bool RT>
 __global__ __launch_bounds__((split_shape(N).NW * 64)) __attribute__((amdgpu_waves_per_eu(split_waves_per_simd(N))))
 void split_kernel(SplitArgs a) {
@@ -215,7 +215,7 @@ void split_kernel(SplitArgs a) {
 
   // phase factors, row blocks in the order this wave takes them (its own first:
   // those are the row stage's factors too)
-  constexpr bool CT = split_third_always(N);
+  constexpr bool CT = RT && split_third_in_columns(N);
   Coef cs[NW], sn[NW];
   h8 cs3[CT ? NW : 1], sn3[CT ? NW : 1];   // third numbers
   {
@@ -622,7 +622,7 @@ const void* split_symbol_n(bool ci4, bool cw) {
 }
 
 const void* split_symbol(int N, bool ci4, bool cw, bool third) {
-  if (N == 64) return split_symbol_n<64, true>(ci4, cw);
+  if (N == 64) return third ? split_symbol_n<64, true>(ci4, cw) : split_symbol_n<64, false>(ci4, cw);
   if (N == 128) return third ? split_symbol_n<128, true>(ci4, cw) : split_symbol_n<128, false>(ci4, cw);
   return nullptr;
 }

@@ -77,11 +77,11 @@ constexpr int split_coef(int N) { return N == 64 ? 2 : 1; }
 // two the error of an image under the uv-plane rule, which takes out the part
 // proportional to the image, came to 1.1 times the FFT kernel's at N = 64 and 0.9
 // to 1.05 at N = 128 (203 antennas of dense complex tables; without that rule to
-// 0.5 and less).  At N = 64, where the gather bounds the kernel, both stages take a
-// third (33 bits): 0.65.  At N = 128 the row stage takes it, for images under that
-// rule only: 0.8 to 1.0 for 5 % more time; the column stage has 4 times as many
-// products and no registers left.
+// 0.5 to 0.7).  Images under that rule take a third (33 bits): at N = 64 in both
+// stages (0.65 of the FFT's error, for 3 to 19 % more time), at N = 128 in the row
+// stage only (0.8 to 1.0, 5 %), whose column stage has 4 times as many products and
+// no registers left.
 constexpr int kSplitParts = 3;
-constexpr bool split_third_always(int N) { return N == 64; }
+constexpr bool split_third_in_columns(int N) { return N == 64; }
 
 }  // namespace moff
