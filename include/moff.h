@@ -240,11 +240,12 @@ moff_status moff_plan_mfma_tables(moff_plan plan, uint32_t* prog, uint16_t* dft,
  * Launch configuration of the fused path.  The frame transform has one or two
  * shape variants per grid size (how output columns are split across
  * workgroups, threads per workgroup) and, in float32 at grid_n 64 and 128, one
- * more on the matrix cores, the last and the default there where its tables fit
- * (at grid_n 256 the default is variant 1; very short calls may default to
- * variant 0); a launch also chooses the number of time
+ * more on the matrix cores, the last, where its tables fit; a launch also
+ * chooses the number of time
  * slices: each (column class, channel, slice) is one workgroup, and per-slice
- * partial sums are reduced afterwards in a fixed order.
+ * partial sums are reduced afterwards in a fixed order.  A plan that is neither
+ * tuned nor set takes the variant and slices of least modelled time for each
+ * call's n_time.
  *
  * moff_plan_autotune times every candidate (variant x slices, including the
  * slice counts that fill whole rounds of resident workgroups) with HIP events

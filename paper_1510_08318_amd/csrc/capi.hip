@@ -19,12 +19,20 @@
 using moff::GatherEntry;
 using moff::HostPlan;
 
-// Work items per time slice, LDS bytes and resident workgroups of a variant.
+// Work items per time slice, LDS bytes and resident workgroups of a variant, and
+// what its gather takes: steps of the longest program, complex weights.
 struct KernelFootprint {
   int per_slice;
   size_t lds;
   int resident;
   int threads;
+  int steps;
+  bool complex_weights;
+};
+
+// How one fused call is launched: shape variant, time slices, workgroups.
+struct LaunchConfig {
+  int variant, slices, grid;
 };
 
 struct moff_plan_s {
@@ -72,10 +80,10 @@ struct moff_plan_s {
   int cu_count = 0;
   KernelFootprint footprints[moff::kMaxVariants + 1] = {};   // of every variant (queried at creation)
   int adj_blocks[moff::kMaxVariants][4] = {};   // fused adjoint: workgroups per CU by variant and waves per SIMD (0: unfit)
-  int variant = 0;          // index into hp.variants
-  int short_variant = -1;   // untuned calls of at most short_time samples: their variant (-1: the same)
-  int64_t short_time = 0;
-  int slices = 0;           // time slices; 0 = heuristic
+  int variant = -1;         // index into hp.variants (or the matrix-core variant after them); -1: by rule
+  int slices = 0;           // time slices; 0: by rule
+  int64_t rule_time = 0;    // the rule's answer for calls of rule_time samples (0: none yet)
+  LaunchConfig rule = {};
   bool tuned = false;
   int adj_waves = 1;        // fused adjoint: waves per SIMD its registers are sized for
   int adj_variant = 0;      // fused adjoint: shape variant (set with the image's, or tuned on its own)
@@ -210,10 +218,6 @@ moff_status uv_finalize(moff_plan p, const float* S, int64_t n_time, float* imag
   return hip_status(moff::launch_uv_finalize(u, st));
 }
 
-struct LaunchConfig {
-  int variant, slices, grid;
-};
-
 constexpr int kTuneReps = 3;    // timed batches per autotuner candidate
 constexpr int kTuneBatch = 3;   // back-to-back calls per timed batch (steady state, as in use)
 constexpr float kTuneSlack = 0.03f;   // calls this much slower than the fastest still count as equal
@@ -223,15 +227,6 @@ bool is_mfma(const HostPlan& hp) { return hp.mfma.prec != 0; }
 // The matrix-core float32 kernel is the shape variant after the FFT kernel's.
 bool is_split(const HostPlan& hp, int variant) {
   return hp.split.on && variant == static_cast<int>(hp.variants.size());
-}
-
-// Workgroups of `lds` bytes a compute unit holds: what the runtime's query says, but
-// its 160 KB are handed out in pieces of 1280 bytes, which the query leaves out (134
-// antennas at N = 32: 20 of 8 KB by the query, 18 in truth, and 20 slices of 253
-// channels ran a second round, 418 us against 302 with 16).
-int held(int query, size_t lds) {
-  const size_t pieces = (lds + 32 + 1279) / 1280;   // (and 32 static bytes)
-  return std::max(1, std::min<int>(query, static_cast<int>(size_t(160) * 1024 / 1280 / pieces)));
 }
 
 // The footprint of a variant, from the plan's device (an occupancy query of
@@ -246,16 +241,21 @@ KernelFootprint query_footprint(moff_plan p, int variant) {
     f.lds = moff::mfma_lds_bytes(hp.N, hp.n_taps, hp.n_ant, hp.mfma.prog_len, in_lds);
     f.resident = std::max(1, moff::mfma_blocks_per_cu(hp.N, hp.mfma.prec, ci4, f.lds)) * std::max(1, p->cu_count);
     f.threads = moff::mfma_threads(hp.N);
+    f.steps = hp.mfma.prog_len;
   } else if (is_split(hp, variant)) {
     f.per_slice = hp.n_chan;
     f.lds = static_cast<size_t>(moff::split_layout(hp.N, hp.n_ant).end);
-    f.resident = held(moff::split_blocks_per_cu(hp.N, ci4, !hp.split.real, uv_rule(hp), hp.n_ant), f.lds) * std::max(1, p->cu_count);
+    f.resident = std::max(1, moff::split_blocks_per_cu(hp.N, ci4, !hp.split.real, uv_rule(hp), hp.n_ant)) * std::max(1, p->cu_count);
+    f.steps = *std::max_element(hp.split.n_steps.begin(), hp.split.n_steps.end());
+    f.complex_weights = !hp.split.real;
     f.threads = moff::split_shape(hp.N).NW * 64;
   } else {
     const HostPlan::Variant& V = hp.variants[variant];
     f.per_slice = V.shape.SX * hp.n_chan;
     f.lds = moff::fused_lds_bytes(hp.N, variant, V.n_weights(), hp.n_ant);
-    f.resident = held(moff::fused_blocks_per_cu(hp.N, variant, ci4, f.lds), f.lds) * std::max(1, p->cu_count);
+    f.resident = std::max(1, moff::fused_blocks_per_cu(hp.N, variant, ci4, f.lds)) * std::max(1, p->cu_count);
+    f.steps = V.prog_len;
+    f.complex_weights = V.progw.empty();
     f.threads = V.shape.NT;
   }
   return f;
@@ -278,58 +278,99 @@ int launch_grid(const HostPlan& hp, int variant, int slices) {
   return hp.variants[variant].shape.SX * ((cs + moff::kXcds - 1) / moff::kXcds * moff::kXcds);
 }
 
-// Time slices of an untuned launch: the count with the least modelled time.
-// Items (channel-slices, times column classes) run in rounds of `resident`
-// workgroups; a round lasts as long as a slice has frames, plus a fixed cost
-// per workgroup (tables, staging and writing its pixels, about two frames'
-// time), and a partly filled round runs its frames faster (fewer workgroups
-// share a CU's units).  Every further slice adds one partial image to read
-// back.  (Two whole rounds however short the slices got, the rule before,
-// cut 37 channels x 50 samples at N = 128 into 28 slices of two frames and a
-// ragged third round, 93 us against 55 with 12 slices; 33 x 257 at N = 64 into
-// 94 slices, 87 us against 77 with 24; 746 x 14 at N = 32 into 11, 46 us
-// against 31 with 4.)
-int default_slices(const HostPlan& hp, const KernelFootprint& f, bool matrix, int64_t n_time) {
-  constexpr double kFixed = 2.0;      // frames' time per workgroup
-  constexpr double kAlone = 0.4;      // a frame's time in a nearly empty round, of that in a full one
-  const double log2n = std::log2(static_cast<double>(hp.N)), pixels = static_cast<double>(hp.N) * hp.N;
-  // seconds of one frame of one workgroup in a full round: 10 pixels log2(N)
-  // flop per frame at the rates the two transforms reach
-  const double classes = static_cast<double>(f.per_slice) / hp.n_chan;
-  const double frame = 10.0 * pixels * log2n / (matrix ? 110e12 : 65e12) * f.resident / classes;
-  const double merge = 4.0 * pixels * hp.n_chan / 4e12 / frame;   // one more partial image, in frames
+// What a fused call takes, in microseconds, for the launch rule below: `unit` of a
+// compute unit's throughput and `alone` of one workgroup's own waits, for a frame, per
+// 10^4 N^2 log2 N of its transform (alone: per wave), step of its gather program
+// (unit: and wave) and antenna (alone: and thread); per workgroup `own` for each of a
+// thread's antennas and `shared` per pixel; `merge` per launch and partial pixel.
+struct LaunchCost {
+  double unit_work, unit_step, unit_ant, alone_work, alone_step, alone_ant, alone, own, shared, merge, merge_pixel;
+};
+constexpr LaunchCost kCostFft = {0.189, 0.00353, 0.00052, 2.09, 0.0573, 0.207, 0.594, 0.446, 0.00035, 1.5, 7e-7};
+constexpr LaunchCost kCostSplit = {0.110, 0.00255, 0.00052, 0.836, 0.0441, 0.207, 0.594, 0.446, 0.000566, 1.5, 7e-7};
+constexpr LaunchCost kCostMfma = {0.096, 0.0035, 0.0, 0.0, 0.0833, 0.0912, 0.477, 0.686, 0.000217, 0.0, 2.36e-6};
+
+// Time slices of an untuned launch in one variant, the count with the least modelled
+// time, and that time in microseconds.
+//
+// Work items (column class, channel, time slice) run in rounds of the workgroups
+// the card holds; r of them on a compute unit take, for a frame each, the larger of
+// one workgroup's own chain of waits and r times its share of the unit (added in
+// squares).  A workgroup's gains and pixels and the partial images that are merged
+// afterwards come on top.  The constants are fitted to 30 000 timings of 1200
+// random calls over all accepted sizes (2 to 4000 antennas spread out, crowded or in
+// a line, tables of 1 to 15 cells, both formats, every grid), which they meet to 9 %
+// (rms), those of the reduced-precision kernel to 3000 timings of 350 calls (15 %).  By
+// grid size the choice takes 1.005 to 1.022 of the best measured choice's time in the
+// mean, and 0.95 to 0.98 of that of the rules before (the matrix-core variant wherever
+// it fits, slices by transform time alone), which crowded arrays, many antennas and
+// very short calls misled: 4 samples of 72 channels of 849 antennas in a line at N =
+// 128 97 us in one slice on the matrix cores, 52 in four of the FFT; 78 of 189
+// channels of 811 antennas 603 and 397.
+int best_slices(const HostPlan& hp, const KernelFootprint& f, const LaunchCost& k, int cu_count, int64_t n_time,
+                double* us) {
+  const double pixels = static_cast<double>(hp.N) * hp.N, classes = static_cast<double>(f.per_slice) / hp.n_chan;
+  const double work = 1e-4 * pixels * std::log2(static_cast<double>(hp.N)) / classes;
+  const double waves = f.threads / 64.0, per_thread = static_cast<double>(hp.n_ant) / f.threads;
+  const double unit = k.unit_work * work + k.unit_step * f.steps * waves + k.unit_ant * hp.n_ant;
+  // (complex weights: two more dependent reads per step)
+  const double alone = k.alone_work * work / waves + k.alone_step * (f.complex_weights ? 1.284 : 1.0) * f.steps +
+                       k.alone_ant * per_thread + k.alone;
+  // (the matrix-core kernels' phase factors grow with the grid's side beside the pixels)
+  const double shared = k.shared * pixels / classes * (&k == &kCostFft ? 1.0 : hp.N / 128.0);
+  auto round = [&](double r, double frames) {   // a round with r workgroups to a compute unit
+    return frames * std::sqrt(alone * alone + r * unit * r * unit) + k.own * per_thread + r * shared;
+  };
+  const double cus = std::max(1, cu_count), merge = k.merge_pixel * pixels * hp.n_chan;
   const int most = static_cast<int>(std::min<int64_t>(n_time, 256));
   int best = 1;
   double least = 0.0;
   for (int sl = 1; sl <= most; ++sl) {
-    const int64_t items = static_cast<int64_t>(f.per_slice) * sl;
-    const double full = static_cast<double>(items / f.resident);
-    const double part = static_cast<double>(items % f.resident) / f.resident;
+    const int64_t items = static_cast<int64_t>(f.per_slice) * sl, full = items / f.resident, left = items % f.resident;
     const double frames = static_cast<double>((n_time + sl - 1) / sl);
-    double cost = full * (frames + kFixed) + (sl > 1 ? merge * sl : 0.0);
-    if (part > 0.0) cost += frames * (kAlone + (1.0 - kAlone) * part) + kFixed;
-    if (sl == 1 || cost < least) {
-      least = cost;
+    double t = sl > 1 ? k.merge + merge * sl : 0.0;
+    if (full > 0) t += static_cast<double>(full) * round(f.resident / cus, frames);
+    if (left > 0) t += round(std::ceil(static_cast<double>(left) / cus), frames);
+    if (sl == 1 || t < least) {
+      least = t;
       best = sl;
     }
   }
+  *us = least;
   return best;
 }
 
 // Launch configuration for n_time frames: the tuned or set choice, else the
-// plan's shape variant and the slice count above.  One work item (column
-// class, channel, time slice) per workgroup.
+// variant and slices with the least modelled time (kept for the next call of the
+// same length).  One work item per workgroup.
 LaunchConfig launch_config(moff_plan p, int64_t n_time) {
   const HostPlan& hp = p->hp;
+  if (p->slices <= 0 && p->rule_time == n_time) return p->rule;
   LaunchConfig lc{};
-  const bool brief = p->short_variant >= 0 && n_time <= p->short_time;
-  lc.variant = std::min<int>(brief ? p->short_variant : p->variant, n_variants(hp) - 1);
-  int slices = p->slices;
-  if (slices <= 0)
-    slices = default_slices(hp, footprint(p, lc.variant), is_mfma(hp) || is_split(hp, lc.variant), n_time);
-  slices = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({static_cast<int64_t>(slices), n_time, 256})));
-  lc.slices = slices;
-  lc.grid = launch_grid(hp, lc.variant, slices);
+  lc.variant = std::max(0, std::min<int>(p->variant, n_variants(hp) - 1));
+  if (p->slices > 0) {
+    lc.slices = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({static_cast<int64_t>(p->slices), n_time, 256})));
+  } else {
+    double least = 0.0;
+    lc.slices = 0;
+    for (int v = 0; v < n_variants(hp); ++v) {
+      if (p->variant >= 0 ? v != lc.variant : footprint(p, v).lds > size_t(159) * 1024) continue;
+      double us = 0.0;
+      const LaunchCost& k = is_mfma(hp) ? kCostMfma : is_split(hp, v) ? kCostSplit : kCostFft;
+      const int sl = best_slices(hp, footprint(p, v), k, p->cu_count, n_time, &us);
+      if (lc.slices == 0 || us < least) {
+        least = us;
+        lc.variant = v;
+        lc.slices = sl;
+      }
+    }
+    if (lc.slices == 0) lc.slices = 1;   // (no variant fits: the call is refused)
+  }
+  lc.grid = launch_grid(hp, lc.variant, lc.slices);
+  if (p->slices <= 0) {
+    p->rule = lc;
+    p->rule_time = n_time;
+  }
   return lc;
 }
 
@@ -737,7 +778,6 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
       up(upload(&p->d_split_ends, T.ends.data(), sizeof(uint32_t) * T.ends.size()));
       up(upload(&p->d_split_steps, T.n_steps.data(), sizeof(int32_t) * T.n_steps.size()));
       up(upload(&p->d_split_coef, T.coef.data(), sizeof(uint16_t) * T.coef.size()));
-      p->variant = static_cast<int>(hp.variants.size());
     }
     if (hipDeviceGetAttribute(&p->cu_count, hipDeviceAttributeMultiprocessorCount, hip_device) != hipSuccess)
       p->cu_count = 0;
@@ -775,33 +815,10 @@ moff_status plan_create_body(const moff_geometry* geom, int hip_device, moff_pla
         p->adj_blocks[v][w] = std::max(
             0, moff::adjoint_fused_blocks_per_cu(hp.N, static_cast<int>(v), hp.flags & MOFF_IN_CI4, w, lds));
     }
-    // A call too short to give every compute unit a frame: at N = 128 the FFT's two
-    // classes of a frame run on two of them (23.2 against 26.7 us at 1 channel x 16
-    // samples of 359 antennas, 26.8 against 31.3 at 8 x 16, 33.6 against 36.6 at 2 x
-    // 128; 40.6 against 40.9 at 24 x 16).  At N = 64 there is one class.
-    if (hp.N == 128 && hp.split.on && p->footprints[0].lds <= size_t(159) * 1024) {
-      p->short_variant = 0;
-      p->short_time = std::max(1, p->cu_count) / hp.n_chan;
-    }
-    // Where the second FFT shape at N = 256 fits its LDS, its two classes of 512
-    // threads beat the four of 256 (image 21.3 against 26.9 ms at 1024 channels x
-    // 256 samples of 350 antennas, 60 against 69 us at 4 x 23 of 578), and so
-    // they do for the gradient (7.4 against 16.7 ms at 256 x 128 of 1024).
-    // Not for an image of few antennas with complex tables, whose weights are looked
-    // up in LDS (0.95-0.99 of the first shape's speed at 6 x 30 and 64 x 9, 40-250
-    // antennas; 1.10 and more where the tables are real or the antennas 600).
-    if (hp.N == 256 && hp.variants.size() > 1 && !is_mfma(hp)) {
-      const bool few = hp.n_ant <= hp.variants[0].shape.NT;
-      if (p->footprints[1].lds <= size_t(159) * 1024 && !(few && !p->d_progw[1])) {
-        p->variant = 1;
-        // (a call of fewer than eight samples of few antennas is mostly what a
-        // workgroup does once, less with 256 threads than with 512: 30.0 against
-        // 31.2 us at 3 channels x 6 samples of 68, 36.9 against 38.6 at 20 x 3 of 100)
-        p->short_variant = few ? 0 : -1;
-        p->short_time = 7;
-      }
-      if (p->adj_blocks[1][p->adj_waves] > 0) p->adj_variant = 1;
-    }
+    // The gradient at N = 256: where the second FFT shape fits its LDS, its two classes
+    // of 512 threads beat the four of 256 (7.4 against 16.7 ms at 256 channels x 128
+    // samples of 1024 antennas).
+    if (hp.N == 256 && hp.variants.size() > 1 && !is_mfma(hp) && p->adj_blocks[1][p->adj_waves] > 0) p->adj_variant = 1;
   }
   return MOFF_OK;
 }
@@ -950,7 +967,7 @@ moff_status moff_plan_mfma_tables(moff_plan p, uint32_t* prog, uint16_t* dft, in
 moff_status moff_plan_set_config(moff_plan p, int32_t variant, int32_t slices) {
   if (!p || variant < 0 || variant >= n_variants(p->hp) || slices < 0 || slices > 256) return MOFF_ERR_INVALID_ARG;
   p->variant = variant;
-  p->short_variant = -1;
+  p->rule_time = 0;
   if (variant < static_cast<int32_t>(p->hp.variants.size())) p->adj_variant = variant;
   p->slices = slices;
   p->tuned = false;
@@ -989,13 +1006,13 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
     (void)hipFree(img);
     return MOFF_ERR_HIP;
   }
-  const int saved_v = p->variant, saved_s = p->slices, saved_short = p->short_variant;
+  const int saved_v = p->variant, saved_s = p->slices;
   const int saved_w = p->adj_waves, saved_av = p->adj_variant;
-  p->short_variant = -1;
+  p->rule_time = 0;
   const bool saved_timing = p->timing;
   p->timing = false;
   float best = 1e30f;
-  int bv = saved_v, bs = saved_s;
+  int bv = std::max(0, saved_v), bs = saved_s;
   // every timed candidate (at most 11 slice counts per shape variant)
   struct Timed {
     int v, sl;
@@ -1124,7 +1141,6 @@ moff_status moff_plan_autotune(moff_plan p, const void* E, int64_t n_time, const
   p->timing = saved_timing;
   if (result != MOFF_OK) {
     p->variant = saved_v;
-    p->short_variant = saved_short;
     p->slices = saved_s;
     p->adj_waves = saved_w;
     p->adj_variant = saved_av;

@@ -195,6 +195,8 @@ struct SplitArgs {
 };
 // grid: workgroups, a multiple of kXcds covering every (channel, slice)
 hipError_t launch_split(const SplitArgs& a, int N, bool ci4, int grid, hipStream_t st);
+// Workgroups of `lds` dynamic bytes that a compute unit holds (0: the query failed).
+int blocks_held(const void* kernel, int threads, size_t lds);
 int split_blocks_per_cu(int N, bool ci4, bool cw, bool third, int n_ant);
 
 size_t mfma_lds_bytes(int N, int n_taps, int n_ant, int prog_len, bool prog_in_lds);

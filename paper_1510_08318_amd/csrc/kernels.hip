@@ -1258,9 +1258,21 @@ int fused_blocks_per_cu(int N, int V, bool ci4, size_t lds) {
   // (both antenna variants are sized for the same waves per SIMD)
   const void* k = fused_kernel_symbol(N, V, ci4, false);
   if (!k) return 0;
-  int blocks = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, k, frame_shape(N, V).NT, lds) != hipSuccess) return 0;
-  return blocks;
+  return blocks_held(k, frame_shape(N, V).NT, lds);
+}
+
+// What the runtime's query says, but the 160 KB of LDS are handed out in pieces of
+// 1280 bytes, which the query leaves out (134 antennas at N = 32: 20 workgroups of 8
+// KB by the query, 18 in truth, and 20 slices of 253 channels ran a second round, 418
+// us against 302 with 16), the kernel's static arrays among them.
+int blocks_held(const void* kernel, int threads, size_t lds) {
+  int n = 0;
+  hipFuncAttributes attr{};
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, kernel, threads, lds) != hipSuccess ||
+      hipFuncGetAttributes(&attr, kernel) != hipSuccess)
+    return 0;
+  const size_t pieces = (lds + attr.sharedSizeBytes + 1279) / 1280;
+  return std::max(1, std::min<int>(n, static_cast<int>(size_t(160) * 1024 / 1280 / std::max<size_t>(1, pieces))));
 }
 
 hipError_t launch_reduce(const ReduceArgs& a, hipStream_t st) {

@@ -642,11 +642,7 @@ hipError_t launch_split(const SplitArgs& a, int N, bool ci4, int grid, hipStream
 
 int split_blocks_per_cu(int N, bool ci4, bool cw, bool third, int n_ant) {
   const void* k = split_symbol(N, ci4, cw, third);
-  int n = 0;
-  if (!k || hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k, split_shape(N).NW * 64, split_layout(N, n_ant).end) !=
-                hipSuccess)
-    return 0;
-  return n;
+  return k ? blocks_held(k, split_shape(N).NW * 64, split_layout(N, n_ant).end) : 0;
 }
 
 }  // namespace moff
