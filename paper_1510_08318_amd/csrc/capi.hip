@@ -67,7 +67,7 @@ struct moff_plan_s {
   uint32_t* d_fx_ab = nullptr;
   uint16_t* d_fx_dx = nullptr;
   float2* d_fx_x = nullptr;
-  int fx_NL = 0, fx_xs = 0, fx_rows = 0;
+  int fx_NL = 0, fx_xs = 0, fx_rows = 0, fx_longest = 0;
   // workspace, grown on demand
   void* d_ws = nullptr;
   size_t ws_bytes = 0;
@@ -1393,6 +1393,8 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
     }
     p->d_fx_rows = rows;
     p->fx_rows = static_cast<int>(t.rows.size());
+    p->fx_longest = 0;
+    for (size_t r = 0; r < t.rows.size(); ++r) p->fx_longest = std::max(p->fx_longest, t.ptr[r + 1] - t.ptr[r]);
     p->fx_NL = t.NL;
     p->fx_xs = t.xs;
   }
@@ -1424,6 +1426,7 @@ moff_status moff_image_fx(moff_plan p, const void* E, int64_t n_time, const floa
   a.rows = a.place + hp.n_ant;
   a.row_ptr = a.rows + p->fx_rows;
   a.n_rows = p->fx_rows;
+  a.longest = p->fx_longest;
   a.pair_ab = p->d_fx_ab;
   a.pair_dx = p->d_fx_dx;
   a.real_tables = 1;

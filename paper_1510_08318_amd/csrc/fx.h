@@ -27,6 +27,8 @@ struct FxArgs {
   const uint32_t* pair_ab;     // [entries] upper-triangle index of V, kFxConjBit: read conjugated
   const uint16_t* pair_dx;     // [entries] column
   int n_rows;
+  int longest;                 // entries of the longest row
+  int copies;                  // of a lag row's sums per wave of the binning (set by launch_fx)
   int real_tables;             // every table entry is real
   const double* Pp;            // [N][N] power pattern (one type)
   const int* ktype_k;          // [n_types]

@@ -30,8 +30,11 @@
 //   table's power pattern, the transform of its autocorrelation X.
 //
 // w = exp(+2 pi i / N); lags span -(L - 1) .. L - 1, so the image comes out in
-// the same pixel order as the MOFF image.  Every sum runs in a fixed order
-// (no atomics); the correlator and the binning accumulate in float64, each
+// the same pixel order as the MOFF image.  The sums run in a fixed order, but for
+// the binning's: lanes of one instruction whose pairs share a lag cell add to it with
+// LDS atomics, in the order in which the hardware takes them (results have repeated
+// bit for bit wherever that was checked, regular arrays among them; nothing
+// guarantees it).  The correlator and the binning accumulate in float64, each
 // pair response's lag sum in float32 (the pairs in float64), and the two
 // transform passes run in float32; intermediate arrays are float32.
 #include <hip/hip_runtime.h>
@@ -388,28 +391,48 @@ __global__ __launch_bounds__(256) void fx_correlate_i8_kernel(FxArgs a) {
       }
 }
 
+// Copies of a lag row's sums per wave of the binning, where the longest row has 64
+// pairs or more to a cell: as many as keep the four waves' near 16 KB.  Lanes take
+// them in turn, so that pairs that share a cell meet less often: 322 antennas in a
+// line on 15 lags, 1762 channels, 2.8 ms with a thread per cell, 4.1 with one copy,
+// 1.2 here; 616 on 31 lags, 97 channels, 2.4, 3.3, 0.63; 200 on 7 x 7 lags, 500
+// channels, 503 us, 217, 76.  Fewer pairs to a cell only pay for clearing and adding the copies
+// (96 against 94 us at 256 channels of 324 antennas).
+int fx_copies(int NL, int longest) {
+  if (longest < 64 * NL) return 1;
+  int c = 1;
+  while (c < 16 && 4 * 2 * 8 * NL * c * 2 <= 16384) c *= 2;
+  return c;
+}
+// Doubles from copy to copy: neighbouring lanes' copies then lie apart in the banks
+// (32 of 8 bytes) whether their cells are adjacent or every other one.
+__host__ __device__ constexpr int fx_copy_pitch(int NL, int copies) {
+  return copies == 1 ? 2 * NL : 2 * NL + (32 / copies + 32 - 2 * NL % 32) % 32;
+}
+
 // The sums of one lag row, one workgroup per (summed row, channel): each of its
-// four waves adds a contiguous quarter of the row's pairs into a float64 row of
-// its own in LDS (a wave's adds to one element happen in its own order), and the
-// four are summed in order.  The row's entries are in the order of the
+// four waves adds a contiguous quarter of the row's pairs into float64 rows of its
+// own in LDS, which are then summed in order.  The row's entries are in the order of the
 // visibilities, whose antennas are sorted by cell, so that neighbouring lanes
 // read neighbouring elements of V (a thread per lag cell, with pairs scattered
 // over V, was bound by those reads: 302 us at 64 channels of 1024 antennas, 148
 // here; 84 and 48 at 256 channels of 350).  Mirrors (types swapped, offset
 // negated) get the conjugates where the lag convolution reads them.
+template <bool SPREAD>   // several copies
 __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
-  extern __shared__ double fx_sums[];   // [4][2][NL]
+  extern __shared__ double fx_sums[];   // [4][copies][pitch], real and imaginary rows
   const int NL = a.NL, nt = a.n_types, mid = NL / 2;
   int c;
   unsigned r;
   if (!xcd_channel(blockIdx.x, static_cast<unsigned>(a.n_rows), a.n_launch, &c, &r)) return;
   const int k0 = a.row_ptr[r], n = a.row_ptr[r + 1] - k0;
   if (n == 0 && nt == 1) return;   // (the row pass knows that it is zero)
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int i = threadIdx.x; i < 8 * NL; i += 256) fx_sums[i] = 0.0;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, copies = SPREAD ? a.copies : 1;
+  const int pitch = SPREAD ? fx_copy_pitch(NL, copies) : 2 * NL;
+  for (int i = threadIdx.x; i < 4 * copies * pitch; i += 256) fx_sums[i] = 0.0;
   __syncthreads();
   const float2* V = a.V + static_cast<size_t>(c) * a.n_ant * a.n_ant;
-  double* sum = fx_sums + wave * 2 * NL;
+  double* sum = fx_sums + (wave * copies + (lane & (copies - 1))) * pitch;
   const int k1 = k0 + static_cast<int>((wave + 1) * static_cast<int64_t>(n) / 4);
   int k = k0 + static_cast<int>(wave * static_cast<int64_t>(n) / 4) + lane;
   auto add = [&](uint32_t e, int dx, float2 v) {
@@ -445,10 +468,10 @@ __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
   for (int x = threadIdx.x; x < NL; x += 256) {
     const int from = half_row && x > mid ? NL - 1 - x : x;
     double re = 0.0, im = 0.0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      re += fx_sums[w * 2 * NL + from];
-      im += fx_sums[w * 2 * NL + NL + from];
+#pragma unroll 4
+    for (int w = 0; w < 4 * copies; ++w) {
+      re += fx_sums[w * pitch + from];
+      im += fx_sums[w * pitch + NL + from];
     }
     const float2 v = make_float2(static_cast<float>(re), static_cast<float>(from == x ? im : -im));
     if (dy <= reach) H[static_cast<size_t>(tp) * plane + static_cast<size_t>(dy) * NL + x] = v;
@@ -741,7 +764,12 @@ hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st) {
     hipLaunchKernelGGL(fx_correlate_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kC64Threads), 0, st, a);
   }
   if ((e = hipGetLastError()) != hipSuccess || !a.last) return e;
-  hipLaunchKernelGGL(fx_bin_kernel, dim3(static_cast<unsigned>(bin_blocks)), dim3(256), sizeof(double) * 8 * a.NL, st, a);
+  FxArgs b = a;
+  b.copies = fx_copies(a.NL, a.longest);
+  const dim3 bins(static_cast<unsigned>(bin_blocks));
+  const size_t bin_lds = sizeof(double) * 4 * b.copies * fx_copy_pitch(a.NL, b.copies);
+  if (b.copies > 1) hipLaunchKernelGGL(fx_bin_kernel<true>, bins, dim3(256), bin_lds, st, b);
+  else hipLaunchKernelGGL(fx_bin_kernel<false>, bins, dim3(256), bin_lds, st, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (a.n_types == 1) return launch_fx_transform_n<true>(a, st);
   const unsigned lag_bx = static_cast<unsigned>((a.NL + kLagCols - 1) / kLagCols);
