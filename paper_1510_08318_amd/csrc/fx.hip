@@ -410,31 +410,46 @@ __host__ __device__ constexpr int fx_copy_pitch(int NL, int copies) {
   return copies == 1 ? 2 * NL : 2 * NL + (32 / copies + 32 - 2 * NL % 32) % 32;
 }
 
-// The sums of one lag row, one workgroup per (summed row, channel): each of its
-// four waves adds a contiguous quarter of the row's pairs into float64 rows of its
-// own in LDS, which are then summed in order.  The row's entries are in the order of the
+// The sums of one lag row per workgroup (row, channel) and, where no row has more than
+// kFxShortRow pairs, of four rows, one per wave.  The waves of a row add contiguous
+// parts of its pairs into float64 rows of their own in LDS, which are then summed
+// in order.  The row's entries are in the order of the
 // visibilities, whose antennas are sorted by cell, so that neighbouring lanes
 // read neighbouring elements of V (a thread per lag cell, with pairs scattered
 // over V, was bound by those reads: 302 us at 64 channels of 1024 antennas, 148
-// here; 84 and 48 at 256 channels of 350).  Mirrors (types swapped, offset
-// negated) get the conjugates where the lag convolution reads them.
-template <bool SPREAD>   // several copies
+// here; 84 and 48 at 256 channels of 350).  Short rows are bound by starting,
+// clearing and adding up: 1052 channels of 51 antennas of two types at N = 64, with a
+// thread per cell, a workgroup per row and a wave per row, take 46, 132 and 45 us; the
+// call of 256 channels of 128 antennas at N = 128 (rows to 1024) 58 and 50 us with four
+// waves and one to a row, of 128 antennas at N = 16 (rows to 4096) 45 and 74.  Mirrors
+// (types swapped, offset negated) get the conjugates where the lag convolution reads them.
+constexpr int kFxShortRow = 1024;
+__host__ __device__ constexpr unsigned fx_bin_groups(int n_rows, int rows) {
+  return static_cast<unsigned>((n_rows + rows - 1) / rows);
+}
+
+template <bool SPREAD, int ROWS>   // several copies; rows per workgroup (1 or 4)
 __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
   extern __shared__ double fx_sums[];   // [4][copies][pitch], real and imaginary rows
   const int NL = a.NL, nt = a.n_types, mid = NL / 2;
+  constexpr int W = 4 / ROWS;   // waves of a row
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, copies = SPREAD ? a.copies : 1;
   int c;
   unsigned r;
-  if (!xcd_channel(blockIdx.x, static_cast<unsigned>(a.n_rows), a.n_launch, &c, &r)) return;
-  const int k0 = a.row_ptr[r], n = a.row_ptr[r + 1] - k0;
-  if (n == 0 && nt == 1) return;   // (the row pass knows that it is zero)
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, copies = SPREAD ? a.copies : 1;
+  if (!xcd_channel(blockIdx.x, fx_bin_groups(a.n_rows, ROWS), a.n_launch, &c, &r)) return;
+  r = r * ROWS + wave / W;
+  const bool in = ROWS == 1 || r < static_cast<unsigned>(a.n_rows);   // (a wave beyond the last row adds nothing)
+  const int k0 = in ? a.row_ptr[r] : 0, n = in ? a.row_ptr[r + 1] - k0 : 0;
+  const bool empty = n == 0 && nt == 1;   // (the row pass knows that it is zero)
+  if (ROWS == 1 && empty) return;
   const int pitch = SPREAD ? fx_copy_pitch(NL, copies) : 2 * NL;
   for (int i = threadIdx.x; i < 4 * copies * pitch; i += 256) fx_sums[i] = 0.0;
   __syncthreads();
   const float2* V = a.V + static_cast<size_t>(c) * a.n_ant * a.n_ant;
   double* sum = fx_sums + (wave * copies + (lane & (copies - 1))) * pitch;
-  const int k1 = k0 + static_cast<int>((wave + 1) * static_cast<int64_t>(n) / 4);
-  int k = k0 + static_cast<int>(wave * static_cast<int64_t>(n) / 4) + lane;
+  const int part = wave % W;
+  const int k1 = k0 + static_cast<int>((part + 1) * static_cast<int64_t>(n) / W);
+  int k = k0 + static_cast<int>(part * static_cast<int64_t>(n) / W) + lane;
   auto add = [&](uint32_t e, int dx, float2 v) {
     unsafeAtomicAdd(sum + dx, static_cast<double>(v.x));
     unsafeAtomicAdd(sum + NL + dx, static_cast<double>((e & kFxConjBit) ? -v.y : v.y));
@@ -459,19 +474,21 @@ __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
     add(e, a.pair_dx[k], V[e & ~kFxConjBit]);
   }
   __syncthreads();
+  if (ROWS > 1 && (!in || empty)) return;
   const int tp = a.rows[r] / NL, dy = a.rows[r] % NL, p = tp / nt, q = tp % nt;
   const bool half_row = p == q && dy == mid;   // only columns up to the zero lag were summed
   const size_t plane = static_cast<size_t>(nt == 1 ? a.L : NL) * NL;
   float2* H = a.H + static_cast<size_t>(c) * nt * nt * plane;
   // rows that the lag convolution reads: up to the zero lag and the responses' reach
   const int reach = mid + a.xs;
-  for (int x = threadIdx.x; x < NL; x += 256) {
+  const double* row = fx_sums + wave / W * W * copies * pitch;
+  for (int x = threadIdx.x % (64 * W); x < NL; x += 64 * W) {
     const int from = half_row && x > mid ? NL - 1 - x : x;
     double re = 0.0, im = 0.0;
 #pragma unroll 4
-    for (int w = 0; w < 4 * copies; ++w) {
-      re += fx_sums[w * pitch + from];
-      im += fx_sums[w * pitch + NL + from];
+    for (int w = 0; w < W * copies; ++w) {
+      re += row[w * pitch + from];
+      im += row[w * pitch + NL + from];
     }
     const float2 v = make_float2(static_cast<float>(re), static_cast<float>(from == x ? im : -im));
     if (dy <= reach) H[static_cast<size_t>(tp) * plane + static_cast<size_t>(dy) * NL + x] = v;
@@ -750,7 +767,10 @@ hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st) {
   const size_t nt = static_cast<size_t>((a.n_ant + kFxTile - 1) / kFxTile);
   const int64_t steps = (a.t1 - a.t0 + fx_step(ci4) - 1) / fx_step(ci4);
   const size_t blocks = xcd_grid(nt * (nt + 1) / 2, a.n_launch);
-  const size_t bin_blocks = xcd_grid(static_cast<size_t>(a.n_rows), a.n_launch);
+  FxArgs b = a;
+  b.copies = fx_copies(a.NL, a.longest);
+  const int bin_rows = b.copies == 1 && a.longest <= kFxShortRow ? 4 : 1;
+  const size_t bin_blocks = xcd_grid(fx_bin_groups(a.n_rows, bin_rows), a.n_launch);
   if (steps < 1 || steps > 0x7FFFFFFF || blocks > 0x7FFFFFFFu || bin_blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
   const dim3 stage(static_cast<unsigned>(steps), static_cast<unsigned>(nt), a.n_launch);
   hipError_t e;
@@ -764,12 +784,11 @@ hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st) {
     hipLaunchKernelGGL(fx_correlate_kernel, dim3(static_cast<unsigned>(blocks)), dim3(kC64Threads), 0, st, a);
   }
   if ((e = hipGetLastError()) != hipSuccess || !a.last) return e;
-  FxArgs b = a;
-  b.copies = fx_copies(a.NL, a.longest);
   const dim3 bins(static_cast<unsigned>(bin_blocks));
   const size_t bin_lds = sizeof(double) * 4 * b.copies * fx_copy_pitch(a.NL, b.copies);
-  if (b.copies > 1) hipLaunchKernelGGL(fx_bin_kernel<true>, bins, dim3(256), bin_lds, st, b);
-  else hipLaunchKernelGGL(fx_bin_kernel<false>, bins, dim3(256), bin_lds, st, b);
+  if (bin_rows > 1) hipLaunchKernelGGL((fx_bin_kernel<false, 4>), bins, dim3(256), bin_lds, st, b);
+  else if (b.copies > 1) hipLaunchKernelGGL((fx_bin_kernel<true, 1>), bins, dim3(256), bin_lds, st, b);
+  else hipLaunchKernelGGL((fx_bin_kernel<false, 1>), bins, dim3(256), bin_lds, st, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (a.n_types == 1) return launch_fx_transform_n<true>(a, st);
   const unsigned lag_bx = static_cast<unsigned>((a.NL + kLagCols - 1) / kLagCols);
