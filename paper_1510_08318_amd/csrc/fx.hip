@@ -398,10 +398,18 @@ __global__ __launch_bounds__(256) void fx_correlate_i8_kernel(FxArgs a) {
 // 1.2 here; 616 on 31 lags, 97 channels, 2.4, 3.3, 0.63; 200 on 7 x 7 lags, 500
 // channels, 503 us, 217, 76.  Fewer pairs to a cell only pay for clearing and adding the copies
 // (96 against 94 us at 256 channels of 324 antennas).
-int fx_copies(int NL, int longest) {
+//
+// Longer rows (256 pairs or more to a cell, which lines of antennas reach) pay for more:
+// near 32 KB, and near 64 KB where the launch has too few of them to share a unit's
+// LDS.  A line of 1088 antennas, 285 channels: 9.0 ms with 16 KB, 4.5 with 32 and 2.7
+// with 64 at N = 256 (143 long rows to a pass), 9.4, 3.7 and 2.5 at N = 128; 600 at N = 64, 3.3, 2.1
+// and 2.6 at 1000 channels, 1.12, 0.36 and 0.20 at 97.  (900 antennas
+// in one cell of N = 64, 32 channels, lose by it: 110, 113 and 121 us.)
+int fx_copies(int NL, int longest, int64_t groups) {
   if (longest < 64 * NL) return 1;
+  const int lds = longest < 256 * NL ? 16384 : groups > 512 ? 32768 : 65536;
   int c = 1;
-  while (c < 16 && 4 * 2 * 8 * NL * c * 2 <= 16384) c *= 2;
+  while (c < 16 && 4 * 2 * 8 * NL * c * 2 <= lds) c *= 2;
   return c;
 }
 // Doubles from copy to copy: neighbouring lanes' copies then lie apart in the banks
@@ -768,7 +776,9 @@ hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st) {
   const int64_t steps = (a.t1 - a.t0 + fx_step(ci4) - 1) / fx_step(ci4);
   const size_t blocks = xcd_grid(nt * (nt + 1) / 2, a.n_launch);
   FxArgs b = a;
-  b.copies = fx_copies(a.NL, a.longest);
+  // (rows as long as the longest that the pairs would fill)
+  const int64_t full_rows = (static_cast<int64_t>(a.n_ant) * a.n_ant / 2 + a.longest) / std::max(a.longest, 1);
+  b.copies = fx_copies(a.NL, a.longest, full_rows * a.n_launch);
   const int bin_rows = b.copies == 1 && a.longest <= kFxShortRow ? 4 : 1;
   const size_t bin_blocks = xcd_grid(fx_bin_groups(a.n_rows, bin_rows), a.n_launch);
   if (steps < 1 || steps > 0x7FFFFFFF || blocks > 0x7FFFFFFFu || bin_blocks > 0x7FFFFFFFu) return hipErrorInvalidValue;
@@ -787,8 +797,13 @@ hipError_t launch_fx(const FxArgs& a, bool ci4, hipStream_t st) {
   const dim3 bins(static_cast<unsigned>(bin_blocks));
   const size_t bin_lds = sizeof(double) * 4 * b.copies * fx_copy_pitch(a.NL, b.copies);
   if (bin_rows > 1) hipLaunchKernelGGL((fx_bin_kernel<false, 4>), bins, dim3(256), bin_lds, st, b);
-  else if (b.copies > 1) hipLaunchKernelGGL((fx_bin_kernel<true, 1>), bins, dim3(256), bin_lds, st, b);
-  else hipLaunchKernelGGL((fx_bin_kernel<false, 1>), bins, dim3(256), bin_lds, st, b);
+  else if (b.copies > 1) {
+    auto k = fx_bin_kernel<true, 1>;
+    if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(k), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 static_cast<int>(bin_lds))) != hipSuccess)
+      return e;
+    hipLaunchKernelGGL(k, bins, dim3(256), bin_lds, st, b);
+  } else hipLaunchKernelGGL((fx_bin_kernel<false, 1>), bins, dim3(256), bin_lds, st, b);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (a.n_types == 1) return launch_fx_transform_n<true>(a, st);
   const unsigned lag_bx = static_cast<unsigned>((a.NL + kLagCols - 1) / kLagCols);
