@@ -445,7 +445,7 @@ __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
   int c;
   unsigned r;
   if (!xcd_channel(blockIdx.x, fx_bin_groups(a.n_rows, ROWS), a.n_launch, &c, &r)) return;
-  r = r * ROWS + wave / W;
+  if (ROWS > 1) r = r * ROWS + wave;
   const bool in = ROWS == 1 || r < static_cast<unsigned>(a.n_rows);   // (a wave beyond the last row adds nothing)
   const int k0 = in ? a.row_ptr[r] : 0, n = in ? a.row_ptr[r + 1] - k0 : 0;
   const bool empty = n == 0 && nt == 1;   // (the row pass knows that it is zero)
@@ -455,7 +455,7 @@ __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
   __syncthreads();
   const float2* V = a.V + static_cast<size_t>(c) * a.n_ant * a.n_ant;
   double* sum = fx_sums + (wave * copies + (lane & (copies - 1))) * pitch;
-  const int part = wave % W;
+  const int part = ROWS > 1 ? 0 : wave;
   const int k1 = k0 + static_cast<int>((part + 1) * static_cast<int64_t>(n) / W);
   int k = k0 + static_cast<int>(part * static_cast<int64_t>(n) / W) + lane;
   auto add = [&](uint32_t e, int dx, float2 v) {
@@ -489,8 +489,8 @@ __global__ __launch_bounds__(256) void fx_bin_kernel(FxArgs a) {
   float2* H = a.H + static_cast<size_t>(c) * nt * nt * plane;
   // rows that the lag convolution reads: up to the zero lag and the responses' reach
   const int reach = mid + a.xs;
-  const double* row = fx_sums + wave / W * W * copies * pitch;
-  for (int x = threadIdx.x % (64 * W); x < NL; x += 64 * W) {
+  const double* row = fx_sums + (ROWS > 1 ? wave * pitch : 0);
+  for (int x = ROWS > 1 ? lane : threadIdx.x; x < NL; x += 64 * W) {
     const int from = half_row && x > mid ? NL - 1 - x : x;
     double re = 0.0, im = 0.0;
 #pragma unroll 4
