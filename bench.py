@@ -49,91 +49,107 @@ PEAK_MFMA_16BIT_TFLOPS = 2500.0   # MI355X dense fp16 / bf16 matrix peak (spec s
 # the current sources.  Keyed by (workload, precision, shape variant,
 # workgroups); valid only for the kernel sources they were measured on,
 # identified by TRAFFIC_SOURCES_SHA (KERNEL_SOURCES).
-TRAFFIC_SOURCES_SHA = "e4f70da47563606b"
+TRAFFIC_SOURCES_SHA = "f0647062ce221256"
 FETCH_SCALE, WRITE_SCALE = 262144.0 / 131093.0, 1.0
 TRAFFIC_KIB = {
-    (2, "f32", 0, 256): (25802, 57728),
-    (2, "f32", 0, 512): (33537, 49922),
-    (2, "f32", 0, 1024): (17279, 34308),
-    (2, "f32", 0, 2048): (17534, 68562),
-    (2, "f32", 0, 3072): (17787, 102787),
-    (2, "f32", 0, 4096): (17891, 137051),
-    (2, "f32", 0, 8192): (17492, 273957),
-    (2, "f32", 0, 16384): (17334, 548572),
-    (2, "f32", 1, 128): (25488, 57344),
-    (2, "f32", 1, 256): (33167, 49154),
-    (2, "f32", 1, 512): (16802, 32772),
-    (2, "f32", 1, 1024): (16905, 65544),
-    (2, "f32", 1, 1536): (16820, 98316),
-    (2, "f32", 1, 2048): (16871, 131088),
-    (2, "f32", 1, 4096): (16931, 262176),
-    (2, "f32", 1, 8192): (17274, 524352),
-    (3, "f32", 0, 4096): (54035, 262144),
-    (3, "f32", 0, 8192): (50060, 524304),
-    (3, "f32", 0, 16384): (50853, 1048609),
-    (3, "f32", 0, 32768): (52323, 2097217),
-    (3, "f32", 0, 65536): (58021, 4194433),
-    (3, "f32", 0, 131072): (73561, 8388866),
-    (3, "f32", 0, 262144): (1486197, 16777747),
-    (3, "f32", 1, 2048): (70928, 286676),
-    (3, "f32", 1, 4096): (60810, 573356),
-    (3, "f32", 1, 8192): (102210, 1146896),
-    (3, "f32", 1, 16384): (163573, 2293809),
-    (3, "f32", 1, 32768): (319042, 4587654),
-    (3, "f32", 1, 65536): (656732, 9175348),
-    (3, "f32", 1, 131072): (1296538, 18350714),
+    (2, "f32", 0, 256): (25728, 57600),
+    (2, "f32", 0, 512): (33402, 49666),
+    (2, "f32", 0, 1024): (17012, 33796),
+    (2, "f32", 0, 2048): (17012, 67592),
+    (2, "f32", 0, 3072): (17013, 101388),
+    (2, "f32", 0, 4096): (17012, 135156),
+    (2, "f32", 0, 8192): (17011, 270194),
+    (2, "f32", 0, 16384): (17010, 540524),
+    (2, "f32", 1, 128): (25496, 57344),
+    (2, "f32", 1, 256): (33155, 49154),
+    (2, "f32", 1, 512): (16806, 32772),
+    (2, "f32", 1, 1024): (16844, 65544),
+    (2, "f32", 1, 1536): (16808, 98316),
+    (2, "f32", 1, 2048): (16829, 131088),
+    (2, "f32", 1, 4096): (16906, 262176),
+    (2, "f32", 1, 8192): (17235, 524352),
+    (2, "f32", 2, 128): (26650, 59908),
+    (2, "f32", 2, 256): (35655, 54512),
+    (2, "f32", 2, 512): (20848, 43028),
+    (2, "f32", 2, 1024): (25525, 86049),
+    (2, "f32", 2, 1536): (30112, 129078),
+    (2, "f32", 2, 2048): (34811, 172096),
+    (2, "f32", 2, 4096): (48623, 344141),
+    (2, "f32", 2, 8192): (80034, 687997),
+    (3, "f32", 0, 4096): (53971, 262144),
+    (3, "f32", 0, 8192): (50019, 524304),
+    (3, "f32", 0, 16384): (50766, 1048609),
+    (3, "f32", 0, 32768): (52340, 2097217),
+    (3, "f32", 0, 65536): (57424, 4194433),
+    (3, "f32", 0, 131072): (65074, 8388865),
+    (3, "f32", 0, 262144): (1460322, 16777781),
+    (3, "f32", 1, 2048): (66373, 262144),
+    (3, "f32", 1, 4096): (52436, 524304),
+    (3, "f32", 1, 8192): (65939, 1048608),
+    (3, "f32", 1, 16384): (123549, 2097217),
+    (3, "f32", 1, 32768): (259615, 4194449),
+    (3, "f32", 1, 65536): (531062, 8388919),
+    (3, "f32", 1, 131072): (1047245, 16777851),
     (4, "bf16", 0, 128): (129004, 8192),
-    (4, "bf16", 0, 256): (128441, 16393),
+    (4, "bf16", 0, 256): (128440, 16393),
     (4, "bf16", 0, 512): (128653, 32785),
     (4, "bf16", 0, 768): (128866, 49177),
-    (4, "bf16", 0, 1024): (129079, 65569),
-    (4, "bf16", 0, 2048): (129616, 131136),
-    (4, "bf16", 0, 4096): (129734, 262272),
-    (4, "bf16", 0, 8192): (130841, 524546),
+    (4, "bf16", 0, 1024): (129078, 65569),
+    (4, "bf16", 0, 2048): (129612, 131136),
+    (4, "bf16", 0, 4096): (129720, 262272),
+    (4, "bf16", 0, 8192): (131067, 524544),
     (4, "f16", 0, 128): (129019, 8192),
-    (4, "f16", 0, 256): (128460, 16392),
-    (4, "f16", 0, 512): (128672, 32784),
-    (4, "f16", 0, 768): (128885, 49177),
-    (4, "f16", 0, 1024): (129098, 65569),
-    (4, "f16", 0, 2048): (129633, 131137),
+    (4, "f16", 0, 256): (128459, 16392),
+    (4, "f16", 0, 512): (128672, 32785),
+    (4, "f16", 0, 768): (128884, 49176),
+    (4, "f16", 0, 1024): (129097, 65569),
+    (4, "f16", 0, 2048): (129634, 131136),
     (4, "f16", 0, 4096): (129757, 262272),
-    (4, "f16", 0, 8192): (130846, 524544),
-    (4, "f32", 0, 256): (137860, 57728),
-    (4, "f32", 0, 512): (145601, 49922),
-    (4, "f32", 0, 1024): (129344, 34308),
-    (4, "f32", 0, 2048): (129634, 68616),
-    (4, "f32", 0, 3072): (129903, 102924),
-    (4, "f32", 0, 4096): (130175, 137232),
-    (4, "f32", 0, 8192): (131174, 274464),
-    (4, "f32", 0, 16384): (133180, 548853),
-    (4, "f32", 1, 128): (137537, 57344),
-    (4, "f32", 1, 256): (145210, 49154),
-    (4, "f32", 1, 512): (128915, 32772),
-    (4, "f32", 1, 1024): (129386, 65544),
-    (4, "f32", 1, 1536): (129854, 98316),
-    (4, "f32", 1, 2048): (130301, 131088),
-    (4, "f32", 1, 4096): (131640, 262176),
-    (4, "f32", 1, 8192): (130414, 524352),
-    (5, "f32", 0, 1024): (158456, 65536),
-    (5, "f32", 0, 2048): (150892, 131080),
-    (5, "f32", 0, 4096): (160215, 262160),
-    (5, "f32", 0, 8192): (143492, 524320),
-    (5, "f32", 0, 16384): (151870, 1048640),
-    (5, "f32", 0, 32768): (168397, 2097280),
-    (5, "f32", 0, 65536): (201060, 4194560),
-    (5, "f32", 1, 512): (150456, 79360),
-    (5, "f32", 1, 1024): (152983, 158729),
-    (5, "f32", 1, 2048): (174530, 317458),
-    (5, "f32", 1, 4096): (217594, 634913),
-    (5, "f32", 1, 8192): (303225, 1269824),
-    (5, "f32", 1, 16384): (474974, 2539648),
-    (5, "f32", 1, 32768): (818068, 5079296),
+    (4, "f16", 0, 8192): (131029, 524544),
+    (4, "f32", 0, 256): (137792, 57600),
+    (4, "f32", 0, 512): (145468, 49666),
+    (4, "f32", 0, 1024): (129084, 33796),
+    (4, "f32", 0, 2048): (129120, 67592),
+    (4, "f32", 0, 3072): (129132, 101388),
+    (4, "f32", 0, 4096): (129150, 135184),
+    (4, "f32", 0, 8192): (129122, 270368),
+    (4, "f32", 0, 16384): (129082, 540736),
+    (4, "f32", 1, 128): (137517, 57344),
+    (4, "f32", 1, 256): (145192, 49154),
+    (4, "f32", 1, 512): (128857, 32772),
+    (4, "f32", 1, 1024): (129197, 65544),
+    (4, "f32", 1, 1536): (129537, 98316),
+    (4, "f32", 1, 2048): (129872, 131088),
+    (4, "f32", 1, 4096): (130653, 262176),
+    (4, "f32", 1, 8192): (129733, 524352),
+    (4, "f32", 2, 128): (139218, 61060),
+    (4, "f32", 2, 256): (148015, 56702),
+    (4, "f32", 2, 512): (133933, 48361),
+    (4, "f32", 2, 1024): (139231, 96330),
+    (4, "f32", 2, 1536): (144385, 144463),
+    (4, "f32", 2, 2048): (149589, 192558),
+    (4, "f32", 2, 4096): (170806, 385082),
+    (4, "f32", 2, 8192): (215593, 768368),
+    (5, "f32", 0, 1024): (159082, 65536),
+    (5, "f32", 0, 2048): (151657, 131080),
+    (5, "f32", 0, 4096): (163372, 262160),
+    (5, "f32", 0, 8192): (144458, 524320),
+    (5, "f32", 0, 16384): (153559, 1048640),
+    (5, "f32", 0, 32768): (172871, 2097280),
+    (5, "f32", 0, 65536): (201453, 4194560),
+    (5, "f32", 1, 512): (146591, 68608),
+    (5, "f32", 1, 1024): (145308, 137225),
+    (5, "f32", 1, 2048): (159168, 274449),
+    (5, "f32", 1, 4096): (186782, 548896),
+    (5, "f32", 1, 8192): (241354, 1097792),
+    (5, "f32", 1, 16384): (350626, 2195584),
+    (5, "f32", 1, 32768): (567286, 4391168),
 }
 
 
 # Sources that define the timed kernels and their tables (not the launch logic).
 KERNEL_SOURCES = ("dft.h", "frame.h", "ingest.h", "kernels.h", "kernels.hip", "mfma.hip", "plan.cpp", "plan.h",
-                  "shape.h")
+                  "shape.h", "split.hip", "split_shape.h", "split_tables.cpp")
 
 
 def library_sources_sha():
